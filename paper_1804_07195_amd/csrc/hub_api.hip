@@ -221,6 +221,13 @@ class Server {
           t->state = 2;
           continue;
         }
+        if (engine_->join_gangs({&s}, s.owned) != hipSuccess) {
+          engine_->remove(&s);
+          t->status = HUB_ERR_HIP;
+          t->info = hub_solve_info{};
+          t->state = 2;
+          continue;
+        }
         t->state = 1;
         running_.push_back(t);
       }
@@ -475,32 +482,27 @@ namespace api {
 hub_status run_solves(hub_ctx* ctx, std::vector<System>& sys, const hub_solve_opts& o, hipStream_t stream) {
   Engine* eng = engine_for(ctx, stream);
   if (!eng) return HUB_ERR_OOM;
-  // the phase e^{i phi} once per distinct phi (complex64 too for the mixed solver, and the
-  // (cos, sin) table of the single-workgroup CG for small systems)
+  // the phase e^{i phi} once per distinct phi (the float angle too for the mixed solver)
   const bool want32 = o.solver == HUB_FGMRES_MIXED;
   struct Phase {
     double2* p64;
     float* p32;
-    float2* cs32;
   };
   std::map<const double*, Phase> phase;
   std::vector<void*> owned;
   hub_status result = HUB_OK;
   for (System& sy : sys) {
     if (phase.count(sy.phi)) continue;
-    const bool wantcs = want32 && wg_of(sy.g.n);
     double2* p64 = (double2*)ctx->pool->alloc((size_t)sy.g.n * 16, stream);
     float* p32 = want32 ? (float*)ctx->pool->alloc((size_t)sy.g.n * 4, stream) : nullptr;
-    float2* pcs = wantcs ? (float2*)ctx->pool->alloc((size_t)sy.g.n * 8, stream) : nullptr;
     if (p64) owned.push_back(p64);
     if (p32) owned.push_back(p32);
-    if (pcs) owned.push_back(pcs);
-    if (!p64 || (want32 && !p32) || (wantcs && !pcs)) {
+    if (!p64 || (want32 && !p32)) {
       result = fail(HUB_ERR_OOM, "workspace for the phase of phi");
       break;
     }
-    phase[sy.phi] = {p64, p32, pcs};
-    const hipError_t e = launch_phase(sy.phi, p64, p32, sy.g.n, stream, pcs);
+    phase[sy.phi] = {p64, p32};
+    const hipError_t e = launch_phase(sy.phi, p64, p32, sy.g.n, stream);
     if (e != hipSuccess) {
       result = hip_fail(e, "phase");
       break;
@@ -511,7 +513,6 @@ hub_status run_solves(hub_ctx* ctx, std::vector<System>& sys, const hub_solve_op
     if (result != HUB_OK) break;
     sy.ph64 = phase[sy.phi].p64;
     sy.ph32 = phase[sy.phi].p32;
-    sy.cs32 = phase[sy.phi].cs32;
     sy.opts = o;
     const Engine::AddResult ar = eng->add(&sy);
     if (ar != Engine::ADD_OK) {
@@ -519,6 +520,12 @@ hub_status run_solves(hub_ctx* ctx, std::vector<System>& sys, const hub_solve_op
       break;
     }
     ++added;
+  }
+  if (result == HUB_OK) {
+    std::vector<System*> all;
+    for (System& sy : sys) all.push_back(&sy);
+    const hipError_t e = eng->join_gangs(all, owned);
+    if (e != hipSuccess) result = hip_fail(e, "solve");
   }
   if (result == HUB_OK) {
     for (;;) {

@@ -60,9 +60,10 @@ class Pool {
 
 // Block length (CG iterations between flag reads) near a system's expected end.
 constexpr int kTailBlock = 4;
-// Block length when only single-workgroup systems iterate (their kernel leaves the
-// block at convergence).
-constexpr int kWgBlockIters = 48;
+// Iterations of a gang launch (a gang leaves its launch at convergence) and meetings in a
+// row that a gang may miss before its system goes on with the tiled kernels.
+constexpr int kGangIters = 128;
+constexpr int kGangMisses = 3;
 
 // Host-side state of one linear system (M M^dagger + mu2) x = b.
 struct System {
@@ -72,7 +73,6 @@ struct System {
   const double* phi = nullptr;
   const double2* ph64 = nullptr;  // (cos phi, sin phi); computed on add if NULL
   const float* ph32 = nullptr;    // reduced float phi (mixed solver); computed on add if NULL
-  const float2* cs32 = nullptr;   // (cos, sin) of ph32 (small mixed-solver systems); computed on add if NULL
   const double2* b = nullptr;
   double2* x = nullptr;
   hub_solve_opts opts{};
@@ -90,7 +90,10 @@ struct System {
   int enq = 0;          // CG iterations enqueued since the last CG setup
   int gen = 0;          // number of CG setups so far (tags in-flight blocks)
   int pred = 0;         // iterations of the system's previous CG run (0: none yet)
-  bool wg = false;      // CG iterations in the single-workgroup kernel (small systems)
+  bool gang = false;    // CG iterations by a gang of workgroups (desc.gang, desc.gang_mem)
+  unsigned gang_tag = 0, gang_seq = 0;  // exchange tags handed out, launches so far
+  int gang_missed = 0;  // meetings missed in a row
+  bool gang_leave = false;  // to the tiled kernels once no launch of the gang is in flight
   double bnorm = 0.0, err = 0.0, wnorm = 0.0, rnorm_cycle = 0.0, bb = -1.0;
   std::vector<std::complex<double>> H;  // (m+1) x m, column-major
   std::vector<void*> owned;             // workspace blocks of this system
@@ -112,6 +115,10 @@ class Engine {
   // the workspace is over budget; ADD_HIP: a HIP call failed while joining.
   enum AddResult { ADD_OK = 0, ADD_NO_ROOM = 1, ADD_HIP = 2 };
   AddResult add(System* s);
+  // Let the systems of v that have just been added iterate by gangs, where their lattice
+  // has a cut and the exchange memory (one block for all of v, appended to `owned`) fits in
+  // the budget; the others keep the tiled kernels.
+  hipError_t join_gangs(const std::vector<System*>& v, std::vector<void*>& owned);
   // Remove a finished system and return its workspace to the pool.
   void remove(System* s);
   // Advance every system: host-side phases, then one block of CG iterations.
@@ -129,7 +136,7 @@ class Engine {
     double bytes = 0.0;
   };
   void set_profiling(bool on);
-  // [single][kernel]: stage 1, stage 2 of the tiled CG; the single-workgroup CG block
+  // [single][kernel]: stage 1, stage 2 of the tiled CG; the gang launches
   KernelStat stat[2][3];
   // Serving epilogue of a converged system: S = Re chi^dagger x (host), and
   // dS/dphi into dSdphi (device, may be null).  Synchronises the stream.
@@ -146,10 +153,9 @@ class Engine {
     bool single = false;
     int k = 0;
     int buf = 0;
-    std::vector<System*> v;             // grouped by tile class, then the single-workgroup systems
+    std::vector<System*> v;             // grouped by tile class, then the gangs' systems
     std::vector<int> cls_end;           // end of each tile class in v
-    int nwg = 0;                        // single-workgroup systems at the end of v
-    std::vector<hipEvent_t> wgev;       // start/stop of their launch (profiling)
+    std::vector<hipEvent_t> gev;        // start/stop of the gang launches (profiling)
     std::vector<int> gen;               // System::gen of each system at enqueue
     std::vector<std::vector<int>> its;  // iteration index per launch and system (profiling)
     std::vector<hipEvent_t> kev;        // kernel start/stop events (profiling)
@@ -158,6 +164,11 @@ class Engine {
   hipError_t launch_block(bool single, bool& launched);
   hipError_t finish_block(Block& b);
   hipError_t wait_block(unsigned seq);
+  hipError_t launch_gangs(const std::vector<System*>& v, bool single, Block& b);
+  size_t gang_entry(GangList& G, System* s, bool single) const;
+  hipError_t leave_gangs(bool single);
+  hipError_t take_event(std::vector<hipEvent_t>& dst);
+  GangCut cut_of(const Geom& g, bool single);
   hipError_t read_scal(const std::vector<System*>& v);
   // Descriptors and FGMRES update coefficients go to pinned staging rows (slot-indexed)
   // and reach the device in one copy per kind: flush_desc at the start of every step,
@@ -192,6 +203,8 @@ class Engine {
   Scal* h_flags_ = nullptr;             // host-coherent, 4 buffers x kMaxSys, then h_blk_flag_
   unsigned* h_blk_flag_ = nullptr;      // sequence number of the last block whose flags were written
   unsigned blk_seq_ = 0;
+  GangCut cut_[2] = {};                 // the last cut computed per precision, of extents cut_ext_
+  int cut_ext_[2][3] = {};
   int next_buf_[2] = {0, 0};
 };
 

@@ -277,8 +277,7 @@ size_t Engine::workspace_bytes(const Geom& g, const hub_solve_opts& o) {
   // (FP64 phase n * 16; the mixed solver's float angle n * 4)
   if (!is_fgmres(o)) return 5 * Pool::rounded(n * 16) + part;
   const int m = o.restart_m;
-  // small systems also keep the (cos, sin) table of the single-workgroup CG
-  return (size_t)(m + 4) * Pool::rounded(n * 16) + (size_t)(m + 4 + (wg_of(g.n) ? 1 : 0)) * Pool::rounded(n * 8) +
+  return (size_t)(m + 4) * Pool::rounded(n * 16) + (size_t)(m + 4) * Pool::rounded(n * 8) +
          Pool::rounded(n * 4) + part;
 }
 
@@ -348,22 +347,18 @@ Engine::AddResult Engine::add(System* s) {
   // the phase e^{i phi} of the solver kernels (shared with other systems when the
   // caller precomputed it)
   const bool want32 = is_fgmres(s->opts);
-  const bool wantcs = want32 && wg_of(s->g.n);
-  if (ok && (!s->ph64 || (want32 && !s->ph32) || (wantcs && !s->cs32))) {
+  if (ok && (!s->ph64 || (want32 && !s->ph32))) {
     double2* p64 = (double2*)get(n * 16);
     float* p32 = want32 ? (float*)get(n * 4) : nullptr;
-    float2* pcs = wantcs ? (float2*)get(n * 8) : nullptr;
-    ok = ok && p64 && (!want32 || p32) && (!wantcs || pcs);
-    if (ok && launch_phase(s->phi, p64, p32, (int)n, st_, pcs) != hipSuccess) ok = hip_ok = false;
+    ok = ok && p64 && (!want32 || p32);
+    if (ok && launch_phase(s->phi, p64, p32, (int)n, st_) != hipSuccess) ok = hip_ok = false;
     if (ok) {
       s->ph64 = p64;
       s->ph32 = p32;
-      s->cs32 = pcs;
     }
   }
   d.ph64 = s->ph64;
   d.ph32 = s->ph32;
-  d.cs32 = s->cs32;
   if (!ok) {
     pool_->release_all(s->owned, st_);
     s->owned.clear();
@@ -371,13 +366,69 @@ Engine::AddResult Engine::add(System* s) {
     return hip_ok ? ADD_NO_ROOM : ADD_HIP;
   }
   s->slot = slot;
-  s->wg = wantcs;
   s->phase = PH_NEW;
   s->done = false;
   s->info = hub_solve_info{};
   slots_[slot] = s;
   upload_desc(s);
   return ADD_OK;
+}
+
+GangCut Engine::cut_of(const Geom& g, bool single) {
+  const int k = single ? 1 : 0;
+  int* e = cut_ext_[k];
+  if (e[0] != g.L1 || e[1] != g.L2 || e[2] != g.Nt) {
+    cut_[k] = single ? gang_cut<float>(g.L1, g.L2, g.Nt) : gang_cut<double>(g.L1, g.L2, g.Nt);
+    e[0] = g.L1, e[1] = g.L2, e[2] = g.Nt;
+  }
+  return cut_[k];
+}
+
+hipError_t Engine::join_gangs(const std::vector<System*>& v, std::vector<void*>& owned) {
+  auto exch = [](const GangCut& c, bool single) {
+    return single ? gang_exch_words<float>(c.g, c.nslot) : gang_exch_words<double>(c.g, c.nslot);
+  };
+  auto state = [](const GangCut& c, bool single) {
+    return single ? gang_state_words<float>(c.g, c.cls) : gang_state_words<double>(c.g, c.cls);
+  };
+  size_t words = 0, clear = 0;
+  for (System* s : v) {
+    const bool single = is_fgmres(s->opts);
+    const GangCut c = cut_of(s->g, single);
+    s->desc.gang = c;
+    s->desc.gang_mem = s->desc.gang_state = nullptr;
+    if (c.g > 1) clear += exch(c, single);
+    if (c.g > 0) words += state(c, single);
+  }
+  unsigned long long* mem = nullptr;
+  if (words > 0) {
+    mem = (unsigned long long*)pool_->alloc((clear + words) * 8, st_);
+    if (mem) {
+      owned.push_back(mem);
+      if (clear > 0) HUB_TRY(launch_gang_clear(mem, clear, st_));
+    } else {
+      set_error("");  // over budget: these systems keep the tiled kernels
+    }
+  }
+  unsigned long long* st = mem + clear;
+  for (System* s : v) {
+    const bool single = is_fgmres(s->opts);
+    const GangCut c = s->desc.gang;
+    s->gang = c.g > 0 && mem;
+    s->gang_tag = s->gang_seq = 0;
+    s->gang_missed = 0;
+    s->gang_leave = false;
+    if (s->gang) {
+      if (c.g > 1) {
+        s->desc.gang_mem = mem;
+        mem += exch(c, single);
+      }
+      s->desc.gang_state = st;
+      st += state(c, single);
+    }
+    upload_desc(s);
+  }
+  return hipSuccess;
 }
 
 void Engine::remove(System* s) {
@@ -677,12 +728,8 @@ hipError_t Engine::group_phase(int phase, const std::vector<System*>& g) {
       if (!gw.empty()) {
         WgList W;
         std::memset(&W, 0, sizeof(W));
-        W.scal = d_scal_;
         W.nsys = (int)gw.size();
-        for (size_t q = 0; q < gw.size(); ++q) {
-          W.sys[q] = gw[q]->slot;
-          W.nmax = std::max(W.nmax, gw[q]->g.n);
-        }
+        for (size_t q = 0; q < gw.size(); ++q) W.sys[q] = gw[q]->slot;
         HUB_TRY(launch_arnoldi_wg(d_desc_, W, j, st_));
       }
       HUB_TRY(read_scal(g));
@@ -777,18 +824,96 @@ hipError_t Engine::confirm(const std::vector<System*>& g) {
   return hipSuccess;
 }
 
+hipError_t Engine::take_event(std::vector<hipEvent_t>& dst) {
+  if (events_.empty()) {
+    hipEvent_t ev;
+    HUB_TRY(hipEventCreate(&ev));
+    events_.push_back(ev);
+  }
+  dst.push_back(events_.back());
+  events_.pop_back();
+  return hipSuccess;
+}
+
+// System s joins the launch G; returns the LDS it needs.
+size_t Engine::gang_entry(GangList& G, System* s, bool single) const {
+  const GangCut c = s->desc.gang;
+  const GangBlock B = gang_largest(s->g.L1, s->g.L2, s->g.Nt, c.gt, c.gi, c.gj);
+  G.scal = d_scal_;
+  G.sys[G.nsys] = s->slot;
+  G.pi[G.nsys] = single ? S_Z0 + s->j : S_X;
+  G.tag[G.nsys] = s->gang_tag;
+  G.seq[G.nsys] = ++s->gang_seq;
+  ++G.nsys;
+  G.begin[G.nsys] = G.begin[G.nsys - 1] + c.g;
+  return single ? gang_lds<float>(B) : gang_lds<double>(B);
+}
+
+// Gang launches over the systems of v, as many systems to a launch as the device has CUs
+// for: every workgroup of a launch has to be on the device for its gang to meet.
+hipError_t Engine::launch_gangs(const std::vector<System*>& v, bool single, Block& b) {
+  for (size_t q = 0; q < v.size();) {
+    GangList G;
+    std::memset(&G, 0, sizeof(G));
+    size_t lds = 0;
+    for (; q < v.size(); ++q) {
+      System* s = v[q];
+      if (G.begin[G.nsys] + s->desc.gang.g > kGangMaxWgs) break;
+      lds = std::max(lds, gang_entry(G, s, single));
+      s->gang_tag += kGangIters + 2;  // a launch uses two tags before its iterations'
+      s->enq += kGangIters;
+    }
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    if (profiling_) {
+      HUB_TRY(take_event(b.gev));
+      HUB_TRY(take_event(b.gev));
+      e0 = b.gev[b.gev.size() - 2];
+      e1 = b.gev.back();
+    }
+    HUB_TRY(launch_gang(d_desc_, G, kGangIters, single, lds, st_, e0, e1));
+  }
+  return hipSuccess;
+}
+
+// Systems whose gang keeps missing its meetings (other work holds the CUs) go on with the
+// tiled kernels, from the iteration that the gang has reached.
+hipError_t Engine::leave_gangs(bool single) {
+  bool any = false;
+  for (System* s : slots_) any = any || (s && !s->done && s->gang && s->gang_leave && is_fgmres(s->opts) == single);
+  if (!any) return hipSuccess;
+  auto& q = inflight_[single ? 1 : 0];
+  for (auto& b : q) HUB_TRY(finish_block(b));
+  q.clear();
+  for (System* s : slots_) {
+    if (!s || s->done || !s->gang || !s->gang_leave || is_fgmres(s->opts) != single) continue;
+    if (s->phase == (single ? (int)PH_F_INNER : (int)PH_CG_ITER)) {
+      HUB_TRY(read_scal({s}));
+      s->enq = h_scal_[s->slot].git;
+      GangList G;
+      std::memset(&G, 0, sizeof(G));
+      const size_t lds = gang_entry(G, s, single);
+      HUB_TRY(launch_gang_leave(d_desc_, G, s->desc.ntiles, single, lds, st_));
+    }
+    s->gang = false;
+  }
+  return hipSuccess;
+}
+
 // Enqueue one block of CG iterations over every system that is iterating in the
 // given precision, followed by an asynchronous read-back of their flags.
 hipError_t Engine::launch_block(bool single, bool& launched) {
   launched = false;
-  std::vector<System*> v;
+  HUB_TRY(leave_gangs(single));
+  std::vector<System*> v, gangs;
   int k = 1 << 30;
-  bool any_tiled = false;
   for (System* s : slots_) {
     if (!s || s->done) continue;
     if ((single && s->phase == PH_F_INNER) || (!single && s->phase == PH_CG_ITER)) {
+      if (s->gang) {
+        gangs.push_back(s);
+        continue;
+      }
       v.push_back(s);
-      any_tiled = any_tiled || !(single && s->wg);
       int ks = std::max(1, s->opts.check_every);
       // near the iteration count of the system's previous CG run, enqueue short
       // blocks: launches after convergence return at once but still cost a launch
@@ -796,21 +921,14 @@ hipError_t Engine::launch_block(bool single, bool& launched) {
       k = std::min(k, ks);
     }
   }
-  if (v.empty()) return hipSuccess;
-  // Only single-workgroup systems iterating: their kernel stops by itself within a
-  // block, so long blocks cost nothing after convergence and save the per-block
-  // flag read-backs.
-  if (!any_tiled) k = std::max(k, kWgBlockIters);
-  // small systems run the whole block in one single-workgroup launch
-  std::vector<System*> wgs;
-  for (System* s : v)
-    if (single && s->wg) wgs.push_back(s);
-  // the others by the tile size of their CG stages: one launch per size class
+  if (v.empty() && gangs.empty()) return hipSuccess;
+  if (v.empty()) k = 0;
+  // tiled systems by the tile size of their CG stages: one launch per size class
   std::vector<System*> ordered;
   std::vector<int> cls_spt, cls_end;
   for (int spt : {(int)kSitesPerThread, (int)kSmallSpt}) {
     for (System* s : v)
-      if (!(single && s->wg) && s->desc.spt == spt) ordered.push_back(s);
+      if (s->desc.spt == spt) ordered.push_back(s);
     if (!ordered.empty() && (cls_end.empty() || (int)ordered.size() > cls_end.back())) {
       cls_spt.push_back(spt);
       cls_end.push_back((int)ordered.size());
@@ -824,8 +942,7 @@ hipError_t Engine::launch_block(bool single, bool& launched) {
   b.single = single;
   b.k = k;
   b.v = v;
-  b.v.insert(b.v.end(), wgs.begin(), wgs.end());
-  b.nwg = (int)wgs.size();
+  b.v.insert(b.v.end(), gangs.begin(), gangs.end());
   b.cls_end = cls_end;
   for (System* s : b.v) b.gen.push_back(s->gen);
   b.buf = next_buf_[single ? 1 : 0];
@@ -839,38 +956,9 @@ hipError_t Engine::launch_block(bool single, bool& launched) {
     for (size_t q = 0; q < vc.size(); ++q) L.pi[q] = single ? S_Z0 + vc[q]->j : S_X;
     Ls.push_back(L);
   }
-  auto take_event = [&](std::vector<hipEvent_t>& dst) -> hipError_t {
-    if (events_.empty()) {
-      hipEvent_t ev;
-      HUB_TRY(hipEventCreate(&ev));
-      events_.push_back(ev);
-    }
-    dst.push_back(events_.back());
-    events_.pop_back();
-    return hipSuccess;
-  };
-  if (profiling_) {
+  if (profiling_)
     for (int e = 0; e < 4 * k * ncls; ++e) HUB_TRY(take_event(b.kev));
-    if (b.nwg > 0) {
-      HUB_TRY(take_event(b.wgev));
-      HUB_TRY(take_event(b.wgev));
-    }
-  }
-  if (b.nwg > 0) {
-    WgList W;
-    std::memset(&W, 0, sizeof(W));
-    W.scal = d_scal_;
-    W.nsys = b.nwg;
-    for (int q = 0; q < b.nwg; ++q) {
-      System* s = wgs[q];
-      W.nmax = std::max(W.nmax, s->g.n);
-      W.sys[q] = s->slot;
-      W.pi[q] = single ? S_Z0 + s->j : S_X;
-      W.it[q] = s->enq;
-      s->enq += k;
-    }
-    HUB_TRY(launch_cg_wg(d_desc_, W, k, st_, profiling_ ? b.wgev[0] : nullptr, profiling_ ? b.wgev[1] : nullptr));
-  }
+  HUB_TRY(launch_gangs(gangs, single, b));
   for (int it = 0; it < k && ntile > 0; ++it) {
     std::vector<int> its(ntile);
     for (int q = 0; q < ntile; ++q) its[q] = v[q]->enq++;
@@ -953,17 +1041,18 @@ hipError_t Engine::finish_block(Block& b) {
       }
     }
   }
-  if (profiling_ && b.wgev.size() == 2) {
+  for (size_t e = 0; e + 1 < b.gev.size(); e += 2) {
     float ms = 0.0f;
-    HUB_TRY(hipEventElapsedTime(&ms, b.wgev[0], b.wgev[1]));
+    HUB_TRY(hipEventSynchronize(b.gev[e + 1]));
+    HUB_TRY(hipEventElapsedTime(&ms, b.gev[e], b.gev[e + 1]));
     KernelStat& ks = stat[single ? 1 : 0][2];
     ks.launches++;
     ks.ms += ms;
   }
   for (hipEvent_t e : b.kev) events_.push_back(e);
-  for (hipEvent_t e : b.wgev) events_.push_back(e);
+  for (hipEvent_t e : b.gev) events_.push_back(e);
   b.kev.clear();
-  b.wgev.clear();
+  b.gev.clear();
   for (size_t q = 0; q < b.v.size(); ++q) {
     System* s = b.v[q];
     const bool want = single ? (s->phase == PH_F_INNER) : (s->phase == PH_CG_ITER);
@@ -971,6 +1060,14 @@ hipError_t Engine::finish_block(Block& b) {
     // belong to a finished CG run)
     if (s->done || !want || s->gen != b.gen[q]) continue;
     const Scal& sc = flags[s->slot];
+    if (s->gang) {
+      if (sc.gang == 2) {
+        set_error("a workgroup of the CG did not answer");
+        return hipErrorUnknown;
+      }
+      if (sc.gang != 3) s->gang_missed = sc.gang == 1 ? s->gang_missed + 1 : 0;
+      if (s->gang_missed >= kGangMisses) s->gang_leave = true;
+    }
     if (sc.active) continue;
     s->pred = sc.iters;
     if (single) {

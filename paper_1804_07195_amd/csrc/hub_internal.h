@@ -7,6 +7,8 @@
 #include <cstddef>
 #include <cstdint>
 
+#include "hub_gang.h"
+
 namespace hub {
 
 constexpr int kBlock = 256;                   // threads per workgroup (4 wave64)
@@ -65,6 +67,8 @@ struct Scal {
   int iters;      // CG iterations performed when the CG stopped
   int maxit;
   int active;     // CG: 1 iterating, 2 stopped by the last stage 1 (the next stage 2 sets 0), 0 stopped
+  int git;        // gang CG: iterations done so far
+  int gang;       // gang CG, last launch: 0 ran, 1 nobody met in time, 2 a wait ran out, 3 refused (no room)
   int pad;
 };
 
@@ -75,7 +79,6 @@ struct SysDesc {
   const double* phi;     // float64 phi [n]
   const double2* ph64;   // (cos phi, sin phi) [n], FP64 solver kernels
   const float* ph32;     // phi reduced to [-pi, pi] and rounded to float [n] (single-precision path)
-  const float2* cs32;    // (cos, sin) of ph32 [n] (single-workgroup CG of small mixed-solver systems)
   Scal* sc;
   double* part;          // per-tile partials of the generic reductions [ntiles][kMaxRed]
   double* part1;         // per-tile partials of CG stage 1 [ntiles]
@@ -85,6 +88,9 @@ struct SysDesc {
   int tnb;               // tiles per segment
   int tbsz;              // sites per tile (the last tile of a segment may hold fewer)
   int tseg;              // sites per segment (a plane, or the whole vector)
+  GangCut gang;          // how a gang iterates on the system (g = 0: the tiled kernels do)
+  unsigned long long* gang_mem;    // its exchange memory (gang_exch_words; unused if g = 1)
+  unsigned long long* gang_state;  // and its state between launches (gang_state_words)
   void* vec[kMaxSlots];  // vector slots (type fixed by the slot's role)
 };
 
@@ -157,38 +163,32 @@ struct CgList {
 };
 constexpr int kSmallCg = 4;
 
-// Mixed-solver systems of at most kWgMaxSites sites run their complex64 CG in the
-// single-workgroup kernel (one workgroup of kWgBlock threads per system, all of its
-// state in registers and LDS, a block of iterations per launch); their other solver
-// kernels use the small tile class.  The limit: p and u in complex64 (2 x 8 bytes per
-// site) plus the reduction scratch fit in the 160 KB of LDS of a gfx950 CU, and a
-// thread holds at most kWgPerThread sites.
-constexpr int kWgBlock = 1024;
-constexpr int kWgPerThread = 10;
-#ifndef HUB_WG_MAX_SITES
-#define HUB_WG_MAX_SITES 10200
-#endif
-constexpr int kWgMaxSites = HUB_WG_MAX_SITES;
-static_assert(kWgMaxSites <= kWgBlock * kWgPerThread, "sites per thread");
-static_assert(kWgPerThread % 2 == 0, "whole site pairs per thread");
-static_assert(2 * kWgMaxSites * 8 + 2 * (kWgBlock / 64) * 8 <= 160 * 1024, "LDS of one CU");
-inline bool wg_of(int n) { return n <= kWgMaxSites; }
 // Systems whose FGMRES Arnoldi step runs as one fused single-workgroup launch instead of
 // the tiled kernels: one CU streams the basis twice, which beats the tiled path's launches
 // up to about this size (6x6x32: 7% faster per solve, 6x6x64 and 8x8x36: 2-4%, 12x12x32:
 // 5% slower).
+constexpr int kWgBlock = 1024;
+constexpr int kWgPerThread = 5;
 constexpr int kArnWgMaxSites = 4608;
+static_assert(kArnWgMaxSites <= kWgBlock * kWgPerThread, "sites per thread");
 inline bool arn_wg_of(int n) { return n <= kArnWgMaxSites; }
-// Systems of one single-workgroup CG launch: workgroup k runs system sys[k] from
-// iteration it[k], solution slot pi[k]; nmax = the largest system (LDS per workgroup).
+// Systems of one fused Arnoldi launch: workgroup k runs system sys[k].
 struct WgList {
+  int nsys;
+  int sys[kMaxSys];
+};
+
+// Systems of one gang launch: system sys[k], iterating into solution slot pi[k], takes the
+// workgroups [begin[k], begin[k + 1]); tag[k]: exchange tags used so far, seq[k]: the
+// number of this launch of the system (from 1).
+struct GangList {
   Scal* scal;
   int nsys;
-  int nmax;
-  int cs_lds;  // set by the launcher: the (cos, sin) tables are staged in LDS (nmax small enough)
+  int begin[kMaxSys + 1];
   int sys[kMaxSys];
   int pi[kMaxSys];
-  int it[kMaxSys];
+  unsigned tag[kMaxSys];
+  unsigned seq[kMaxSys];
 };
 
 // Tile class of a system: sites per thread of all its solver kernels.  Large systems
@@ -282,10 +282,7 @@ hipError_t launch_dot_re(const Geom& g, const double2* a, const double2* b, int 
                          double* result, hipStream_t st);
 // p64 = (cos phi, sin phi) in FP64 and, if p32 is not NULL, phi reduced to [-pi, pi]
 // and rounded to float (the complex64 kernels evaluate the phase from it).
-// With cs32, also (cos, sin) of that float angle as the complex64 kernels evaluate it (the
-// single-workgroup CG reads it instead of evaluating it twice per site and iteration).
-hipError_t launch_phase(const double* phi, double2* p64, float* p32, int n, hipStream_t st,
-                        float2* cs32 = nullptr);
+hipError_t launch_phase(const double* phi, double2* p64, float* p32, int n, hipStream_t st);
 // y_b = M u_b + mu2_b x_b (the second pass of the public normal operator, u = M^dagger x).
 hipError_t launch_normal2(const Geom& g, const double* phi, const double mu2_host[kMaxSys], const double2* u,
                           const double2* x, double2* y, int batch, hipStream_t st);
@@ -306,10 +303,16 @@ hipError_t launch_cg_iter(const SysDesc* sys, const LaunchList& L, bool single, 
 // kernel's own start and end timestamps into them (hipExtLaunchKernel).
 hipError_t launch_cg_stage(const SysDesc* sys, const LaunchList& L, bool single, int stage, hipStream_t st,
                            hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
-// K iterations of the complex64 CG of every system of L, one workgroup per system
-// (small systems, see kWgMaxSites); optional start/stop events.
-hipError_t launch_cg_wg(const SysDesc* sys, const WgList& L, int K, hipStream_t st,
-                        hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
+// Up to K iterations of the CG of every system of L, each by its gang (hub_gang.hip), `lds`
+// bytes for the largest block's tables; optional start/stop events.  At most kGangMaxWgs
+// workgroups in all.
+hipError_t launch_gang(const SysDesc* sys, const GangList& L, int K, bool single, size_t lds, hipStream_t st,
+                       hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
+// The one system of L goes on with the tiled kernels at the iteration its gang has reached:
+// the vectors back to their slots, and what stage 1 of the tiled iteration expects.
+hipError_t launch_gang_leave(const SysDesc* sys, const GangList& L, int ntiles, bool single, size_t lds, hipStream_t st);
+// Exchange memory starts from zero (no tag is 0).
+hipError_t launch_gang_clear(unsigned long long* mem, size_t words, hipStream_t st);
 // Arnoldi step j (w = A z_j, Gram-Schmidt against v_0 .. v_j, |w|^2 into the Scal records)
 // of every system of L, one workgroup per system (small systems, see kArnWgMaxSites).
 hipError_t launch_arnoldi_wg(const SysDesc* sys, const WgList& L, int j, hipStream_t st);

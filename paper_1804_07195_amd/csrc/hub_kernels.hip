@@ -23,7 +23,7 @@
 #include <cstring>
 #include <type_traits>
 
-#include "hub_internal.h"
+#include "hub_device.h"
 
 namespace hub {
 namespace {
@@ -45,10 +45,6 @@ namespace {
 template <typename R> struct Spt;
 template <> struct Spt<double> { static constexpr int v = HUB_SPT64; };
 template <> struct Spt<float> { static constexpr int v = HUB_SPT32; };
-
-template <typename R> struct V2;
-template <> struct V2<double> { using T = double2; };
-template <> struct V2<float> { using T = float2; };
 
 // cos x and sin x in FP64 for the public operator kernels (the phase of each site from
 // phi): Cody-Waite reduction r = x - q pi/2 with q the integer nearest 2x/pi and pi/2
@@ -93,107 +89,6 @@ __device__ __forceinline__ int xcd_remap(int b, int G) {
   const int per = G / kNumXcd, rem = G % kNumXcd;
   const int x = b % kNumXcd, k = b / kNumXcd;
   return (x < rem) ? x * (per + 1) + k : rem * (per + 1) + (x - rem) * per + k;
-}
-
-template <typename C> __device__ __forceinline__ C cz() { C z; z.x = 0; z.y = 0; return z; }
-
-template <typename R, typename C>
-__device__ __forceinline__ R norm2(C a) { return a.x * a.x + a.y * a.y; }
-
-// Views of device vectors in the global address space.  Pointers read from a
-// descriptor are generic; accessing them through these views makes the compiler
-// emit global_* instead of flat_* memory instructions.
-#define HUB_GAS __attribute__((address_space(1)))
-typedef double hub_d2v __attribute__((ext_vector_type(2)));
-typedef float hub_f2v __attribute__((ext_vector_type(2)));
-template <typename C> struct Vec;
-template <> struct Vec<double2> {
-  HUB_GAS hub_d2v* p;
-  __device__ __forceinline__ explicit Vec(const void* q) : p((HUB_GAS hub_d2v*)q) {}
-  __device__ __forceinline__ double2 operator[](int k) const {
-    const hub_d2v v = p[k];
-    double2 r;
-    r.x = v.x;
-    r.y = v.y;
-    return r;
-  }
-  __device__ __forceinline__ void set(int k, double2 a) const {
-    hub_d2v v;
-    v.x = a.x;
-    v.y = a.y;
-    p[k] = v;
-  }
-};
-typedef float hub_f4v __attribute__((ext_vector_type(4)));
-// Two consecutive complex64 values (sites k, k+1 with k even: one 16-byte access).
-struct C64x2 {
-  float2 a, b;
-};
-template <> struct Vec<float2> {
-  HUB_GAS hub_f2v* p;
-  __device__ __forceinline__ explicit Vec(const void* q) : p((HUB_GAS hub_f2v*)q) {}
-  __device__ __forceinline__ C64x2 pair(int k) const {
-    const hub_f4v v = ((HUB_GAS hub_f4v*)p)[k >> 1];
-    C64x2 r;
-    r.a.x = v.x;
-    r.a.y = v.y;
-    r.b.x = v.z;
-    r.b.y = v.w;
-    return r;
-  }
-  __device__ __forceinline__ void set_pair(int k, C64x2 a) const {
-    hub_f4v v;
-    v.x = a.a.x;
-    v.y = a.a.y;
-    v.z = a.b.x;
-    v.w = a.b.y;
-    ((HUB_GAS hub_f4v*)p)[k >> 1] = v;
-  }
-  __device__ __forceinline__ float2 operator[](int k) const {
-    const hub_f2v v = p[k];
-    float2 r;
-    r.x = v.x;
-    r.y = v.y;
-    return r;
-  }
-  __device__ __forceinline__ void set(int k, float2 a) const {
-    hub_f2v v;
-    v.x = a.x;
-    v.y = a.y;
-    p[k] = v;
-  }
-};
-template <typename T> struct Real {
-  HUB_GAS T* p;
-  __device__ __forceinline__ explicit Real(const void* q) : p((HUB_GAS T*)q) {}
-  __device__ __forceinline__ T operator[](int k) const { return p[k]; }
-  __device__ __forceinline__ void set(int k, T v) const { p[k] = v; }
-  // values at k, k+1 (k even): one 8-byte access for float
-  __device__ __forceinline__ hub_f2v pair(int k) const { return ((HUB_GAS hub_f2v*)p)[k >> 1]; }
-};
-
-// cos x and sin x in FP32 for the complex64 solver kernels, |x| <= pi in practice (the
-// angle is reduced when the solve starts): r = x - q pi/2 with q the integer nearest
-// 2x/pi (difference and product in FP64, exact far below FP32 rounding), cos r and
-// sin r on |r| <= pi/4 from their Taylor series through degree 10 and 9 (the first
-// omitted terms are below 2.5e-9, under half an FP32 ulp), then (cos r, sin r) turned
-// by q quarter turns.  Error against e^{ix}: about one FP32 ulp.
-__device__ __forceinline__ void cis32(float x, float& c, float& s) {
-  const float q = rintf(x * 0.636619772f);
-  const float r = (float)fma(-(double)q, 1.5707963267948966, (double)x);
-  const float r2 = r * r;
-  float ps = fmaf(r2, 2.75573192e-6f, -1.98412698e-4f);  // 1/9!, -1/7!
-  ps = fmaf(ps, r2, 8.33333333e-3f);                      // 1/5!
-  ps = fmaf(ps, r2, -1.66666667e-1f);                     // -1/3!
-  const float sr = fmaf(ps * r2, r, r);
-  float pc = fmaf(r2, -2.75573192e-7f, 2.48015873e-5f);  // -1/10!, 1/8!
-  pc = fmaf(pc, r2, -1.38888889e-3f);                     // -1/6!
-  pc = fmaf(pc, r2, 4.16666667e-2f);                      // 1/4!
-  pc = fmaf(pc, r2, -0.5f);
-  const float cr = fmaf(pc, r2, 1.0f);
-  const int k = (int)q & 3;
-  c = (k == 0) ? cr : (k == 1) ? -sr : (k == 2) ? -cr : sr;
-  s = (k == 0) ? sr : (k == 1) ? cr : (k == 2) ? -sr : -cr;
 }
 
 // The phase e^{i phi} a stencil needs, from one of three sources:
@@ -611,13 +506,6 @@ template <> __device__ __forceinline__ PhasePhi<double> phase_of<double>(const S
 }
 template <> __device__ __forceinline__ Angle32 phase_of<float>(const SysDesc* d) { return Angle32(d->ph32); }
 
-__device__ __forceinline__ int load_active(Scal* sc) {
-  return __hip_atomic_load(&sc->active, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void store_active(Scal* sc, int v) {
-  __hip_atomic_store(&sc->active, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 // ---------------------------------------------------------------------------
 // Public operator kernels (shared phi, batch of vectors, no descriptors).  They
 // have no reduction partials, so they use smaller tiles (two sites per thread,
@@ -1010,7 +898,7 @@ __global__ __launch_bounds__(kBlock) void k_dot_finish(const double* __restrict_
 // (cos phi, sin phi) per site in FP64 and, when p32 is given, phi - 2 pi k (k the
 // integer nearest phi / 2 pi, in FP64) rounded to float.
 __global__ __launch_bounds__(kBlock) void k_phase(const double* __restrict__ phi, double2* __restrict__ p64,
-                                                  float* __restrict__ p32, float2* __restrict__ cs32, int n) {
+                                                  float* __restrict__ p32, int n) {
   const int i = blockIdx.x * kBlock + threadIdx.x;
   if (i >= n) return;
   const double a = phi[i];
@@ -1022,12 +910,6 @@ __global__ __launch_bounds__(kBlock) void k_phase(const double* __restrict__ phi
   p64[i] = v;
   const float a32 = (float)fma(-rint(a * 0.15915494309189535), 6.283185307179586, a);
   if (p32) p32[i] = a32;
-  if (cs32) {
-    // the complex64 kernels' phase of that angle, as they would evaluate it
-    float2 e;
-    cis32(a32, e.x, e.y);
-    cs32[i] = e;
-  }
 }
 
 // Molecular dynamics (Sec. 5.2): phi += eps pi (T_pi), and the momentum kick
@@ -1305,24 +1187,6 @@ __global__ __launch_bounds__(kBlock) void k_cg2(const SysDesc* __restrict__ sys,
   if (threadIdx.x == 0) Real<double>(d->part2).set(tile, tot);
 }
 
-// ---------------------------------------------------------------------------
-// Single-workgroup complex64 CG for small systems, resident on one compute unit.
-// One workgroup of kWgBlock threads owns a system of at most kWgMaxSites sites and
-// runs up to K iterations of the same recurrence as k_cg1<float> / k_cg2<float> in one
-// launch.  Each thread keeps r and the solution of its sites (threadIdx.x + m *
-// kWgBlock, m < kWgPerThread) in registers, and the two vectors the stencil reads at
-// neighbouring sites, p and u = M^dagger p, live in LDS (2 x 8 bytes x 10,200 sites
-// fit in the 160 KB of a gfx950 CU); only the phase angles at the temporal neighbours
-// are read from memory inside the loop.  Kernel boundaries become workgroup barriers
-// and the reductions workgroup sums (wave64 butterflies, then the 16 wave results in
-// a fixed order), so an iteration costs LDS traffic and two barriers instead of two
-// launch floors and the vectors' round trips through L2.  An FP64 system of this size
-// does not fit (p and u would take 2 x 16 bytes per site): FP64 CG keeps the tiled
-// kernels.  The solution advances every iteration (x += alpha p).  Entry: r, x and
-// p_old (slot S_P32 + (it & 1)) from memory; exit: the same slots written back,
-// rrv[it & 1] = |r_it|^2, rrv[(it - 1) & 1] = |r_{it-1}|^2, and on a stop iters = it,
-// active = 0.
-// ---------------------------------------------------------------------------
 // Sum over the workgroup in a fixed order; every thread gets the value.  `buf` holds one
 // double per wave; callers alternate two buffers, so that the one barrier here also
 // guarantees that the previous sum over the same buffer has been read by every thread
@@ -1336,288 +1200,6 @@ __device__ __forceinline__ double wg_sum(T v, double* buf) {
 #pragma unroll
   for (int k = 0; k < kWgBlock / 64; ++k) s += buf[k];
   return s;
-}
-
-// Coordinates of the sites n0 + m * step, m = 0, 1, ...: one division pair for m = 0, then
-// a step of `step` sites per m (dj columns, then di rows and dq planes with one carry each:
-// di + 1 <= L1 and dj < L2 keep every carry to one subtraction).
-struct WgWalk {
-  int i, j;
-  uint32_t q2;
-  int dj, di, dq;
-  __device__ __forceinline__ void next(const Geom& g) {
-    j += dj;
-    const int cj = j >= g.L2;
-    j -= cj * g.L2;
-    i += di + cj;
-    const int ci = i >= g.L1;
-    i -= ci * g.L1;
-    q2 += (uint32_t)(dq + ci);
-  }
-};
-
-__device__ __forceinline__ WgWalk wg_walk(const Geom& g, int n0, int step) {
-  WgWalk w;
-  const uint32_t q1 = fdiv((uint32_t)n0, g.dL2);
-  w.j = n0 - (int)q1 * g.L2;
-  w.q2 = fdiv(q1, g.dL1);
-  w.i = (int)q1 - (int)w.q2 * g.L1;
-  const int rows = step / g.L2;  // whole rows in a step
-  w.dj = step - rows * g.L2;
-  w.dq = rows / g.L1;
-  w.di = rows - w.dq * g.L1;
-  // the start is laundered so that the walk is redone in every pass rather than hoisted
-  // out of the iteration loop, where its ten sites' coordinates would not fit in registers
-  asm volatile("" : "+v"(w.i), "+v"(w.j), "+v"(w.q2));
-  return w;
-}
-
-// (cos, sin) of row h of a pair of precomputed phases.
-__device__ __forceinline__ void pick(const C64x2& e, int h, float& c, float& s) {
-  c = h ? e.b.x : e.a.x;
-  s = h ? e.b.y : e.a.y;
-}
-
-// Pair view of an LDS array of complex64 values: sites k, k + 1 (k even) in one 16-byte
-// access.
-__device__ __forceinline__ C64x2 lds_pair(const float2* a, int k) {
-  const hub_f4v v = reinterpret_cast<const hub_f4v*>(a)[k >> 1];
-  C64x2 r;
-  r.a.x = v.x;
-  r.a.y = v.y;
-  r.b.x = v.z;
-  r.b.y = v.w;
-  return r;
-}
-__device__ __forceinline__ void lds_set_pair(float2* a, int k, C64x2 v) {
-  hub_f4v w;
-  w.x = v.a.x;
-  w.y = v.a.y;
-  w.z = v.b.x;
-  w.w = v.b.y;
-  reinterpret_cast<hub_f4v*>(a)[k >> 1] = w;
-}
-
-// The iterations of one system.  PAIR (even L2): each thread owns the site pairs
-// (2u, 2u + 1), u = threadIdx.x + m * kWgBlock, and applies the stencil a pair at a time
-// (index arithmetic once per pair, 16-byte LDS accesses); otherwise the single sites
-// threadIdx.x + m * kWgBlock.  Site k of unit m sits in rv[m * S + k] etc., S sites per unit.
-template <bool PAIR, bool CSL>
-__device__ __forceinline__ void wg_cg(const SysDesc* __restrict__ d, Scal* sc, const WgList& L, int kk, int K,
-                                      float2* __restrict__ lp, float2* __restrict__ lu, float2* __restrict__ lc,
-                                      double (*red)[kWgBlock / 64]) {
-  constexpr int S = PAIR ? 2 : 1;
-  constexpr int U = kWgPerThread / S;  // units per thread
-  const int u0 = S * (int)threadIdx.x, ustep = S * kWgBlock;
-  const Geom g = d->g;
-  const int N = g.n;
-  const int it0 = L.it[kk];
-  const float mu2 = (float)d->mu2;
-  const double stop2 = sc->stop2;
-  const int maxit = sc->maxit;
-  const Vec<float2> r(d->vec[S_R32]), x(d->vec[L.pi[kk]]), cs(d->cs32);
-  float2 rv[kWgPerThread], xv[kWgPerThread], ev[kWgPerThread];  // ev: (cos, sin) of the own site
-  {
-    const Vec<float2> po(d->vec[S_P32 + (it0 & 1)]);
-#pragma unroll
-    for (int m = 0; m < U; ++m) {
-      const int n = u0 + m * ustep;
-      if (n < N) {
-        if constexpr (PAIR) {
-          const C64x2 a = r.pair(n), b = x.pair(n), e = cs.pair(n);
-          rv[2 * m] = a.a;
-          rv[2 * m + 1] = a.b;
-          xv[2 * m] = b.a;
-          xv[2 * m + 1] = b.b;
-          ev[2 * m] = e.a;
-          ev[2 * m + 1] = e.b;
-          if (it0 > 0) lds_set_pair(lp, n, po.pair(n));
-        } else {
-          rv[m] = r[n];
-          xv[m] = x[n];
-          ev[m] = cs[n];
-          if (it0 > 0) lp[n] = po[n];
-        }
-      }
-    }
-  }
-  if constexpr (CSL)
-    for (int n = threadIdx.x; n < N; n += kWgBlock) lc[n] = cs[n];
-  double rr = sc->rrv[it0 & 1];
-  double rr_prev = it0 > 0 ? sc->rrv[(it0 - 1) & 1] : 1.0;
-  int it = it0;
-  bool stopped = false;
-  __syncthreads();
-  for (int step = 0; step < K; ++step, ++it) {
-    // the stopping test of iteration it (at it = 0 the CG setup decided)
-    if (it > 0 && (!(rr > stop2) || it >= maxit)) {
-      stopped = true;
-      break;
-    }
-    const float beta = it == 0 ? 0.0f : (float)(rr / rr_prev);
-    float acc = 0.0f;
-    // p = r + beta p_old on this thread's sites
-#pragma unroll
-    for (int m = 0; m < U; ++m) {
-      const int n = u0 + m * ustep;
-      if (n < N) {
-        if constexpr (PAIR) {
-          C64x2 pv;
-          pv.a = rv[2 * m];
-          pv.b = rv[2 * m + 1];
-          if (it > 0) {
-            const C64x2 q = lds_pair(lp, n);
-            pv.a.x = fmaf(beta, q.a.x, pv.a.x);
-            pv.a.y = fmaf(beta, q.a.y, pv.a.y);
-            pv.b.x = fmaf(beta, q.b.x, pv.b.x);
-            pv.b.y = fmaf(beta, q.b.y, pv.b.y);
-          }
-          lds_set_pair(lp, n, pv);
-          acc += mu2 * (norm2<float>(pv.a) + norm2<float>(pv.b));
-        } else {
-          float2 pv = rv[m];
-          if (it > 0) {
-            const float2 q = lp[n];
-            pv.x = fmaf(beta, q.x, pv.x);
-            pv.y = fmaf(beta, q.y, pv.y);
-          }
-          lp[n] = pv;
-          acc += mu2 * norm2<float>(pv);
-        }
-      }
-    }
-    __syncthreads();
-    // u = M^dagger p (the phase of the temporal neighbour, from the table); <p, A p> =
-    // |u|^2 + mu2 |p|^2
-    {
-      WgWalk wk = wg_walk(g, u0, ustep);
-#pragma unroll
-      for (int m = 0; m < U; ++m) {
-        const int n = u0 + m * ustep;
-        if (n < N) {
-          if constexpr (PAIR) {
-            const PairIdx sm = pair_index_at<true>(g, n, wk.i, wk.j, wk.q2);
-            const C64x2 e = CSL ? lds_pair(lc, sm.tn) : cs.pair(sm.tn);
-            const C64x2 y = pair_stencil<true>(g, sm, [&](int h, float& c, float& s) { pick(e, h, c, s); },
-                                               lds_pair(lp, n), lds_pair(lp, sm.tn), lds_pair(lp, sm.h0),
-                                               lds_pair(lp, sm.h1), lp[sm.hx]);
-            lds_set_pair(lu, n, y);
-            acc += norm2<float>(y.a) + norm2<float>(y.b);
-          } else {
-            const SiteIdx st = site_index_at<true>(g, n, wk.i, wk.j, wk.q2);
-            const float2 e = CSL ? lc[st.pn] : cs[st.pn];
-            const float2 xs = lp[st.n], xt = lp[st.tn], x0 = lp[st.h0], x1 = lp[st.h1], x2 = lp[st.h2];
-            const float2 y = stencil_combine<float, true>(g, st, e.x, e.y, xs, xt, x0, x1, x2);
-            lu[n] = y;
-            acc += norm2<float>(y);
-          }
-        }
-        wk.next(g);
-      }
-    }
-    // FP32 sums within a wave (as the tiled kernels' workgroup sums), FP64 across waves
-    const double pap = wg_sum(acc, red[0]);  // its barrier also publishes u
-    const float alpha = (float)(rr / pap);
-    // q = M u + mu2 p; r -= alpha q; x += alpha p; |r|^2
-    float acc2 = 0.0f;
-    {
-      WgWalk wk = wg_walk(g, u0, ustep);
-#pragma unroll
-      for (int m = 0; m < U; ++m) {
-        const int n = u0 + m * ustep;
-        if (n < N) {
-          float2 q[S], pv[S];
-          if constexpr (PAIR) {
-            const PairIdx sm = pair_index_at<false>(g, n, wk.i, wk.j, wk.q2);
-            C64x2 e;
-            e.a = ev[2 * m];
-            e.b = ev[2 * m + 1];
-            const C64x2 y = pair_stencil<false>(g, sm, [&](int h, float& c, float& s) { pick(e, h, c, s); },
-                                                lds_pair(lu, n), lds_pair(lu, sm.tn), lds_pair(lu, sm.h0),
-                                                lds_pair(lu, sm.h1), lu[sm.hx]);
-            const C64x2 pp = lds_pair(lp, n);
-            q[0] = y.a;
-            q[S - 1] = y.b;
-            pv[0] = pp.a;
-            pv[S - 1] = pp.b;
-          } else {
-            const SiteIdx st = site_index_at<false>(g, n, wk.i, wk.j, wk.q2);
-            const float2 xs = lu[st.n], xt = lu[st.tn], x0 = lu[st.h0], x1 = lu[st.h1], x2 = lu[st.h2];
-            q[0] = stencil_combine<float, false>(g, st, ev[m].x, ev[m].y, xs, xt, x0, x1, x2);
-            pv[0] = lp[n];
-          }
-#pragma unroll
-          for (int h = 0; h < S; ++h) {
-            float2& rk = rv[m * S + h];
-            float2& xk = xv[m * S + h];
-            rk.x -= alpha * fmaf(mu2, pv[h].x, q[h].x);
-            rk.y -= alpha * fmaf(mu2, pv[h].y, q[h].y);
-            xk.x = fmaf(alpha, pv[h].x, xk.x);
-            xk.y = fmaf(alpha, pv[h].y, xk.y);
-            acc2 += norm2<float>(rk);
-          }
-        }
-        wk.next(g);
-      }
-    }
-    rr_prev = rr;
-    rr = wg_sum(acc2, red[1]);
-  }
-  // write the state back: r, x, and p_{it-1} to the slot iteration `it` reads it from
-  {
-    const Vec<float2> pw(d->vec[S_P32 + (it & 1)]);
-#pragma unroll
-    for (int m = 0; m < U; ++m) {
-      const int n = u0 + m * ustep;
-      if (n < N) {
-        if constexpr (PAIR) {
-          C64x2 a, b;
-          a.a = rv[2 * m];
-          a.b = rv[2 * m + 1];
-          b.a = xv[2 * m];
-          b.b = xv[2 * m + 1];
-          r.set_pair(n, a);
-          x.set_pair(n, b);
-          if (it > 0) pw.set_pair(n, lds_pair(lp, n));
-        } else {
-          r.set(n, rv[m]);
-          x.set(n, xv[m]);
-          if (it > 0) pw.set(n, lp[n]);
-        }
-      }
-    }
-  }
-  if (threadIdx.x == 0) {
-    sc->rrv[it & 1] = rr;
-    if (it > 0) sc->rrv[(it - 1) & 1] = rr_prev;
-    if (stopped) {
-      sc->iters = it;
-      store_active(sc, 0);
-    }
-  }
-}
-
-__global__ __launch_bounds__(kWgBlock) void k_cg_wg32(const SysDesc* __restrict__ sys, WgList L, int K) {
-  extern __shared__ __attribute__((aligned(16))) float2 wlds[];  // p [nmax], u [nmax] (nmax even), cs [nmax]
-  const int kk = blockIdx.x;
-  const SysDesc* __restrict__ d = sys + L.sys[kk];
-  Scal* sc = L.scal + L.sys[kk];
-  if (!load_active(sc)) return;
-  float2* __restrict__ lp = wlds;
-  float2* __restrict__ lu = wlds + L.nmax;
-  float2* __restrict__ lc = wlds + 2 * L.nmax;
-  __shared__ double red[2][kWgBlock / 64];  // the two alternating buffers of wg_sum
-  if ((d->g.L2 & 1) == 0) {
-    if (L.cs_lds)
-      wg_cg<true, true>(d, sc, L, kk, K, lp, lu, lc, red);
-    else
-      wg_cg<true, false>(d, sc, L, kk, K, lp, lu, lc, red);
-  } else {
-    if (L.cs_lds)
-      wg_cg<false, true>(d, sc, L, kk, K, lp, lu, lc, red);
-    else
-      wg_cg<false, false>(d, sc, L, kk, K, lp, lu, lc, red);
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -2143,6 +1725,8 @@ __global__ __launch_bounds__(kBlock) void k_finish(const SysDesc* __restrict__ s
       sc->stop2 = stop2;
       sc->maxit = L.pi[kk];
       sc->iters = 0;
+      sc->git = 0;
+      sc->gang = 0;
       store_active(sc, s > stop2 ? 1 : 0);
     }
   }
@@ -2390,8 +1974,8 @@ hipError_t launch_normal2(const Geom& g, const double* phi, const double mu2_hos
 }
 
 
-hipError_t launch_phase(const double* phi, double2* p64, float* p32, int n, hipStream_t st, float2* cs32) {
-  hipLaunchKernelGGL(k_phase, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, st, phi, p64, p32, cs32, n);
+hipError_t launch_phase(const double* phi, double2* p64, float* p32, int n, hipStream_t st) {
+  hipLaunchKernelGGL(k_phase, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, st, phi, p64, p32, n);
   return hipGetLastError();
 }
 
@@ -2467,31 +2051,8 @@ hipError_t launch_cg_stage(const SysDesc* sys, const LaunchList& L, bool single,
 }
 
 
-hipError_t launch_cg_wg(const SysDesc* sys, const WgList& L, int K, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
-  // nmax even: the pair path's 16-byte LDS accesses of u stay aligned
-  if (L.nsys < 1 || L.nsys > kMaxSys || K < 1 || L.nmax < 2 || L.nmax > kWgMaxSites || (L.nmax & 1))
-    return hipErrorInvalidValue;
-  // the (cos, sin) tables join p and u in LDS when all three fit
-  WgList W = L;
-  W.cs_lds = 3 * (size_t)L.nmax * sizeof(float2) <= 2 * (size_t)kWgMaxSites * sizeof(float2) ? 1 : 0;
-  const size_t lds = (W.cs_lds ? 3 : 2) * (size_t)L.nmax * sizeof(float2);
-  static bool attr_set = false;  // the 160 KB of dynamic LDS exceed the default limit
-  if (!attr_set) {
-    const hipError_t e = hipFuncSetAttribute((const void*)k_cg_wg32, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                             (int)(2 * (size_t)kWgMaxSites * sizeof(float2)));
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
-  const dim3 grid(L.nsys), block(kWgBlock);
-  if (e0)
-    hipExtLaunchKernelGGL(k_cg_wg32, grid, block, lds, st, e0, e1, 0, sys, W, K);
-  else
-    hipLaunchKernelGGL(k_cg_wg32, grid, block, lds, st, sys, W, K);
-  return hipGetLastError();
-}
-
 hipError_t launch_arnoldi_wg(const SysDesc* sys, const WgList& L, int j, hipStream_t st) {
-  if (L.nsys < 1 || L.nsys > kMaxSys || j < 0 || j >= kMaxRestart || L.nmax > kWgMaxSites) return hipErrorInvalidValue;
+  if (L.nsys < 1 || L.nsys > kMaxSys || j < 0 || j >= kMaxRestart) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_arnoldi_wg, dim3(L.nsys), dim3(kWgBlock), 0, st, sys, L, j);
   return hipGetLastError();
 }
