@@ -165,7 +165,7 @@ class Engine {
   hipError_t finish_block(Block& b);
   hipError_t wait_block(unsigned seq);
   hipError_t launch_gangs(const std::vector<System*>& v, bool single, Block& b);
-  size_t gang_entry(GangList& G, System* s, bool single) const;
+  bool gang_entry(GangList& G, System* s, bool single) const;
   hipError_t leave_gangs(bool single);
   hipError_t take_event(std::vector<hipEvent_t>& dst);
   GangCut cut_of(const Geom& g, bool single);

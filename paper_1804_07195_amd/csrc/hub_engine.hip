@@ -835,18 +835,49 @@ hipError_t Engine::take_event(std::vector<hipEvent_t>& dst) {
   return hipSuccess;
 }
 
-// System s joins the launch G; returns the LDS it needs.
-size_t Engine::gang_entry(GangList& G, System* s, bool single) const {
-  const GangCut c = s->desc.gang;
-  const GangBlock B = gang_largest(s->g.L1, s->g.L2, s->g.Nt, c.gt, c.gi, c.gj);
+// System s joins the launch G; false: no room.  Blocks go to the XCDs in turn (block b to
+// XCD b mod 8), so a gang takes its blocks with a stride, consecutive workgroups on one XCD:
+// a reduction among 16 workgroups takes 2.0 us on one XCD and 2.45 us over all.  More than
+// about a dozen of one gang on an XCD get into each other's way (the FP64 iteration of a
+// 48x48x64 system 8.1 us with 28 on each of five XCDs, 7.0 us with 18 on each of eight).
+bool Engine::gang_entry(GangList& G, System* s, bool single) const {
+  constexpr int kPer = kGangMaxWgs / kNumXcd;  // blocks per XCD
+  constexpr int kSpread = 12;                  // workgroups of a gang per XCD, while others are free
+  if (G.nsys == 0) std::memset(G.list, kGangNone, sizeof(G.list));
+  int room[kNumXcd] = {0}, total = 0;
+  for (int b = 0; b < kGangMaxWgs; ++b)
+    if (G.list[b] == kGangNone) ++room[b % kNumXcd], ++total;
+  const int g = s->desc.gang.g;
+  if (g > total || G.nsys == kMaxSys) return false;
+  // the XCDs with the most room, an even share on each
+  int order[kNumXcd];
+  for (int x = 0; x < kNumXcd; ++x) order[x] = x;
+  std::stable_sort(order, order + kNumXcd, [&](int a, int b) { return room[a] > room[b]; });
+  int nx = 0, sum = 0;
+  while (nx < kNumXcd && (sum < g || nx * kSpread < g)) sum += room[order[nx++]];
+  int left = g, wg = 0;
+  for (int k = 0; k < nx; ++k) {
+    const int x = order[k];
+    int later = 0;
+    for (int q = k + 1; q < nx; ++q) later += room[order[q]];
+    int n = std::max(std::min((left + nx - k - 1) / (nx - k), room[x]), left - later);
+    left -= n;
+    for (int b = x; b < kGangMaxWgs && n > 0; b += kNumXcd)
+      if (G.list[b] == kGangNone) {
+        G.list[b] = (unsigned char)G.nsys;
+        G.wg[b] = (unsigned char)wg++;
+        G.nblock = std::max(G.nblock, b + 1);
+        --n;
+      }
+  }
+  static_assert(kPer * kNumXcd == kGangMaxWgs && kGangMaxWgs <= 256 && kMaxSys < kGangNone, "block table");
   G.scal = d_scal_;
   G.sys[G.nsys] = s->slot;
   G.pi[G.nsys] = single ? S_Z0 + s->j : S_X;
   G.tag[G.nsys] = s->gang_tag;
   G.seq[G.nsys] = ++s->gang_seq;
   ++G.nsys;
-  G.begin[G.nsys] = G.begin[G.nsys - 1] + c.g;
-  return single ? gang_lds<float>(B) : gang_lds<double>(B);
+  return true;
 }
 
 // Gang launches over the systems of v, as many systems to a launch as the device has CUs
@@ -855,11 +886,9 @@ hipError_t Engine::launch_gangs(const std::vector<System*>& v, bool single, Bloc
   for (size_t q = 0; q < v.size();) {
     GangList G;
     std::memset(&G, 0, sizeof(G));
-    size_t lds = 0;
     for (; q < v.size(); ++q) {
       System* s = v[q];
-      if (G.begin[G.nsys] + s->desc.gang.g > kGangMaxWgs) break;
-      lds = std::max(lds, gang_entry(G, s, single));
+      if (!gang_entry(G, s, single)) break;
       s->gang_tag += kGangIters + 2;  // a launch uses two tags before its iterations'
       s->enq += kGangIters;
     }
@@ -870,7 +899,7 @@ hipError_t Engine::launch_gangs(const std::vector<System*>& v, bool single, Bloc
       e0 = b.gev[b.gev.size() - 2];
       e1 = b.gev.back();
     }
-    HUB_TRY(launch_gang(d_desc_, G, kGangIters, single, lds, st_, e0, e1));
+    HUB_TRY(launch_gang(d_desc_, G, kGangIters, single, st_, e0, e1));
   }
   return hipSuccess;
 }
@@ -891,8 +920,8 @@ hipError_t Engine::leave_gangs(bool single) {
       s->enq = h_scal_[s->slot].git;
       GangList G;
       std::memset(&G, 0, sizeof(G));
-      const size_t lds = gang_entry(G, s, single);
-      HUB_TRY(launch_gang_leave(d_desc_, G, s->desc.ntiles, single, lds, st_));
+      gang_entry(G, s, single);
+      HUB_TRY(launch_gang_leave(d_desc_, G, s->desc.ntiles, single, st_));
     }
     s->gang = false;
   }

@@ -11,7 +11,12 @@ namespace hub {
 constexpr int kGangThreads = 512;              // threads per workgroup: half per sublattice
 constexpr int kGangHalf = kGangThreads / 2;
 constexpr int kGangMaxWgs = 256;               // workgroups of one launch: one per CU
-constexpr int kGangLdsBytes = 160 * 1024 - 1024;  // both tables; the rest holds the reductions
+// LDS of a workgroup: the reductions, the field table, and the table of links a fixed
+// distance behind it, so that one address reaches both (the immediate offset of an LDS
+// access is 16 bits).
+constexpr int kGangHead = 256;
+constexpr int kGangLinks = 65280;
+constexpr int kGangLdsBytes = kGangHead + 2 * kGangLinks;
 constexpr int kGangRecWords = 4;               // 8-byte words of a reduction record
 constexpr int kGangCtlWords = 32;              // 8-byte control words in front of the records
 
@@ -22,19 +27,20 @@ constexpr int kGangCtlWords = 32;              // 8-byte control words in front 
 struct GangClass {
   int M, H, X;
 };
-constexpr int kGangClasses = 5;
 template <typename R> struct GangTab;
 template <> struct GangTab<float> {
-  static constexpr GangClass c[kGangClasses] = {{1, 2, 1}, {3, 2, 1}, {6, 4, 2}, {9, 6, 3}, {11, 6, 3}};
+  static constexpr int n = 7;
+  static constexpr GangClass c[n] = {{1, 2, 1}, {2, 3, 1}, {3, 3, 1}, {4, 4, 2}, {6, 5, 2}, {8, 6, 3}, {11, 6, 3}};
 };
 template <> struct GangTab<double> {
-  static constexpr GangClass c[kGangClasses] = {{1, 2, 1}, {2, 3, 1}, {3, 4, 2}, {4, 4, 2}, {6, 5, 2}};
+  static constexpr int n = 4;
+  static constexpr GangClass c[n] = {{1, 2, 1}, {2, 3, 1}, {3, 4, 2}, {4, 4, 2}};
 };
 
 // The cut: gt x gi x gj blocks along t, i and j (g = 0: the system is not iterated by a gang).
 struct GangCut {
   int gt, gi, gj, g;
-  int nslot;  // sites of the largest block
+  int nslot;  // exchange elements of the largest block
   int cls;    // class of the largest block
 };
 
@@ -69,7 +75,9 @@ __host__ __device__ inline int gang_div(int n, float r) { return (int)(((float)n
 __host__ __device__ inline GangBlock gang_block(int L1, int L2, int Nt, int gt, int gi, int gj, int wg) {
   GangBlock B;
   B.L1 = L1, B.L2 = L2, B.Nt = Nt, B.gt = gt, B.gi = gi, B.gj = gj;
-  const int bj = wg % gj, q = wg / gj, bi = q % gi, bt = q / gi;
+  // slices fastest: the largest faces of a block lie towards its neighbours in time, and
+  // consecutive workgroups are placed on the same XCD
+  const int bt = wg % gt, q = wg / gt, bj = q % gj, bi = q / gj;
   B.t0 = gang_start(Nt, gt, bt), B.T = gang_start(Nt, gt, bt + 1) - B.t0;
   B.i0 = gang_start(L1, gi, bi), B.a = gang_start(L1, gi, bi + 1) - B.i0;
   B.j0 = gang_start(L2, gj, bj), B.b = gang_start(L2, gj, bj + 1) - B.j0;
@@ -118,11 +126,17 @@ __host__ __device__ inline GangPlace gang_place(const GangBlock& B, int q) {
   return c;
 }
 
-// Whether another workgroup reads this own site: it lies on a face of a cut direction.
+// What a workgroup sends.  Sites of cells on a face of a cut spatial direction go to their
+// place among the block's sites (A sites first, then B sites; a cell's slices adjacent).
+// With time cut the first and the last slice go to planes behind them as well, cells
+// adjacent: read from their columns, every element of a plane would cost a memory line.
 __host__ __device__ inline bool gang_sent(const GangBlock& B, GangSite c) {
-  return (B.oi && (c.i == 0 || c.i == B.a - 1)) || (B.oj && (c.j == 0 || c.j == B.b - 1)) ||
-         (B.gt > 1 && (c.t == 0 || c.t == B.T - 1));
+  return (B.oi && (c.i == 0 || c.i == B.a - 1)) || (B.oj && (c.j == 0 || c.j == B.b - 1));
 }
+__host__ __device__ inline int gang_plane(const GangBlock& B, int last, int s, int cell) {
+  return 2 * B.half + (2 * last + s) * B.a * B.b + cell;
+}
+__host__ __device__ inline int gang_slots(const GangBlock& B) { return 2 * B.half + (B.gt > 1 ? 4 * B.a * B.b : 0); }
 
 // The two bonds of a site beside the one inside its cell: A(i, j) has B(i - 1, j) and
 // B(i, j - 1), B(i, j) has A(i + 1, j) and A(i, j + 1).  Entries of both at slot te.
@@ -180,17 +194,23 @@ __host__ __device__ inline GangHalo gang_halo(const GangBlock& B, int e) {
   }
   return h;
 }
-// Where a halo element comes from: the owning workgroup and the element's place among its
-// sites (A sites first, then B sites, `half` of that block each).
+// Where a halo element comes from: the owning workgroup and the element's place there.
 __host__ __device__ inline void gang_source(const GangBlock& B, GangHalo h, int& wg, int& k) {
   const int gi_ = gang_wrap(B.i0 + h.i, B.L1), gj_ = gang_wrap(B.j0 + h.j, B.L2),
             gt_ = gang_wrap(B.t0 + h.te - 1, B.Nt);
   const int bt = gang_owner(B.Nt, B.gt, gt_), bi = gang_owner(B.L1, B.gi, gi_), bj = gang_owner(B.L2, B.gj, gj_);
-  wg = (bt * B.gi + bi) * B.gj + bj;
-  const int t0 = gang_start(B.Nt, B.gt, bt), T = gang_start(B.Nt, B.gt, bt + 1) - t0;
-  const int i0 = gang_start(B.L1, B.gi, bi), a = gang_start(B.L1, B.gi, bi + 1) - i0;
-  const int j0 = gang_start(B.L2, B.gj, bj), b = gang_start(B.L2, B.gj, bj + 1) - j0;
-  k = h.s * a * b * T + ((gi_ - i0) * b + (gj_ - j0)) * T + (gt_ - t0);
+  wg = (bi * B.gj + bj) * B.gt + bt;
+  GangBlock O = B;
+  const int t0 = gang_start(B.Nt, B.gt, bt), i0 = gang_start(B.L1, B.gi, bi), j0 = gang_start(B.L2, B.gj, bj);
+  O.T = gang_start(B.Nt, B.gt, bt + 1) - t0;
+  O.a = gang_start(B.L1, B.gi, bi + 1) - i0;
+  O.b = gang_start(B.L2, B.gj, bj + 1) - j0;
+  O.half = O.a * O.b * O.T;
+  const int cell = (gi_ - i0) * O.b + (gj_ - j0);
+  if (h.te >= 1 && h.te <= B.T)
+    k = h.s * O.half + cell * O.T + (gt_ - t0);
+  else
+    k = gang_plane(O, h.te == 0, h.s, cell);
 }
 
 // Extra sites of sublattice s at which u = M^dagger r is computed here although another
@@ -224,17 +244,11 @@ inline GangBlock gang_largest(int L1, int L2, int Nt, int gt, int gi, int gj) {
 // that stands for sites a thread does not have (every neighbour it reads is zero too).
 __host__ __device__ inline int gang_zero(const GangBlock& B) { return gang_entries(B) + B.TS; }
 __host__ __device__ inline int gang_table(const GangBlock& B) { return gang_entries(B) + 2 * B.TS + 1; }
-// LDS of a block: the field and the temporal links.
-template <typename R>
-__host__ __device__ inline size_t gang_lds(const GangBlock& B) {
-  return (size_t)gang_table(B) * 4 * sizeof(R);
-}
-
 // The first class that holds a block, or -1.
 template <typename R>
 inline int gang_class(const GangBlock& B) {
-  if (gang_lds<R>(B) > (size_t)kGangLdsBytes) return -1;
-  for (int k = 0; k < kGangClasses; ++k) {
+  if ((size_t)gang_table(B) * 2 * sizeof(R) > (size_t)kGangLinks) return -1;
+  for (int k = 0; k < GangTab<R>::n; ++k) {
     const GangClass c = GangTab<R>::c[k];
     if (B.half <= c.M * kGangHalf && gang_halos(B) <= c.H * kGangThreads && gang_extras(B) <= c.X * kGangHalf)
       return k;
@@ -255,26 +269,33 @@ __host__ __device__ inline size_t gang_state_words(int g, int cls) {
   return 4 * (size_t)g * GangTab<R>::c[cls].M * kGangThreads * (sizeof(R) / 4);
 }
 
-// Estimated time of one CG iteration of a cut, in microseconds: the work of the largest
-// block, and two exchanges that reach every workgroup.
+// Time of one CG iteration of a cut in microseconds, fitted to measurements (complex64 /
+// complex128; one workgroup 1.8 / 2.5 at 6x6x16; 12x12x32 3.25 / 4.7 with 8 workgroups and
+// 2.95 / 3.6 with 16; 24x24x64 3.5 / 5.0 with 64; 48x48x64 4.8 with 128, 4.2 / 6.2 with 256;
+// 102x102x64 8.9 with 256): the arithmetic of the largest block, and with more than one
+// workgroup a reduction and an exchange of faces.
 template <typename R>
-inline double gang_cost(const GangBlock& B, int g) {
-  const double site = sizeof(R) == 4 ? 0.45e-3 : 0.75e-3;
-  const int per = (B.half + kGangHalf - 1) / kGangHalf;
-  double t = 0.5 + site * kGangThreads * per;
-  if (g > 1) {
-    double hop = 1.1;
-    for (int k = 2; k <= g; k *= 2) hop += 0.2;
-    t += 2.0 * hop + 0.3e-3 * gang_halos(B) * (sizeof(R) / 4);
-  }
-  return t;
+inline double gang_cost(const GangBlock& B, int cls, int g) {
+  constexpr bool single = sizeof(R) == 4;
+  const int M = GangTab<R>::c[cls].M;
+  if (g == 1) return 0.9 + (single ? (M > 6 ? 0.4 : 0.32) : 0.55) * M;
+  double l = 0.0;
+  for (int k = 2; k <= g; k *= 2) l += 1.0;
+  if (single) return 1.75 + 0.14 * l + 0.42 * (M - 1) + (M > 6 ? 0.25 * (M - 6) : 0.0) + 0.3e-3 * gang_halos(B);
+  return 2.1 + 0.17 * l + 0.6 * (M - 1) + (M > 3 ? 0.6 : 0.0) + 0.5e-3 * gang_halos(B);
 }
 
 // The cut of a lattice; g = 0: none fits.  It depends on the lattice alone, so that a
-// system's results do not depend on what it shares a launch with.  The time of one
-// iteration is weighed against the share of the device a system takes.
+// system's results do not depend on what it shares a launch with: the shortest iteration
+// among the cuts whose workgroups times their time, per site, stay below what a launch full
+// of such systems may take.  The bounds are the device time per site and iteration of the
+// kernels that a batch would otherwise run on: the tiled iteration at a full device (88 and
+// 184 bytes per site at 5 TB/s over 256 CUs, less a fifth), and for complex64 systems of
+// up to 10,200 sites one workgroup per system (7.1 us at 9,216 sites) with 64 systems.
 template <typename R>
 inline GangCut gang_cut(int L1, int L2, int Nt) {
+  const double n = 2.0 * L1 * L2 * Nt;
+  const double room = n * (sizeof(R) == 8 ? 7.5e-3 : n > 10200 ? 3.6e-3 : 3.1e-3);
   GangCut best{0, 0, 0, 0, 0, 0};
   double cost = 0.0;
   for (int gt = 1; gt <= 16 && gt <= Nt; gt *= 2)
@@ -285,9 +306,13 @@ inline GangCut gang_cut(int L1, int L2, int Nt) {
         const GangBlock B = gang_largest(L1, L2, Nt, gt, gi, gj);
         const int cls = gang_class<R>(B);
         if (cls < 0) continue;
-        const double c = gang_cost<R>(B, g) * (1.0 + g / 64.0);
+        // a fifth more where the gangs of a full launch leave CUs over (sixteen systems of
+        // 18 workgroups take two launches, of 16 workgroups one); a cut beyond its room
+        // counts by how far it is beyond
+        const double t = gang_cost<R>(B, cls, g) * (kGangMaxWgs % g == 0 ? 1.0 : 1.2);
+        const double c = g == 1 || t * g <= room ? t : 1000.0 * t * g;
         if (best.g == 0 || c < cost) {
-          best = GangCut{gt, gi, gj, g, 2 * B.half, cls};
+          best = GangCut{gt, gi, gj, g, gang_slots(B), cls};
           cost = c;
         }
       }

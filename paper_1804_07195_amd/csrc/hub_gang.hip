@@ -26,6 +26,8 @@
 // with the tiled kernels.  Every later wait is bounded too.
 #include <hip/hip_ext.h>
 
+#include <type_traits>
+
 #include "hub_device.h"
 #include "hub_gang.h"
 
@@ -261,28 +263,31 @@ __device__ __forceinline__ void gang_run(const SysDesc* __restrict__ d, Scal* sc
   using TW = Tagged<C>;
   constexpr int M = GangTab<R>::c[CLS].M, H = GangTab<R>::c[CLS].H, X = GangTab<R>::c[CLS].X;
   constexpr bool single = sizeof(R) == 4;
-  constexpr int CH = !single && M > 3 ? 2 : M % 3 == 0 || M > 6 ? 3 : M % 4 == 0 ? 4 : M;
+  constexpr int CH = !single && M > 3 ? 2 : M > 6 ? 4 : M % 3 == 0 ? 3 : M;
   // The largest bodies have no registers left for the solution: it stays in the state
   // memory (the XCD's L2) and is read ahead of its update while the records travel.
-  constexpr bool ZMEM = CLS == kGangClasses - 1;
+  constexpr bool ZMEM = CLS == GangTab<R>::n - 1;
+  // Two bonds of a site share a register where a register per bond would not fit.
+  constexpr bool PACK = single ? M > 8 : M > 3;
   constexpr int sR = single ? (int)S_R32 : (int)S_R, sP = single ? (int)S_P32 : (int)S_P0;
-  __shared__ double2 red[kGangWaves];         // (gamma, |u|^2) of each wave
-  __shared__ double2 red2[kGangMaxWgs / 64];  // of each wave's share of the records
-  __shared__ int sh_off, sh_bad;
+  double2* const red = reinterpret_cast<double2*>(lds);        // (gamma, |u|^2) of each wave
+  double2* const red2 = red + kGangWaves;                      // of each wave's share of the records
+  int* const flag = reinterpret_cast<int*>(red2 + kGangMaxWgs / 64);
+  int &sh_off = flag[0], &sh_bad = flag[1];
+  static_assert((kGangWaves + kGangMaxWgs / 64) * 16 + 8 <= kGangHead, "head of the LDS");
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int g = d->gang.g, nslot = d->gang.nslot;
   if (tid == 0) sh_bad = 0;
   const GangBlock B = gang_block(d->g.L1, d->g.L2, d->g.Nt, d->gang.gt, d->gang.gi, d->gang.gj, wg);
   const int it0 = sc->git;
-  C* const F = reinterpret_cast<C*>(lds);  // the field: r, then M^dagger r in its place
-  C* const E = F + gang_table(B);          // the temporal links
+  C* const F = reinterpret_cast<C*>(lds + kGangHead);               // the field: r, then M^dagger r in its place
+  C* const E = reinterpret_cast<C*>(lds + kGangHead + kGangLinks);  // the temporal links
   const Mem mem(d->gang_mem, g > 1 ? gang_exch_words<R>(g, nslot) * 8 : 0);
   const unsigned rec_base = kGangCtlWords * 8, rec_half = (unsigned)g * (kGangRecWords * 8);
   const unsigned ex_base = rec_base + 2 * rec_half, ex_half = (unsigned)g * nslot * TW::BYTES;
 
   // This thread's sites: k = k0 + m kGangHalf of sublattice sub (the same in a whole wave).
-  // Places in the tables are kept as byte offsets, those of the two outer bonds as entries
-  // in the halves of one word.  Each list is worked out by a rolled loop into LDS and read
+  // Places in the tables are kept as byte offsets.  Each list is worked out by a rolled loop into LDS and read
   // back by the thread that wrote it: unrolled into registers, the index arithmetic of all
   // sites would be a hundred kilobytes of code.
   const int sub = __builtin_amdgcn_readfirstlane(tid / kGangHalf);
@@ -290,32 +295,34 @@ __device__ __forceinline__ void gang_run(const SysDesc* __restrict__ d, Scal* sc
   constexpr int SZ = (int)sizeof(C);
   const int dh = (sub ? -B.TS : B.TS) * SZ;  // to the bond inside the cell
   const int wrap = B.T * SZ;                 // from a slice to its copy past the end
-  const int eoff = gang_table(B) * SZ;       // from the field to the links
-  const int zero = gang_zero(B);
-  int4* const list = reinterpret_cast<int4*>(lds);
-  int a0[M];
-  unsigned hh[M];
-  unsigned ends = 0, sent = 0;  // ends: bit m: the first slice (time uncut), bit M + m: the last
+  auto place = [](int entry) { return kGangHead + entry * SZ; };
+  const int zero = place(gang_zero(B));
+  int4* const list = reinterpret_cast<int4*>(F);
+  int a0[M], h1[M], h2[M];  // packed: both bonds in h1, in units of 8 bytes
+  unsigned ends = 0, sent = 0;  // ends: bit m: the first slice, bit M + m: the last
 #pragma unroll 1
   for (int k = k0; k < B.half; k += kGangHalf) {
     const GangSite c = gang_site(B, k);
     int4 v;
-    v.x = gang_entry(B, c.i, c.j, sub, c.t + 1) * SZ;
+    v.x = place(gang_entry(B, c.i, c.j, sub, c.t + 1));
     gang_bonds(B, c.i, c.j, sub, c.t + 1, v.y, v.z);
-    v.w = (gang_sent(B, c) ? 1 : 0) | (B.gt == 1 && c.t == 0 ? 2 : 0) | (B.gt == 1 && c.t == B.T - 1 ? 4 : 0);
+    v.y = place(v.y);
+    v.z = place(v.z);
+    v.w = (gang_sent(B, c) ? 1 : 0) | (c.t == 0 ? 2 : 0) | (c.t == B.T - 1 ? 4 : 0);
     list[sub * B.half + k] = v;
   }
 #pragma unroll
   for (int m = 0; m < M; ++m) {
-    a0[m] = zero * SZ;
-    hh[m] = (unsigned)zero << 16 | (unsigned)zero;
+    a0[m] = h1[m] = h2[m] = zero;
     if (k0 + m * kGangHalf < B.half) {
       const int4 v = list[sub * B.half + k0 + m * kGangHalf];
       a0[m] = v.x;
-      hh[m] = (unsigned)v.z << 16 | (unsigned)v.y;
+      h1[m] = v.y;
+      h2[m] = v.z;
       sent |= (unsigned)(v.w & 1) << m;
       ends |= (unsigned)(v.w >> 1 & 1) << m | (unsigned)(v.w >> 2 & 1) << (M + m);
     }
+    if (PACK) h1[m] = h1[m] >> 3 | h2[m] >> 3 << 16;
   }
   __syncthreads();
   // Halo elements this thread receives: byte offset at the sender; place here and, in the
@@ -332,17 +339,16 @@ __device__ __forceinline__ void gang_run(const SysDesc* __restrict__ d, Scal* sc
     gang_source(B, el, src, k);
     int2 v;
     v.x = (int)(((unsigned)src * nslot + k) * TW::BYTES);
-    v.y = gang_entry(B, el.i, el.j, el.s, el.te) * SZ | (B.gt == 1 && el.te == 1 ? 1 << 18 : 0) |
+    v.y = place(gang_entry(B, el.i, el.j, el.s, el.te)) | (B.gt == 1 && el.te == 1 ? 1 << 18 : 0) |
           (B.gt == 1 && el.te == B.T ? 1 << 19 : 0);
-    reinterpret_cast<int2*>(lds)[e] = v;
+    reinterpret_cast<int2*>(F)[e] = v;
   }
 #pragma unroll
   for (int h = 0; h < H; ++h) {
     const int e = tid + h * kGangThreads;
-    hsrc[h] = 0;
-    hdst[h] = 0;
+    hsrc[h] = hdst[h] = 0;
     if (e < nh) {
-      const int2 v = reinterpret_cast<const int2*>(lds)[e];
+      const int2 v = reinterpret_cast<const int2*>(F)[e];
       hsrc[h] = (unsigned)v.x;
       hdst[h] = (unsigned)v.y;
       hvalid |= 1u << h;
@@ -350,31 +356,34 @@ __device__ __forceinline__ void gang_run(const SysDesc* __restrict__ d, Scal* sc
   }
   __syncthreads();
   // Extra sites it computes.
-  int xa[X];
-  unsigned xh[X];
+  int xa[X], x1[X], x2[X];
   const int nx = g > 1 ? gang_extras(B) : 0;
 #pragma unroll 1
   for (int e = k0; e < nx; e += kGangHalf) {
     int i, j, te;
     gang_extra(B, sub, e, i, j, te);
     int4 v;
-    v.x = gang_entry(B, i, j, sub, te) * SZ;
+    v.x = place(gang_entry(B, i, j, sub, te));
     gang_bonds(B, i, j, sub, te, v.y, v.z);
+    v.y = place(v.y);
+    v.z = place(v.z);
     v.w = 0;
     list[sub * nx + e] = v;
   }
 #pragma unroll
   for (int x = 0; x < X; ++x) {
-    xa[x] = zero * SZ;
-    xh[x] = (unsigned)zero << 16 | (unsigned)zero;
+    xa[x] = x1[x] = x2[x] = zero;
     if (k0 + x * kGangHalf < nx) {
       const int4 v = list[sub * nx + k0 + x * kGangHalf];
       xa[x] = v.x;
-      xh[x] = (unsigned)v.z << 16 | (unsigned)v.y;
+      x1[x] = v.y;
+      x2[x] = v.z;
     }
+    if (PACK) x1[x] = x1[x] >> 3 | x2[x] >> 3 << 16;
   }
   __syncthreads();
   auto at = [&](int off) -> C& { return *reinterpret_cast<C*>(lds + off); };
+  auto link = [&](int off) -> C& { return *reinterpret_cast<C*>(lds + off + kGangLinks); };
 
   // links of the extended block (j fastest: consecutive lanes read consecutive sites)
 #pragma unroll 4
@@ -466,11 +475,30 @@ __device__ __forceinline__ void gang_run(const SysDesc* __restrict__ d, Scal* sc
 
   // Own faces out; a halo element in.
   const unsigned mine = ((unsigned)wg * nslot + sub * B.half + k0) * TW::BYTES;
-  auto publish = [&](const C* v, unsigned tag, unsigned se) {
-    const unsigned ex = ex_base + (tag & 1) * ex_half;
-    gang_chunks<M, CH>(B.half, [&](int m) {
-      if (se >> m & 1) TW::store(mem, mine + m * kGangHalf * TW::BYTES, ex, v[m], tag);
-    });
+  const unsigned plane = ((unsigned)wg * nslot + gang_plane(B, 0, sub, 0)) * TW::BYTES;
+  auto publish = [&](const C* v, unsigned tag, int o) {
+    const unsigned ex = ex_base + (tag & 1) * ex_half, se = sent + (unsigned)o, en = ends + (unsigned)o;
+    auto column = [&](int m) {
+      if (se >> m & 1) TW::store(mem, mine + (unsigned)((M > 6 ? o : 0) + m * kGangHalf * TW::BYTES), ex, v[m], tag);
+    };
+    auto planes = [&](int m) {
+      const unsigned first = en >> m & 1, last = en >> (M + m) & 1;
+      if (first | last) {
+        const unsigned cell = plane + (unsigned)(gang_div(k0 + o + m * kGangHalf, B.rT) * TW::BYTES);
+        const unsigned up = (unsigned)(2 * B.a * B.b * TW::BYTES);
+        if (first) TW::store(mem, cell, ex, v[m], tag);
+        if (last) TW::store(mem, cell + up, ex, v[m], tag);
+      }
+    };
+    if (M > 6) {  // one pass over the sites: two keep more in registers
+      gang_chunks<M, CH>(B.half, [&](int m) {
+        column(m);
+        if (B.gt > 1) planes(m);
+      });
+    } else {
+      if (B.oi || B.oj) gang_chunks<M, CH>(B.half, column);
+      if (B.gt > 1 && en != 0) gang_chunks<M, CH>(B.half, planes);
+    }
   };
   auto receive = [&](unsigned tag, auto use) {
     const unsigned ex = ex_base + (tag & 1) * ex_half;
@@ -540,19 +568,20 @@ __device__ __forceinline__ void gang_run(const SysDesc* __restrict__ d, Scal* sc
       });
     }
   };
-  // Half an operator application at one site: own - e x(t + dt) + k sum of bonds.
-  auto half_op = [&](C e, C xt, C x0, C y1, C y2, R k, C own) {
+  // Half an operator application at one site: own - e x(t + dt) + k sum of bonds, with e
+  // conjugated for M^dagger (eg = -1).
+  auto half_op = [&](C e, auto adj, C xt, C x0, C y1, C y2, R k, C own) {
+    constexpr bool ADJ = decltype(adj)::value;
     C v;
-    v.x = own.x - (e.x * xt.x - e.y * xt.y) + k * (x0.x + y1.x + y2.x);
-    v.y = own.y - (e.x * xt.y + e.y * xt.x) + k * (x0.y + y1.y + y2.y);
+    v.x = fma(k, x0.x + y1.x + y2.x, fma(ADJ ? -e.y : e.y, xt.y, fma(-e.x, xt.x, own.x)));
+    v.y = fma(k, x0.y + y1.y + y2.y, fma(ADJ ? e.y : -e.y, xt.x, fma(-e.x, xt.y, own.y)));
     return v;
   };
-  auto conj = [](C e) {
-    e.y = -e.y;
-    return e;
-  };
-  auto lo = [&](unsigned h) -> C& { return at((int)(h & 0xffff) * SZ); };
-  auto hi = [&](unsigned h) -> C& { return at((int)(h >> 16) * SZ); };
+  // The two outer bonds of a site (o is zero, see the iteration loop).
+  auto low = [&](int b1) -> C { return at(b1 << 3 & 0x7fff8); };
+  auto high = [&](int b1) -> C { return at((int)((unsigned)b1 >> 13 & 0x7fff8)); };
+  auto bond1 = [&](int b1, int o) -> C { return PACK ? low(b1 + o) : at(b1); };
+  auto bond2 = [&](int b1, int b2, int o) -> C { return PACK ? high(b1 + o) : at(b2); };
 
   // r and s of the halo: sent once per launch, then carried along with the owner's own
   // arithmetic, so that the faces of w can travel while the reduction does.
@@ -561,8 +590,8 @@ __device__ __forceinline__ void gang_run(const SysDesc* __restrict__ d, Scal* sc
   for (int h = 0; h < H; ++h) rh[h] = sh[h] = cz<C>();
   put_own(r, 0);
   if (g > 1) {
-    publish(r, tag0 + 1, sent);
-    if (it0 > 0) publish(s, tag0 + 2, sent);
+    publish(r, tag0 + 1, 0);
+    if (it0 > 0) publish(s, tag0 + 2, 0);
     receive(tag0 + 1, [&](int h, C v) {
       rh[h] = v;
       put(hdst[h], v, 0);
@@ -589,17 +618,19 @@ __device__ __forceinline__ void gang_run(const SysDesc* __restrict__ d, Scal* sc
       return o;
     };
     int o = unseen();
-    int o_h = o + dh, o_t = o + dt1, o_e = o + dt1 + eoff;
+    int o_h = o + dh, o_t = o + dt1;
     // v = M^dagger r (times -1 on A) here and at the extra sites; gamma, |u|^2
     C v[M], xv[X];
     R acc_g = 0, acc_u = 0;
     gang_chunks<M, CH>(B.half, [&](int m) {
-      v[m] = half_op(conj(at(a0[m] + o_e)), at(a0[m] + o_t), at(a0[m] + o_h), lo(hh[m] + o), hi(hh[m] + o), ks, r[m]);
-      acc_g += r[m].x * r[m].x + r[m].y * r[m].y;
-      acc_u += v[m].x * v[m].x + v[m].y * v[m].y;
+      v[m] = half_op(link(a0[m] + o_t), std::true_type{}, at(a0[m] + o_t), at(a0[m] + o_h), bond1(h1[m], o),
+                     bond2(h1[m], h2[m], o), ks, r[m]);
+      acc_g = fma(r[m].x, r[m].x, fma(r[m].y, r[m].y, acc_g));
+      acc_u = fma(v[m].x, v[m].x, fma(v[m].y, v[m].y, acc_u));
     });
     gang_chunks<X, X>(nx, [&](int x) {
-      xv[x] = half_op(conj(at(xa[x] + o_e)), at(xa[x] + o_t), at(xa[x] + o_h), lo(xh[x] + o), hi(xh[x] + o), ks, at(xa[x]));
+      xv[x] = half_op(link(xa[x] + o_t), std::true_type{}, at(xa[x] + o_t), at(xa[x] + o_h), bond1(x1[x], o),
+                      bond2(x1[x], x2[x], o), ks, at(xa[x]));
     });
     acc_g = dpp_wave(acc_g);
     acc_u = dpp_wave(acc_u);
@@ -621,13 +652,14 @@ __device__ __forceinline__ void gang_run(const SysDesc* __restrict__ d, Scal* sc
     __syncthreads();
     // w = M u + mu^2 r, in v; its faces out
     o = unseen();
-    o_h = o + dh, o_t = o - dt1, o_e = o + eoff;
+    o_h = o + dh, o_t = o - dt1;
     gang_chunks<M, CH>(B.half, [&](int m) {
-      v[m] = half_op(at(a0[m] + o_e), at(a0[m] + o_t), at(a0[m] + o_h), lo(hh[m] + o), hi(hh[m] + o), -ks, v[m]);
-      v[m].x += rmu2 * r[m].x;
-      v[m].y += rmu2 * r[m].y;
+      v[m] = half_op(link(a0[m]), std::false_type{}, at(a0[m] + o_t), at(a0[m] + o_h), bond1(h1[m], o),
+                     bond2(h1[m], h2[m], o), -ks, v[m]);
+      v[m].x = fma(rmu2, r[m].x, v[m].x);
+      v[m].y = fma(rmu2, r[m].y, v[m].y);
     });
-    if (g > 1) publish(v, tag, sent + (unsigned)o);
+    if (g > 1) publish(v, tag, o);
     if (ZMEM) load(z, 3, o);
     if (g > 1 && wave < nw) collect(tag);
     __syncthreads();
@@ -706,22 +738,25 @@ __device__ __forceinline__ void gang_run(const SysDesc* __restrict__ d, Scal* sc
 template <typename R>
 __global__ __launch_bounds__(kGangThreads) void k_gang(const SysDesc* __restrict__ sys, GangList L, int K) {
   extern __shared__ __attribute__((aligned(16))) char gang_mem_lds[];
-  int kk = 0;
-  while (kk + 1 < L.nsys && L.begin[kk + 1] <= (int)blockIdx.x) ++kk;
+  const int kk = L.list[blockIdx.x], wg = L.wg[blockIdx.x];
+  if (kk == kGangNone) return;
   const SysDesc* __restrict__ d = sys + L.sys[kk];
   Scal* sc = L.scal + L.sys[kk];
-  const int wg = (int)blockIdx.x - L.begin[kk];
   // every workgroup of a launch counts among the arrivals, also of a system that has stopped
   unsigned arrived = 0;
   if (d->gang.g > 1 && threadIdx.x == 0)
     arrived = __hip_atomic_fetch_add((HUB_GAS unsigned*)d->gang_mem, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
   if (load_active(sc) != 1) return;
+  static_assert(GangTab<float>::n == 7 && GangTab<double>::n == 4, "the cases below");
+  constexpr int last = GangTab<R>::n - 1;
   switch (d->gang.cls) {
     case 0: return gang_run<R, 0>(d, sc, wg, L.pi[kk], L.tag[kk], L.seq[kk], arrived, K, gang_mem_lds);
     case 1: return gang_run<R, 1>(d, sc, wg, L.pi[kk], L.tag[kk], L.seq[kk], arrived, K, gang_mem_lds);
     case 2: return gang_run<R, 2>(d, sc, wg, L.pi[kk], L.tag[kk], L.seq[kk], arrived, K, gang_mem_lds);
     case 3: return gang_run<R, 3>(d, sc, wg, L.pi[kk], L.tag[kk], L.seq[kk], arrived, K, gang_mem_lds);
-    default: return gang_run<R, 4>(d, sc, wg, L.pi[kk], L.tag[kk], L.seq[kk], arrived, K, gang_mem_lds);
+    case 4: return gang_run<R, last < 4 ? last : 4>(d, sc, wg, L.pi[kk], L.tag[kk], L.seq[kk], arrived, K, gang_mem_lds);
+    case 5: return gang_run<R, last < 5 ? last : 5>(d, sc, wg, L.pi[kk], L.tag[kk], L.seq[kk], arrived, K, gang_mem_lds);
+    default: return gang_run<R, last>(d, sc, wg, L.pi[kk], L.tag[kk], L.seq[kk], arrived, K, gang_mem_lds);
   }
 }
 
@@ -758,33 +793,30 @@ __global__ __launch_bounds__(kBlock) void k_gang_clear(u64* p, size_t n) {
 }  // namespace
 
 template <typename R>
-static hipError_t gang_launch(const SysDesc* sys, const GangList& L, int K, size_t lds, hipStream_t st, hipEvent_t e0,
-                              hipEvent_t e1) {
-  const dim3 grid(L.begin[L.nsys]), block(kGangThreads);
+static hipError_t gang_launch(const SysDesc* sys, const GangList& L, int K, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
+  const dim3 grid(L.nblock), block(kGangThreads);
   // the tables exceed the default limit of dynamic LDS
   const hipError_t e = hipFuncSetAttribute((const void*)k_gang<R>, hipFuncAttributeMaxDynamicSharedMemorySize, kGangLdsBytes);
   if (e != hipSuccess) return e;
   if (e0)
-    hipExtLaunchKernelGGL(k_gang<R>, grid, block, lds, st, e0, e1, 0, sys, L, K);
+    hipExtLaunchKernelGGL(k_gang<R>, grid, block, kGangLdsBytes, st, e0, e1, 0, sys, L, K);
   else
-    hipLaunchKernelGGL(k_gang<R>, grid, block, lds, st, sys, L, K);
+    hipLaunchKernelGGL(k_gang<R>, grid, block, kGangLdsBytes, st, sys, L, K);
   return hipGetLastError();
 }
 
-hipError_t launch_gang(const SysDesc* sys, const GangList& L, int K, bool single, size_t lds, hipStream_t st,
-                       hipEvent_t e0, hipEvent_t e1) {
-  if (L.nsys < 1 || L.nsys > kMaxSys || K < 1 || L.begin[L.nsys] < 1 || L.begin[L.nsys] > kGangMaxWgs ||
-      lds > (size_t)kGangLdsBytes)
+hipError_t launch_gang(const SysDesc* sys, const GangList& L, int K, bool single, hipStream_t st, hipEvent_t e0,
+                       hipEvent_t e1) {
+  if (L.nsys < 1 || L.nsys > kMaxSys || K < 1 || L.nblock < 1 || L.nblock > kGangMaxWgs)
     return hipErrorInvalidValue;
-  return single ? gang_launch<float>(sys, L, K, lds, st, e0, e1) : gang_launch<double>(sys, L, K, lds, st, e0, e1);
+  return single ? gang_launch<float>(sys, L, K, st, e0, e1) : gang_launch<double>(sys, L, K, st, e0, e1);
 }
 
-hipError_t launch_gang_leave(const SysDesc* sys, const GangList& L, int ntiles, bool single, size_t lds, hipStream_t st) {
-  if (L.nsys != 1 || L.begin[1] < 1 || L.begin[1] > kGangMaxWgs || lds > (size_t)kGangLdsBytes || ntiles < 1)
-    return hipErrorInvalidValue;
+hipError_t launch_gang_leave(const SysDesc* sys, const GangList& L, int ntiles, bool single, hipStream_t st) {
+  if (L.nsys != 1 || L.nblock < 1 || L.nblock > kGangMaxWgs || ntiles < 1) return hipErrorInvalidValue;
   // zero iterations: the state back to the slots (no workgroup waits for another)
-  const hipError_t e = single ? gang_launch<float>(sys, L, 0, lds, st, nullptr, nullptr)
-                              : gang_launch<double>(sys, L, 0, lds, st, nullptr, nullptr);
+  const hipError_t e = single ? gang_launch<float>(sys, L, 0, st, nullptr, nullptr)
+                              : gang_launch<double>(sys, L, 0, st, nullptr, nullptr);
   if (e != hipSuccess) return e;
   if (single)
     hipLaunchKernelGGL(k_gang_leave<float>, dim3(ntiles), dim3(kBlock), 0, st, sys, L.sys[0]);

@@ -178,17 +178,20 @@ struct WgList {
   int sys[kMaxSys];
 };
 
-// Systems of one gang launch: system sys[k], iterating into solution slot pi[k], takes the
-// workgroups [begin[k], begin[k + 1]); tag[k]: exchange tags used so far, seq[k]: the
-// number of this launch of the system (from 1).
+// Systems of one gang launch: system sys[k], iterating into solution slot pi[k]; tag[k]:
+// exchange tags used so far, seq[k]: the number of this launch of the system (from 1).
+// Block b of the launch is workgroup wg[b] of system list[b] (kGangNone: of none).
+constexpr unsigned char kGangNone = 255;
 struct GangList {
   Scal* scal;
   int nsys;
-  int begin[kMaxSys + 1];
+  int nblock;
   int sys[kMaxSys];
   int pi[kMaxSys];
   unsigned tag[kMaxSys];
   unsigned seq[kMaxSys];
+  unsigned char list[kGangMaxWgs];
+  unsigned char wg[kGangMaxWgs];
 };
 
 // Tile class of a system: sites per thread of all its solver kernels.  Large systems
@@ -303,14 +306,13 @@ hipError_t launch_cg_iter(const SysDesc* sys, const LaunchList& L, bool single, 
 // kernel's own start and end timestamps into them (hipExtLaunchKernel).
 hipError_t launch_cg_stage(const SysDesc* sys, const LaunchList& L, bool single, int stage, hipStream_t st,
                            hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
-// Up to K iterations of the CG of every system of L, each by its gang (hub_gang.hip), `lds`
-// bytes for the largest block's tables; optional start/stop events.  At most kGangMaxWgs
-// workgroups in all.
-hipError_t launch_gang(const SysDesc* sys, const GangList& L, int K, bool single, size_t lds, hipStream_t st,
+// Up to K iterations of the CG of every system of L, each by its gang (hub_gang.hip);
+// optional start/stop events.  At most kGangMaxWgs workgroups in all.
+hipError_t launch_gang(const SysDesc* sys, const GangList& L, int K, bool single, hipStream_t st,
                        hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
 // The one system of L goes on with the tiled kernels at the iteration its gang has reached:
 // the vectors back to their slots, and what stage 1 of the tiled iteration expects.
-hipError_t launch_gang_leave(const SysDesc* sys, const GangList& L, int ntiles, bool single, size_t lds, hipStream_t st);
+hipError_t launch_gang_leave(const SysDesc* sys, const GangList& L, int ntiles, bool single, hipStream_t st);
 // Exchange memory starts from zero (no tag is 0).
 hipError_t launch_gang_clear(unsigned long long* mem, size_t words, hipStream_t st);
 // Arnoldi step j (w = A z_j, Gram-Schmidt against v_0 .. v_j, |w|^2 into the Scal records)

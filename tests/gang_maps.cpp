@@ -85,7 +85,7 @@ static int check(const Lat& l, int gt, int gi, int gj) {
   for (auto& z : r) z = cd(rnd(), rnd());
   const std::vector<cd> want = apply(l, phi, apply(l, phi, r, true), false);
   const GangBlock big = gang_largest(l.L1, l.L2, l.Nt, gt, gi, gj);
-  const int nslot = 2 * big.half;
+  const int nslot = gang_slots(big);
   std::vector<cd> exch((size_t)G * nslot);
   std::vector<char> sent((size_t)G * nslot, 0);
   std::vector<int> owners(l.n(), 0);
@@ -99,10 +99,14 @@ static int check(const Lat& l, int gt, int gi, int gj) {
         const GangSite c = gang_site(B, k);
         const int n = l.at(B.t0 + c.t, s, B.i0 + c.i, B.j0 + c.j);
         owners[n]++;
-        if (gang_sent(B, c)) {
-          exch[(size_t)wg * nslot + s * B.half + k] = r[n];
-          sent[(size_t)wg * nslot + s * B.half + k] = 1;
-        }
+        auto send = [&](int place) {
+          exch[(size_t)wg * nslot + place] = r[n];
+          sent[(size_t)wg * nslot + place] = 1;
+        };
+        if (gang_slots(B) > nslot) return fail("more elements than slots", l, gt, gi, gj);
+        if (gang_sent(B, c)) send(s * B.half + k);
+        if (gt > 1 && c.t == 0) send(gang_plane(B, 0, s, gang_div(k, B.rT)));
+        if (gt > 1 && c.t == B.T - 1) send(gang_plane(B, 1, s, gang_div(k, B.rT)));
       }
   }
   for (int o : owners)
@@ -179,12 +183,12 @@ static int chosen(const Lat& l, bool show) {
     return 0;
   }
   const GangBlock B = gang_largest(l.L1, l.L2, l.Nt, c.gt, c.gi, c.gj);
-  if (c.g != c.gt * c.gi * c.gj || c.g > kGangMaxWgs || gang_class<R>(B) != c.cls || c.nslot != 2 * B.half)
+  if (c.g != c.gt * c.gi * c.gj || c.g > kGangMaxWgs || gang_class<R>(B) != c.cls || c.nslot != gang_slots(B))
     return fail("the chosen cut", l, c.gt, c.gi, c.gj);
   if (show)
-    std::printf("%s %dx%dx%d: %dx%dx%d = %d, class %d half %d halos %d extras %d lds %zu cost %.2f\n", sizeof(R) == 4 ? "f32" : "f64",
+    std::printf("%s %dx%dx%d: %dx%dx%d = %d, class %d half %d halos %d extras %d table %d cost %.2f\n", sizeof(R) == 4 ? "f32" : "f64",
                 l.L1, l.L2, l.Nt, c.gt, c.gi, c.gj, c.g, c.cls, B.half, gang_halos(B), gang_extras(B),
-                gang_lds<R>(B), gang_cost<R>(B, c.g));
+                gang_table(B), gang_cost<R>(B, c.cls, c.g));
   return l.n() <= 40000 ? check(l, c.gt, c.gi, c.gj) : 0;
 }
 

@@ -3,7 +3,8 @@
 * FP64: the k-th iterate against the oracle's textbook CG (1e-12, as for the other CG
   kernels) for one workgroup, cuts in time, in space and in both, partly filled bodies,
   and iterations past the end of a launch (the state kept between launches).
-* complex64: mixed solves over the same range, judged by the oracle's true residual.
+* Mixed solves over the same range and solves with the bodies of the largest blocks,
+  judged by the oracle's true residual.
 * Gangs of several contexts that do not fit on the device together, at once: every
   solve is what it is alone.
 """
@@ -13,6 +14,7 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 from oracle.operator import NormalOperator
 from oracle.solve import cg as oracle_cg
 from paper_1804_07195_amd import binding as hb
@@ -55,13 +57,18 @@ def test_fp64_iterates(hub, shape):
             break
 
 
-@pytest.mark.parametrize("shape", SHAPES + [(48, 48, 32)], ids=["x".join(map(str, s)) for s in SHAPES + [(48, 48, 32)]])
-def test_mixed_residual(hub, shape):
+# with the bodies of the largest blocks: eight and eleven sites per thread, four in FP64
+LARGE = [((48, 48, 32), "fgmres"), ((102, 77, 48), "fgmres"), ((102, 77, 64), "fgmres"), ((102, 77, 24), "cg")]
+SOLVES = [(s, "fgmres") for s in SHAPES + [(10, 9, 12), (10, 4, 20)]] + LARGE
+
+
+@pytest.mark.parametrize("shape,solver", SOLVES, ids=["x".join(map(str, s)) + "-" + v for s, v in SOLVES])
+def test_residual(hub, shape, solver):
     hl, ol, phi, b = _field(shape, 8, ms=0.03)
-    mu2 = [0.0, 0.3]
-    x, info, _ = hb.hub_solve(hub, hl, dev(phi), mu2, dev(np.stack([b, b])), opts=hb.default_opts(solver="fgmres"))
+    mu2 = [0.01, 0.3]
+    x, info, _ = hb.hub_solve(hub, hl, dev(phi), mu2, dev(np.stack([b, b])), opts=hb.default_opts(solver=solver))
     for k, m in enumerate(mu2):
-        r = b.ravel() - NormalOperator(ol, phi, m)(host(x)[k].ravel())
+        r = b - oracle.normal_apply(ol, phi, m, host(x)[k])
         assert np.linalg.norm(r) <= 1e-10 * np.linalg.norm(b)
 
 
