@@ -484,28 +484,30 @@ hub_status run_solves(hub_ctx* ctx, std::vector<System>& sys, const hub_solve_op
   if (!eng) return HUB_ERR_OOM;
   // the phase e^{i phi} once per distinct phi (the float angle too for the mixed solver)
   const bool want32 = o.solver == HUB_FGMRES_MIXED;
-  struct Phase {
-    double2* p64;
-    float* p32;
-  };
-  std::map<const double*, Phase> phase;
+  std::map<const double*, PhaseJob> phase;
+  PhaseJobs J;
+  int nj = 0;
   std::vector<void*> owned;
   hub_status result = HUB_OK;
-  for (System& sy : sys) {
-    if (phase.count(sy.phi)) continue;
-    double2* p64 = (double2*)ctx->pool->alloc((size_t)sy.g.n * 16, stream);
-    float* p32 = want32 ? (float*)ctx->pool->alloc((size_t)sy.g.n * 4, stream) : nullptr;
-    if (p64) owned.push_back(p64);
-    if (p32) owned.push_back(p32);
-    if (!p64 || (want32 && !p32)) {
-      result = fail(HUB_ERR_OOM, "workspace for the phase of phi");
-      break;
-    }
-    phase[sy.phi] = {p64, p32};
-    const hipError_t e = launch_phase(sy.phi, p64, p32, sy.g.n, stream);
-    if (e != hipSuccess) {
-      result = hip_fail(e, "phase");
-      break;
+  const size_t N = sys.empty() ? 0 : (size_t)sys[0].g.n;  // one lattice size per call
+  for (const System& sy : sys)
+    if (phase.emplace(sy.phi, PhaseJob{sy.phi, nullptr, nullptr}).second) ++nj;
+  const size_t b64 = (N * 16 + 255) / 256 * 256, b32 = want32 ? (N * 4 + 255) / 256 * 256 : 0;
+  char* mem = (char*)ctx->pool->alloc((size_t)nj * (b64 + b32), stream);
+  if (mem)
+    owned.push_back(mem);
+  else
+    result = fail(HUB_ERR_OOM, "workspace for the phase of phi");
+  nj = 0;
+  for (auto it = phase.begin(); it != phase.end() && result == HUB_OK;) {
+    it->second.p64 = (double2*)mem;
+    it->second.p32 = want32 ? (float*)(mem + b64) : nullptr;
+    mem += b64 + b32;
+    J.j[nj++] = it->second;
+    if (++it == phase.end() || nj == kMaxSys) {
+      const hipError_t e = launch_phase_jobs(J, nj, (int)N, stream);
+      if (e != hipSuccess) result = hip_fail(e, "phase");
+      nj = 0;
     }
   }
   size_t added = 0;

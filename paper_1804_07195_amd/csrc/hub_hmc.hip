@@ -18,7 +18,8 @@
 using namespace hub;
 using namespace hub::api;
 
-static_assert(HUB_MAX_HB_MASSES + 1 == kMaxLevels, "Hasenbusch levels");
+static_assert(HUB_MAX_HB_MASSES + 1 == kMaxLevels && kMaxLevels == kMaxTerms, "Hasenbusch levels");
+static_assert(HUB_MAX_BATCH <= kMaxSys, "one launch takes the terms of every chain");
 static_assert(HUB_MAX_HB_MASSES + 1 <= kMaxSys, "one batched solve per term");
 static_assert(sizeof(hub_hmc_params) == 232 && sizeof(hub_md_op) == 152 && sizeof(hub_hmc_info) == 120,
               "HMC struct layouts");
@@ -58,35 +59,38 @@ hub_status heatbath_impl(hub_ctx* ctx, const hub_lattice& lat, const double* mt,
                          const hub_solve_opts& o, hipStream_t stream) {
   const size_t N = (size_t)make_geom(lat).n;
   const int C = (int)ch.size();
-  for (const Chain& c : ch)
-    HUB_HIP(launch_apply(geom_with_mass(lat, mt, n - 1), c.phi, c.rho + n * N, c.chi + n * N, 1, false, stream),
-            "apply");
+  const Geom g = make_geom(lat);
+  auto mass = [&](int i) { return geom_with_mass(lat, mt, i).ms; };
+  ApplyJobs J;
+  for (int c = 0; c < C; ++c) J.j[c] = {ch[c].phi, ch[c].rho + n * N, ch[c].chi + n * N, mass(n - 1)};
+  HUB_HIP(launch_apply_jobs(g, J, C, false, stream), "apply");
   if (n == 0) HUB_HIP(hipStreamSynchronize(stream), "heat-bath");
   if (n == 0) return HUB_OK;
   double2* w = (double2*)ctx->pool->alloc(2 * (size_t)C * n * N * 16, stream);
   if (!w) return fail(HUB_ERR_OOM, "heat-bath workspace");
   double2* y = w + (size_t)C * n * N;
   std::vector<System> sys((size_t)C * n);
-  hipError_t e = hipSuccess;
-  for (int c = 0; c < C && e == hipSuccess; ++c)
-    for (int i = 0; i < n && e == hipSuccess; ++i) {
+  for (int c = 0; c < C; ++c)
+    for (int i = 0; i < n; ++i) {
       const size_t k = (size_t)c * n + i;
-      e = launch_apply(geom_with_mass(lat, mt, i - 1), ch[c].phi, ch[c].rho + i * N, w + k * N, 1, false, stream);
+      J.j[k] = {ch[c].phi, ch[c].rho + i * N, w + k * N, mass(i - 1)};
       sys[k].g = geom_with_mass(lat, mt, i);
       sys[k].phi = ch[c].phi;
       sys[k].mu2 = 0.0;
       sys[k].b = w + k * N;
       sys[k].x = y + k * N;
     }
+  hipError_t e = launch_apply_jobs(g, J, C * n, false, stream);
   hub_solve_opts oz = o;
   oz.use_x0 = 0;
   hub_status result = e == hipSuccess ? run_solves(ctx, sys, oz, stream) : hip_fail(e, "apply");
   if (result == HUB_OK || result == HUB_ERR_NOCONV) {
-    for (int c = 0; c < C && e == hipSuccess; ++c)
-      for (int i = 0; i < n && e == hipSuccess; ++i) {
+    for (int c = 0; c < C; ++c)
+      for (int i = 0; i < n; ++i) {
         const size_t k = (size_t)c * n + i;
-        e = launch_apply(sys[k].g, ch[c].phi, y + k * N, ch[c].chi + i * N, 1, true, stream);
+        J.j[k] = {ch[c].phi, y + k * N, ch[c].chi + i * N, mass(i)};
       }
+    e = launch_apply_jobs(g, J, C * n, true, stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
     if (e != hipSuccess) result = hip_fail(e, "apply");
     for (int c = 0; c < C; ++c)
@@ -107,53 +111,48 @@ hub_status eval_impl(hub_ctx* ctx, const hub_lattice& lat, const double* mt, int
   const size_t N = (size_t)g.n;
   const int T = (int)terms.size();
   const int C = (int)ch.size();
-  const int nt = ntiles_of(g.n);
+  const int nt = (g.n + kBlock - 1) / kBlock;
   const size_t CT = (size_t)C * T;
-  // workspace: M_i chi_i for the ratio terms and xi, per (chain, term); dot partials and results
+  // workspace: M_i chi_i for the ratio terms, per (chain, term); dot partials and results
   const size_t vec_bytes = CT * N * 16;
   const size_t part_bytes = CT * nt * sizeof(double);
   const size_t res_bytes = ((CT * sizeof(double) + 255) / 256) * 256;
-  char* ws = (char*)ctx->pool->alloc(2 * vec_bytes + part_bytes + res_bytes, stream);
+  char* ws = (char*)ctx->pool->alloc(vec_bytes + part_bytes + res_bytes, stream);
   if (!ws) return fail(HUB_ERR_OOM, "Hasenbusch workspace");
   double2* wv = (double2*)ws;
-  double2* xv = (double2*)(ws + vec_bytes);
-  double* part = (double*)(ws + 2 * vec_bytes);
-  double* res = (double*)(ws + 2 * vec_bytes + part_bytes);
+  double* part = (double*)(ws + vec_bytes);
+  double* res = (double*)(ws + vec_bytes + part_bytes);
   std::vector<System> sys(CT);
-  std::vector<const double2*> rhs(CT);
-  hipError_t e = hipSuccess;
-  for (int c = 0; c < C && e == hipSuccess; ++c)
-    for (int k = 0; k < T && e == hipSuccess; ++k) {
+  ApplyJobs A;
+  TermJobs J;
+  int na = 0;
+  const bool force = ch[0].dS != nullptr;  // of every chain or of none
+  J.nterm = T;
+  J.accumulate = accumulate;
+  for (int k = 0; k < T; ++k) J.scale[k] = scales[k];
+  for (int c = 0; c < C; ++c) {
+    J.chain[c] = {ch[c].phi, ch[c].dS};
+    for (int k = 0; k < T; ++k) {
       const size_t q = (size_t)c * T + k;
       const int i = terms[k];
       const int den = i == n ? n - 1 : i - 1;
-      if (i == n) {
-        rhs[q] = ch[c].chi + i * N;
-      } else {
-        e = launch_apply(geom_with_mass(lat, mt, i), ch[c].phi, ch[c].chi + i * N, wv + q * N, 1, false, stream);
-        rhs[q] = wv + q * N;
-      }
+      const double2* chi = ch[c].chi + i * N;
+      const double2* rhs = i == n ? chi : wv + q * N;
+      if (i < n) A.j[na++] = {ch[c].phi, chi, wv + q * N, geom_with_mass(lat, mt, i).ms};
       sys[q].g = geom_with_mass(lat, mt, den);
       sys[q].phi = ch[c].phi;
       sys[q].mu2 = 0.0;
-      sys[q].b = rhs[q];
+      sys[q].b = rhs;
       sys[q].x = ch[c].eta + i * N;
+      // S_i = Re rhs_i^dag eta_i; xi_i = M_den^dag eta_i; dS_i/dphi with xi_i (- chi_i)
+      J.term[q] = {sys[q].x, rhs, i == n ? nullptr : chi, sys[q].g.ms};
     }
+  }
+  hipError_t e = na ? launch_apply_jobs(g, A, na, false, stream) : hipSuccess;
   hub_status result = e == hipSuccess ? run_solves(ctx, sys, o, stream) : hip_fail(e, "apply");
   if (result == HUB_OK || result == HUB_ERR_NOCONV) {
     std::vector<double> Sh(CT, 0.0);
-    for (int c = 0; c < C && e == hipSuccess; ++c)
-      for (int k = 0; k < T && e == hipSuccess; ++k) {
-        const size_t q = (size_t)c * T + k;
-        const int i = terms[k];
-        double2* et = ch[c].eta + i * N;
-        // S_i = Re rhs_i^dag eta_i; xi_i = M_den^dag eta_i; dS_i/dphi with xi_i (- chi_i)
-        e = launch_dot_re(g, rhs[q], et, 1, part + q * nt, res + q, stream);
-        if (e == hipSuccess) e = launch_apply(sys[q].g, ch[c].phi, et, xv + q * N, 1, true, stream);
-        if (e == hipSuccess && ch[c].dS)
-          e = launch_force(g, ch[c].phi, et, xv + q * N, scales[k], (k == 0) ? accumulate : 1, ch[c].dS, 1,
-                           stream, i == n ? nullptr : ch[c].chi + i * N);
-      }
+    e = launch_terms(g, J, C, force, part, res, stream);
     if (e == hipSuccess) e = hipMemcpyAsync(Sh.data(), res, CT * sizeof(double), hipMemcpyDeviceToHost, stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
     if (e != hipSuccess) {
@@ -229,21 +228,15 @@ hub_status hmc_impl(hub_ctx* ctx, const hub_lattice& lat, int C, double* phi, do
   std::vector<double> gauge(C), kin(C), gauge1(C), kin1(C);
   auto quadratic = [&](std::vector<double>& gs, std::vector<double>& ks) {
     std::vector<double> h(2 * (size_t)C);
-    for (int c = 0; c < C; ++c) {
-      const double2* pc = (const double2*)(phi + c * N);
-      const double2* qc = (const double2*)(pi + c * N);
-      if (!hip_check(launch_dot_re(gh, pc, pc, 1, part + (size_t)(2 * c) * nt2, res + 2 * c, stream), "norm"))
-        return false;
-      if (!hip_check(launch_dot_re(gh, qc, qc, 1, part + (size_t)(2 * c + 1) * nt2, res + 2 * c + 1, stream),
-                     "norm"))
-        return false;
-    }
+    const double2 *pv = (const double2*)phi, *qv = (const double2*)pi;
+    if (!hip_check(launch_dot_re(gh, pv, pv, C, part, res, stream), "norm")) return false;
+    if (!hip_check(launch_dot_re(gh, qv, qv, C, part + (size_t)C * nt2, res + C, stream), "norm")) return false;
     if (!hip_check(hipMemcpyAsync(h.data(), res, h.size() * sizeof(double), hipMemcpyDeviceToHost, stream), "norm"))
       return false;
     if (!hip_check(hipStreamSynchronize(stream), "norm")) return false;
     for (int c = 0; c < C; ++c) {
-      gs[c] = 0.5 * h[2 * c] / params->U_t;
-      ks[c] = 0.5 * h[2 * c + 1];
+      gs[c] = 0.5 * h[c] / params->U_t;
+      ks[c] = 0.5 * h[C + c];
     }
     return true;
   };

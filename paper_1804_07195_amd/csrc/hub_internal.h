@@ -271,10 +271,9 @@ enum RedMode : int {
 // non-temporally); otherwise library workspace that a following kernel reads.
 hipError_t launch_apply(const Geom& g, const double* phi, const double2* x, double2* y, int batch,
                         bool dag, hipStream_t st, bool to_caller = false);
-// out (+)= scale dS/dphi for eta and xi (minus `sub` when given: Hasenbusch ratio terms).
+// out (+)= scale dS/dphi for eta and xi.
 hipError_t launch_force(const Geom& g, const double* phi, const double2* eta, const double2* xi,
-                        double scale, int accumulate, double* out, int batch, hipStream_t st,
-                        const double2* sub = nullptr);
+                        double scale, int accumulate, double* out, int batch, hipStream_t st);
 // Measurement: a streaming kernel moving the bytes of one FP64 apply of n sites (mode 0:
 // non-temporal stores, 1: non-temporal loads, 2: plain).
 hipError_t launch_stream_bytes(const double* phi, const double2* x, double2* y, int n, int mode, hipStream_t st);
@@ -283,6 +282,53 @@ hipError_t launch_force_sum(const Geom& g, const double* phi, const double2* eta
                             const double* scale_host, int accumulate, double* out, int batch, hipStream_t st);
 hipError_t launch_dot_re(const Geom& g, const double2* a, const double2* b, int batch, double* part,
                          double* result, hipStream_t st);
+// The same work over fields that lie apart, up to kMaxSys jobs in one launch (jobs of one
+// lattice; the lists travel as kernel arguments, inside the 4 KiB these may take).
+struct ApplyJob {
+  const double* phi;
+  const double2* x;
+  double2* y;
+  double ms;
+};
+struct ApplyJobs {
+  ApplyJob j[kMaxSys];
+};
+// y = M x or M^dagger x of every job, with the job's own staggered mass.
+hipError_t launch_apply_jobs(const Geom& g, const ApplyJobs& J, int njob, bool dag, hipStream_t st);
+
+// What follows the solves of one kick group: term k of chain c is entry c * nterm + k.
+struct TermJob {
+  const double2* eta;  // solution
+  const double2* rhs;  // right-hand side it belongs to
+  const double2* sub;  // vector taken from xi (ratio terms) or NULL
+  double ms;           // mass of the operator that was solved with
+};
+struct ChainJob {
+  const double* phi;
+  double* dS;
+};
+constexpr int kMaxTerms = 17;  // terms of one chain
+struct TermJobs {
+  TermJob term[kMaxSys];
+  ChainJob chain[kMaxSys];
+  double scale[kMaxTerms];
+  int nterm, accumulate;
+};
+static_assert(sizeof(TermJobs) + sizeof(Geom) + 64 <= 4096, "kernel arguments");
+// result[q] = Re rhs_q^dagger eta_q and, if `force`, dS_c (+)= sum_k scale_k dS/dphi of
+// (eta, xi - sub) with xi = M^dagger eta, terms in order.  part: njob * nterm partials per
+// kBlock sites.
+hipError_t launch_terms(const Geom& g, const TermJobs& J, int nchain, bool force, double* part, double* result,
+                        hipStream_t st);
+struct PhaseJob {
+  const double* phi;
+  double2* p64;
+  float* p32;
+};
+struct PhaseJobs {
+  PhaseJob j[kMaxSys];
+};
+hipError_t launch_phase_jobs(const PhaseJobs& J, int njob, int n, hipStream_t st);
 // p64 = (cos phi, sin phi) in FP64 and, if p32 is not NULL, phi reduced to [-pi, pi]
 // and rounded to float (the complex64 kernels evaluate the phase from it).
 hipError_t launch_phase(const double* phi, double2* p64, float* p32, int n, hipStream_t st);

@@ -198,7 +198,8 @@ __device__ __forceinline__ C stencil_combine(const Geom& g, const SiteIdx& st, R
   const R sgn = st.wrap ? R(-1) : R(1);
   const R es = (st.isA != DAG) ? s : -s;
   const R cr = sgn * (c - (R)g.ms), ci = sgn * es;
-  const R tr = cr * xt.x - ci * xt.y, ti = cr * xt.y + ci * xt.x;
+  // the product written out: left to the compiler, the rounded half differs from kernel to kernel
+  const R tr = fma(cr, xt.x, -(ci * xt.y)), ti = fma(cr, xt.y, ci * xt.x);
   const R sig = st.isA ? R(-1) : R(1);
   const R kap = (R)g.kappa;
   C y;
@@ -681,13 +682,12 @@ static int pub_group(int ntiles, int batch) {
 
 // dS/dphi at every site: A: 2 Im[conj(eta(t)) s e^{i phi} z(t-1)],
 //                        B: 2 Im[conj(eta(t)) s e^{-i phi} z(t+1)],
-// with z = xi, or z = xi - sub for the ratio terms of the Hasenbusch split
-// (eq. (f_chi_i)); the derivative of M does not depend on the staggered mass.
+// with z = xi; the derivative of M does not depend on the staggered mass.
 __global__ __launch_bounds__(kBlock) void k_force(Geom g, const double* __restrict__ phi,
                                                   const double2* __restrict__ eta,
                                                   const double2* __restrict__ xi,
-                                                  const double2* __restrict__ sub, double scale, int accumulate,
-                                                  double* __restrict__ out, int ntiles) {
+                                                  double scale, int accumulate, double* __restrict__ out,
+                                                  int ntiles) {
   const int l = xcd_remap(blockIdx.x, gridDim.x);
   const int b = l / ntiles, tile = l - b * ntiles;
   const size_t off = (size_t)b * g.n;
@@ -715,12 +715,7 @@ __global__ __launch_bounds__(kBlock) void k_force(Geom g, const double* __restri
       cis64(phi[n], c, s);
       if (!isA) s = -s;
       const double2 e = eta[off + n];
-      double2 z = xi[off + tn];
-      if (sub) {
-        const double2 v = sub[off + tn];
-        z.x -= v.x;
-        z.y -= v.y;
-      }
+      const double2 z = xi[off + tn];
       // w = sgn (c + i s) z ; F = 2 Im(conj(e) w)
       const double wr = sgn * (c * z.x - s * z.y), wi = sgn * (c * z.y + s * z.x);
       const double F = 2.0 * (e.x * wi - e.y * wr);
@@ -735,8 +730,8 @@ __global__ __launch_bounds__(kBlock) void k_force(Geom g, const double* __restri
 __global__ __launch_bounds__(kBlock) void k_force_grp(Geom g, const double* __restrict__ phi,
                                                       const double2* __restrict__ eta,
                                                       const double2* __restrict__ xi,
-                                                      const double2* __restrict__ sub, double scale, int accumulate,
-                                                      double* __restrict__ out, int ntiles, int per, int batch) {
+                                                      double scale, int accumulate, double* __restrict__ out,
+                                                      int ntiles, int per, int batch) {
   const int l = xcd_remap(blockIdx.x, gridDim.x);
   const int grp = l / ntiles, tile = l - grp * ntiles;
   const int b0 = grp * per, b1 = min(batch, b0 + per);
@@ -773,12 +768,7 @@ __global__ __launch_bounds__(kBlock) void k_force_grp(Geom g, const double* __re
       const int n = base + m * kBlock;
       if (n < g.n) {
         const double2 e = eta[off + n];
-        double2 z = xi[off + tn[m]];
-        if (sub) {
-          const double2 v = sub[off + tn[m]];
-          z.x -= v.x;
-          z.y -= v.y;
-        }
+        const double2 z = xi[off + tn[m]];
         // w = s e^{+-i phi} z ; F = 2 Im(conj(e) w)
         const double wr = ec[m] * z.x - es[m] * z.y, wi = ec[m] * z.y + es[m] * z.x;
         const double F = 2.0 * (e.x * wi - e.y * wr);
@@ -787,6 +777,83 @@ __global__ __launch_bounds__(kBlock) void k_force_grp(Geom g, const double* __re
       }
     }
   }
+}
+
+// y = M x or M^dagger x of several jobs (fields, vectors and masses of their own).  One
+// launch for all of them: a job of 256 to 4608 unknowns is a few microseconds of latency
+// by itself, so a launch per job leaves the device idle but for one workgroup (with
+// k_terms and k_phase_jobs: 32 chains of 2x1x64 through a trajectory 30.3 -> 14.1 ms).
+template <bool DAG>
+__global__ __launch_bounds__(kBlock) void k_apply_jobs(Geom g, ApplyJobs J, int ntiles) {
+  const int l = xcd_remap(blockIdx.x, gridDim.x);
+  const int q = l / ntiles, tile = l - q * ntiles;
+  const double2* __restrict__ x = J.j[q].x;
+  double2* __restrict__ y = J.j[q].y;
+  g.ms = J.j[q].ms;
+  const int base = tile * kPubTile + threadIdx.x;
+  auto ld = [=](int k) { return x[k]; };
+  auto pre = [](int) { return NoPre{}; };
+  auto post = [=](int n, double2 v, double2, NoPre) { y[n] = v; };
+  stencil_sites<double, DAG, kPubSites, kPubSites>(g, AnglePhi<double>(J.j[q].phi), base, g.n, ld, Same{}, pre,
+                                                   NoMid{}, post);
+}
+
+// The actions and the summed force of a kick group in one pass (TermJobs): a workgroup
+// owns kBlock sites of one chain and goes through its terms in order.  The force at site m
+// needs xi = M^dagger eta at one site only, its temporal neighbour n in the direction in
+// which M hops, and no other site needs that value: the thread of n evaluates xi(n), whose
+// temporal neighbour is m again with the phase of m, and writes dS(m).  So xi is never
+// stored, each site's phase is evaluated once for all terms, and dS is written once.
+// Memory per site and term: eta, rhs and sub once (16 B each, the hops from the caches).
+// FORCE = false: the actions only.  Ratio terms take xi - sub (eq. (f_chi_i)).
+template <bool FORCE>
+__global__ __launch_bounds__(kBlock) void k_terms(Geom g, TermJobs J, int ntiles, double* __restrict__ part,
+                                                  double* __restrict__ result) {
+  const int l = xcd_remap(blockIdx.x, gridDim.x);
+  const int ch = l / ntiles, tile = l - ch * ntiles;
+  const int n0 = tile * kBlock + threadIdx.x;
+  const bool ok = n0 < g.n;
+  SiteIdx st;
+  st.n = ok ? n0 : g.n - 1;
+  double c = 0.0, s = 0.0, sum = 0.0;
+  double* __restrict__ dS = J.chain[ch].dS;
+  if (FORCE) {
+    st = site_index<true>(g, st.n);
+    cis64(J.chain[ch].phi[st.pn], c, s);
+    if (J.accumulate) sum = dS[st.tn];
+  }
+  const double sgn = st.wrap ? -1.0 : 1.0;
+  const double ec = sgn * c, es = sgn * (st.isA ? s : -s);
+  for (int k = 0; k < J.nterm; ++k) {
+    const TermJob& T = J.term[ch * J.nterm + k];
+    const double2* __restrict__ eta = T.eta;
+    const double2 e0 = eta[st.n], b = T.rhs[st.n];
+    if (FORCE) {
+      const double2 e = eta[st.tn];
+      const double2 x0 = eta[st.h0], x1 = eta[st.h1], x2 = eta[st.h2];
+      double2 v;
+      v.x = v.y = 0.0;
+      if (T.sub) v = T.sub[st.n];
+      g.ms = T.ms;
+      double2 z = stencil_combine<double, true>(g, st, c, s, e0, e, x0, x1, x2);
+      z.x -= v.x;
+      z.y -= v.y;
+      // w = s e^{+-i phi} z ; F = 2 Im(conj(e) w)
+      const double wr = fma(ec, z.x, -(es * z.y)), wi = fma(ec, z.y, es * z.x);
+      const double F = 2.0 * fma(e.x, wi, -(e.y * wr));
+      sum = (k > 0 || J.accumulate) ? sum + J.scale[k] * F : J.scale[k] * F;
+    }
+    const double d = ok ? b.x * e0.x + b.y * e0.y : 0.0;
+    const double tot = block_sum(d);
+    const int q = ch * J.nterm + k;
+    if (threadIdx.x == 0) {
+      if (ntiles == 1)
+        result[q] = tot;
+      else
+        part[(size_t)q * ntiles + tile] = tot;
+    }
+  }
+  if (FORCE && ok) dS[st.tn] = sum;
 }
 
 // Sum over the vectors of a batch: out (+)= sum_b scale_b F_b with F_b the force of
@@ -897,10 +964,8 @@ __global__ __launch_bounds__(kBlock) void k_dot_finish(const double* __restrict_
 
 // (cos phi, sin phi) per site in FP64 and, when p32 is given, phi - 2 pi k (k the
 // integer nearest phi / 2 pi, in FP64) rounded to float.
-__global__ __launch_bounds__(kBlock) void k_phase(const double* __restrict__ phi, double2* __restrict__ p64,
-                                                  float* __restrict__ p32, int n) {
-  const int i = blockIdx.x * kBlock + threadIdx.x;
-  if (i >= n) return;
+__device__ __forceinline__ void phase_site(const double* __restrict__ phi, double2* __restrict__ p64,
+                                           float* __restrict__ p32, int i) {
   const double a = phi[i];
   double c, s;
   sincos(a, &s, &c);
@@ -910,6 +975,19 @@ __global__ __launch_bounds__(kBlock) void k_phase(const double* __restrict__ phi
   p64[i] = v;
   const float a32 = (float)fma(-rint(a * 0.15915494309189535), 6.283185307179586, a);
   if (p32) p32[i] = a32;
+}
+
+__global__ __launch_bounds__(kBlock) void k_phase(const double* __restrict__ phi, double2* __restrict__ p64,
+                                                  float* __restrict__ p32, int n) {
+  const int i = blockIdx.x * kBlock + threadIdx.x;
+  if (i < n) phase_site(phi, p64, p32, i);
+}
+
+// The same for the fields of a batch, one field per grid row.
+__global__ __launch_bounds__(kBlock) void k_phase_jobs(PhaseJobs J, int n) {
+  const int i = blockIdx.x * kBlock + threadIdx.x;
+  const PhaseJob& j = J.j[blockIdx.y];
+  if (i < n) phase_site(j.phi, j.p64, j.p32, i);
 }
 
 // Molecular dynamics (Sec. 5.2): phi += eps pi (T_pi), and the momentum kick
@@ -1895,16 +1973,45 @@ hipError_t launch_apply(const Geom& g, const double* phi, const double2* x, doub
 
 
 hipError_t launch_force(const Geom& g, const double* phi, const double2* eta, const double2* xi, double scale,
-                        int accumulate, double* out, int batch, hipStream_t st, const double2* sub) {
+                        int accumulate, double* out, int batch, hipStream_t st) {
   const int nt = tiles_of(g.n);
   // 2048-site tiles: a quarter of the public kernels' workgroups per vector
   const int per = pub_group(4 * nt, batch);
   const dim3 grid(nt * ((batch + per - 1) / per)), block(kBlock);
   if (per == 1)
-    hipLaunchKernelGGL(k_force, grid, block, 0, st, g, phi, eta, xi, sub, scale, accumulate, out, nt);
+    hipLaunchKernelGGL(k_force, grid, block, 0, st, g, phi, eta, xi, scale, accumulate, out, nt);
   else
-    hipLaunchKernelGGL(k_force_grp, grid, block, 0, st, g, phi, eta, xi, sub, scale, accumulate, out, nt, per,
+    hipLaunchKernelGGL(k_force_grp, grid, block, 0, st, g, phi, eta, xi, scale, accumulate, out, nt, per,
                        batch);
+  return hipGetLastError();
+}
+
+hipError_t launch_apply_jobs(const Geom& g, const ApplyJobs& J, int njob, bool dag, hipStream_t st) {
+  if (njob < 1 || njob > kMaxSys) return hipErrorInvalidValue;
+  const int nt = (g.n + kPubTile - 1) / kPubTile;
+  if (dag)
+    hipLaunchKernelGGL(k_apply_jobs<true>, dim3(nt * njob), dim3(kBlock), 0, st, g, J, nt);
+  else
+    hipLaunchKernelGGL(k_apply_jobs<false>, dim3(nt * njob), dim3(kBlock), 0, st, g, J, nt);
+  return hipGetLastError();
+}
+
+hipError_t launch_terms(const Geom& g, const TermJobs& J, int nchain, bool force, double* part, double* result,
+                        hipStream_t st) {
+  if (nchain < 1 || J.nterm < 1 || J.nterm > kMaxTerms || nchain * J.nterm > kMaxSys) return hipErrorInvalidValue;
+  const int nt = (g.n + kBlock - 1) / kBlock;
+  if (force)
+    hipLaunchKernelGGL(k_terms<true>, dim3(nt * nchain), dim3(kBlock), 0, st, g, J, nt, part, result);
+  else
+    hipLaunchKernelGGL(k_terms<false>, dim3(nt * nchain), dim3(kBlock), 0, st, g, J, nt, part, result);
+  if (nt > 1)
+    hipLaunchKernelGGL(k_dot_finish, dim3(nchain * J.nterm), dim3(kBlock), 0, st, part, nt, result);
+  return hipGetLastError();
+}
+
+hipError_t launch_phase_jobs(const PhaseJobs& J, int njob, int n, hipStream_t st) {
+  if (njob < 1 || njob > kMaxSys) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_phase_jobs, dim3((n + kBlock - 1) / kBlock, njob), dim3(kBlock), 0, st, J, n);
   return hipGetLastError();
 }
 
