@@ -118,5 +118,46 @@ __device__ __forceinline__ void store_active(Scal* sc, int v) {
   __hip_atomic_store(&sc->active, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Sums within a wave by data-parallel primitives (row shifts, then row broadcasts): a few
+// cycles per step where a shuffle through LDS takes some sixty.  dpp_row leaves the sum of
+// lanes 0..15 in lane 15 (of each row of 16), dpp_wave the sum of all in lane 63.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_add(float v) {
+  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROWS, 0xf, false));
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double v) {
+  const long long b = __double_as_longlong(v);
+  const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, ROWS, 0xf, false);
+  const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, ROWS, 0xf, false);
+  return v + __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+template <typename T>
+__device__ __forceinline__ T dpp_row(T v) {
+  v = dpp_add<0x111, 0xf>(v);
+  v = dpp_add<0x112, 0xf>(v);
+  v = dpp_add<0x114, 0xf>(v);
+  return dpp_add<0x118, 0xf>(v);
+}
+template <typename T>
+__device__ __forceinline__ T dpp_wave(T v) {
+  v = dpp_row(v);
+  v = dpp_add<0x142, 0xa>(v);
+  return dpp_add<0x143, 0xc>(v);
+}
+
+// Words exchanged between workgroups inside a kernel: written through to and read past the
+// L2 caches of the XCDs.  drain() waits until this wave's stores have arrived there (or, for
+// system-scope stores, in host memory); a counter increment after it publishes them.
+__device__ __forceinline__ void put_agent(double* p, double v) {
+  __hip_atomic_store((unsigned long long*)p, (unsigned long long)__double_as_longlong(v), __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double get_agent(const double* p) {
+  return __longlong_as_double((long long)__hip_atomic_load((const unsigned long long*)p, __ATOMIC_RELAXED,
+                                                           __HIP_MEMORY_SCOPE_AGENT));
+}
+__device__ __forceinline__ void drain() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 }  // namespace
 }  // namespace hub

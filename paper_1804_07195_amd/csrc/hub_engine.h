@@ -85,6 +85,8 @@ struct System {
   int phase = 0;
   int post = 0;         // what follows the running single-precision CG
   int j = 0;            // Arnoldi step
+  int wslot = 0;        // the slot of S_R, S_U that holds the residual or the Arnoldi vector w
+  bool plain = false;   // the Arnoldi step runs without an inner solve
   int cycles = 0;
   int cg_total = 0;     // FP64 CG iterations over all restarts
   int enq = 0;          // CG iterations enqueued since the last CG setup
@@ -170,6 +172,10 @@ class Engine {
   hipError_t take_event(std::vector<hipEvent_t>& dst);
   GangCut cut_of(const Geom& g, bool single);
   hipError_t read_scal(const std::vector<System*>& v);
+  // The publication of the Scal records of v at the end of a following launch, and the wait
+  // for it (h_scal_ holds the records then).
+  Publish publication(const std::vector<System*>& v);
+  hipError_t wait_publication(const Publish& pub);
   // Descriptors and FGMRES update coefficients go to pinned staging rows (slot-indexed)
   // and reach the device in one copy per kind: flush_desc at the start of every step,
   // flush_y before the update kernel.  A row is rewritten only after the kernels that
@@ -191,9 +197,9 @@ class Engine {
   double* d_y_ = nullptr;       // update coefficients, kYStride doubles per slot
   double* h_y_ = nullptr;       // pinned staging of d_y_
   int desc_lo_ = kMaxSys, desc_hi_ = -1, y_lo_ = kMaxSys, y_hi_ = -1;  // rows to copy
-  Scal* d_scal_ = nullptr;
+  Scal* d_scal_ = nullptr;      // kMaxSys records, then kScalCounters counters
   Scal* h_scal_ = nullptr;      // pinned mirror
-  Scal* h_pub_ = nullptr;       // host-coherent copy written by k_publish, followed by its flag
+  Scal* h_pub_ = nullptr;       // host-coherent copy of published records, followed by its flag
   unsigned* h_pub_flag_ = nullptr;
   unsigned pub_seq_ = 0;
   std::vector<System*> slots_;

@@ -216,16 +216,18 @@ enum Phase : int {
     if (e_ != hipSuccess) return e_;         \
   } while (0)
 
+constexpr size_t kScalBytes = sizeof(Scal) * kMaxSys + sizeof(unsigned) * kScalCounters;
+
 Engine::Engine(Pool* pool, hipStream_t st) : pool_(pool), st_(st), slots_(kMaxSys, nullptr) {
   ok_ = hipMalloc(&d_desc_, sizeof(SysDesc) * kMaxSys) == hipSuccess &&
         hipHostMalloc(&h_desc_, sizeof(SysDesc) * kMaxSys, hipHostMallocDefault) == hipSuccess &&
         hipMalloc(&d_y_, sizeof(double) * kYStride * kMaxSys) == hipSuccess &&
         hipHostMalloc(&h_y_, sizeof(double) * kYStride * kMaxSys, hipHostMallocDefault) == hipSuccess &&
-        hipMalloc(&d_scal_, sizeof(Scal) * kMaxSys) == hipSuccess &&
+        hipMalloc(&d_scal_, kScalBytes) == hipSuccess &&
         hipHostMalloc(&h_scal_, sizeof(Scal) * kMaxSys, hipHostMallocDefault) == hipSuccess &&
         hipHostMalloc(&h_flags_, sizeof(Scal) * kMaxSys * 4 + 256, hipHostMallocCoherent) == hipSuccess &&
         hipHostMalloc(&h_pub_, sizeof(Scal) * kMaxSys + 256, hipHostMallocCoherent) == hipSuccess &&
-        hipMemsetAsync(d_scal_, 0, sizeof(Scal) * kMaxSys, st_) == hipSuccess;
+        hipMemsetAsync(d_scal_, 0, kScalBytes, st_) == hipSuccess;
   if (ok_) {
     std::memset(h_scal_, 0, sizeof(Scal) * kMaxSys);
     std::memset(h_pub_, 0, sizeof(Scal) * kMaxSys + 256);
@@ -504,33 +506,47 @@ LaunchList Engine::list(const std::vector<System*>& v) const {
   return L;
 }
 
-hipError_t Engine::read_scal(const std::vector<System*>& v) {
+Publish Engine::publication(const std::vector<System*>& v) {
   int lo = kMaxSys, hi = -1;
   for (System* s : v) {
     lo = std::min(lo, s->slot);
     hi = std::max(hi, s->slot);
   }
-  if (hi < lo) return hipSuccess;
-  // A kernel writes the records and then a sequence number to host-coherent memory and
-  // the host polls the number: about half the latency of a copy plus a stream
-  // synchronisation.  hipStreamQuery bounds the wait; should the stream drain without
-  // the number showing, the records are read through a copy instead.
-  const int cnt = hi - lo + 1;
-  const unsigned seq = ++pub_seq_;
-  HUB_TRY(launch_publish(d_scal_ + lo, h_pub_ + lo, cnt, h_pub_flag_, seq, st_));
+  Publish pub;
+  pub.d = d_scal_ + lo;
+  pub.h = h_pub_ + lo;
+  pub.cnt = hi - lo + 1;
+  pub.seq = ++pub_seq_;
+  pub.flag = h_pub_flag_;
+  return pub;
+}
+
+// A kernel writes the records and then a sequence number to host-coherent memory and
+// the host polls the number: about half the latency of a copy plus a stream
+// synchronisation.  hipStreamQuery bounds the wait; should the stream drain without
+// the number showing, the records are read through a copy instead.
+hipError_t Engine::wait_publication(const Publish& pub) {
+  const size_t lo = pub.d - d_scal_;
   for (unsigned spin = 1;; ++spin) {
-    if (__atomic_load_n(h_pub_flag_, __ATOMIC_ACQUIRE) == seq) break;
+    if (__atomic_load_n(h_pub_flag_, __ATOMIC_ACQUIRE) == pub.seq) break;
     if ((spin & 255) == 0) {
       const hipError_t q = hipStreamQuery(st_);
       if (q == hipErrorNotReady) continue;
       if (q != hipSuccess) return q;
-      if (__atomic_load_n(h_pub_flag_, __ATOMIC_ACQUIRE) == seq) break;
-      HUB_TRY(hipMemcpyAsync(h_scal_ + lo, d_scal_ + lo, sizeof(Scal) * cnt, hipMemcpyDeviceToHost, st_));
+      if (__atomic_load_n(h_pub_flag_, __ATOMIC_ACQUIRE) == pub.seq) break;
+      HUB_TRY(hipMemcpyAsync(h_scal_ + lo, pub.d, sizeof(Scal) * pub.cnt, hipMemcpyDeviceToHost, st_));
       return hipStreamSynchronize(st_);
     }
   }
-  std::memcpy(h_scal_ + lo, h_pub_ + lo, sizeof(Scal) * cnt);
+  std::memcpy(h_scal_ + lo, pub.h, sizeof(Scal) * pub.cnt);
   return hipSuccess;
+}
+
+hipError_t Engine::read_scal(const std::vector<System*>& v) {
+  if (v.empty()) return hipSuccess;
+  const Publish pub = publication(v);
+  HUB_TRY(launch_publish(pub, st_));
+  return wait_publication(pub);
 }
 
 void Engine::finish(System* s, hub_status st) {
@@ -558,19 +574,15 @@ hipError_t Engine::group_phase(int phase, const std::vector<System*>& g) {
             L.pr[q] = g[q]->opts.tol * g[q]->opts.tol;
             L.pi[q] = g[q]->opts.max_iter;
           }
-          HUB_TRY(launch_cg_init_zero(d_desc_, L, RED_CG_SETUP, st_));
+          HUB_TRY(launch_cg_init_zero(d_desc_, L, RED_CG_SETUP, Publish{}, st_));
         } else {
-          HUB_TRY(launch_multidot(d_desc_, L, S_B, S_B, 1, 0, st_));
-          HUB_TRY(read_scal(g));
           for (size_t q = 0; q < g.size(); ++q) {
-            System* s = g[q];
-            s->bb = h_scal_[s->slot].red[0];
-            L.pa[q] = s->opts.tol * s->opts.tol * s->bb;
+            L.pa[q] = g[q]->opts.tol * g[q]->opts.tol;
             L.pr[q] = 0.0;
-            L.pi[q] = s->opts.max_iter;
-            s->info.applies++;
+            L.pi[q] = g[q]->opts.max_iter;
+            g[q]->info.applies++;
           }
-          HUB_TRY(launch_normal_slot(d_desc_, L, S_X, false, S_B, S_R, RED_CG_SETUP, 1, st_));
+          HUB_TRY(launch_normal_slot(d_desc_, L, S_X, S_B, S_R, RED_CG_SETUP, 1, true, Publish{}, st_));
         }
         for (System* s : g) {
           s->enq = 0;
@@ -580,18 +592,17 @@ hipError_t Engine::group_phase(int phase, const std::vector<System*>& g) {
         return hipSuccess;
       }
       // FGMRES: r = b (or b - A x0), |b|
-      if (!og.use_x0) {
-        HUB_TRY(launch_cg_init_zero(d_desc_, L, RED_STORE, st_));
-      } else {
-        HUB_TRY(launch_multidot(d_desc_, L, S_B, S_B, 1, 0, st_));
-        HUB_TRY(launch_normal_slot(d_desc_, L, S_X, false, S_B, S_R, RED_STORE, 2, st_));
-      }
-      HUB_TRY(read_scal(g));
+      const Publish pub = publication(g);
+      if (!og.use_x0)
+        HUB_TRY(launch_cg_init_zero(d_desc_, L, RED_STORE, pub, st_));
+      else
+        HUB_TRY(launch_normal_slot(d_desc_, L, S_X, S_B, S_R, RED_STORE, 1, true, pub, st_));
+      HUB_TRY(wait_publication(pub));
       std::vector<System*> run, zero;
       for (System* s : g) {
         const Scal& sc = h_scal_[s->slot];
         s->bb = sc.red[0];
-        s->err = og.use_x0 ? std::sqrt(sc.red[2]) : std::sqrt(s->bb);
+        s->err = og.use_x0 ? std::sqrt(sc.red[1]) : std::sqrt(s->bb);
         if (og.use_x0) s->info.applies++;
         s->bnorm = std::sqrt(s->bb);
         if (!std::isfinite(s->bb) || !std::isfinite(s->err)) {
@@ -608,7 +619,7 @@ hipError_t Engine::group_phase(int phase, const std::vector<System*>& g) {
       }
       if (!zero.empty()) {
         // b = 0: x = 0 exactly
-        HUB_TRY(launch_cg_init_zero(d_desc_, list(zero), RED_STORE, st_));
+        HUB_TRY(launch_cg_init_zero(d_desc_, list(zero), RED_STORE, Publish{}, st_));
         for (System* s : zero) {
           s->info.true_rel_resid = 0.0;
           finish(s, HUB_OK);
@@ -625,8 +636,9 @@ hipError_t Engine::group_phase(int phase, const std::vector<System*>& g) {
         R.pr[q] = tau * tau;
         R.pi[q] = o.inner_max_iter;
         R.pj[q] = S_Z0;
+        R.it[q] = S_R;
       }
-      HUB_TRY(launch_prep_inner(d_desc_, R, S_R, -1, st_));
+      HUB_TRY(launch_prep_inner(d_desc_, R, -1, st_));
       for (System* s : run) {
         s->enq = 0;
         s->gen++;
@@ -655,8 +667,9 @@ hipError_t Engine::group_phase(int phase, const std::vector<System*>& g) {
       HUB_TRY(flush_y());
       const LaunchList L = list(g);
       HUB_TRY(launch_xupdate(d_desc_, L, d_y_, 1, !g.front()->opts.use_x0, st_));
-      HUB_TRY(launch_normal_slot(d_desc_, L, S_X, false, S_B, S_R, RED_STORE, 0, st_));
-      HUB_TRY(read_scal(g));
+      const Publish pub = publication(g);
+      HUB_TRY(launch_normal_slot(d_desc_, L, S_X, S_B, S_R, RED_STORE, 0, false, pub, st_));
+      HUB_TRY(wait_publication(pub));
       for (System* s : g) {
         const hub_solve_opts& o = s->opts;
         s->info.applies++;
@@ -667,6 +680,7 @@ hipError_t Engine::group_phase(int phase, const std::vector<System*>& g) {
           continue;
         }
         s->j = 0;
+        s->wslot = S_R;
         s->wnorm = s->err;
         s->rnorm_cycle = s->err;
         s->H.assign((size_t)(o.restart_m + 1) * o.restart_m, std::complex<double>(0.0));
@@ -684,55 +698,58 @@ hipError_t Engine::group_phase(int phase, const std::vector<System*>& g) {
           act.push_back(s);
       }
       if (act.empty()) return hipSuccess;
-      LaunchList L = list(act);
-      for (size_t q = 0; q < act.size(); ++q) {
-        const System* s = act[q];
+      // without an inner solve the step itself makes v_j and z_j (k_arnoldi_dots)
+      std::vector<System*> inner;
+      std::vector<double> tau;
+      for (System* s : act) {
         const hub_solve_opts& o = s->opts;
         const double ratio = o.tol * o.inner_a * s->bnorm / s->err;
+        s->plain = !(ratio < 1.0) || o.inner_max_iter < 1;
+        if (s->plain) {
+          s->phase = PH_F_POST_ARNOLDI;
+          continue;
+        }
+        inner.push_back(s);
+        tau.push_back(std::max(ratio, o.inner_floor));
+      }
+      if (inner.empty()) return hipSuccess;
+      LaunchList L = list(inner);
+      for (size_t q = 0; q < inner.size(); ++q) {
+        System* s = inner[q];
         L.pa[q] = 1.0 / s->wnorm;
         L.pj[q] = S_Z0 + j;
-        if (ratio < 1.0) {
-          const double tau = std::max(ratio, o.inner_floor);
-          L.pr[q] = tau * tau;
-          L.pi[q] = o.inner_max_iter;
-        } else {
-          L.pr[q] = 0.0;
-          L.pi[q] = 0;
-        }
+        L.it[q] = s->wslot;
+        L.pr[q] = tau[q] * tau[q];
+        L.pi[q] = s->opts.inner_max_iter;
+        s->enq = 0;
+        s->gen++;
+        s->phase = PH_F_INNER;
+        s->post = PH_F_POST_ARNOLDI;
       }
-      HUB_TRY(launch_prep_inner(d_desc_, L, S_R, S_V0 + j, st_));
-      for (size_t q = 0; q < act.size(); ++q) {
-        System* s = act[q];
-        if (L.pi[q] > 0) {
-          s->enq = 0;
-          s->gen++;
-          s->phase = PH_F_INNER;
-          s->post = PH_F_POST_ARNOLDI;
-        } else {
-          s->phase = PH_F_POST_ARNOLDI;
-        }
-      }
-      return hipSuccess;
+      return launch_prep_inner(d_desc_, L, S_V0 + j, st_);
     }
     case PH_F_POST_ARNOLDI: {
-      // w = A z_j, classical Gram-Schmidt against v_0 .. v_j, h_{j+1,j} = |w|, ERR *= |w|:
-      // the smallest systems in one fused launch, the others on the tiled kernels
-      std::vector<System*> gw, gt;
-      for (System* s : g) (arn_wg_of(s->g.n) ? gw : gt).push_back(s);
-      if (!gt.empty()) {
-        const LaunchList L = list(gt);
-        HUB_TRY(launch_normal_slot(d_desc_, L, S_Z0 + j, true, -1, S_R, RED_NONE, 0, st_));
-        HUB_TRY(launch_multidot(d_desc_, L, S_R, S_V0, j + 1, 0, st_));
-        HUB_TRY(launch_cgs(d_desc_, L, S_R, S_V0, j + 1, 0, 2 * (j + 1), st_));
+      // w = A z_j, classical Gram-Schmidt against v_0 .. v_j, h_{j+1,j} = |w|, ERR *= |w|.
+      // w stays in its slot after an inner solve (v_j holds the old one) and changes slots
+      // in a step that reads the old w at the neighbours.
+      for (bool plain : {false, true}) {
+        std::vector<System*> v;
+        for (System* s : g)
+          if (s->plain == plain) v.push_back(s);
+        if (v.empty()) continue;
+        LaunchList L = list(v);
+        for (size_t q = 0; q < v.size(); ++q) {
+          if (plain) v[q]->wslot = S_R + S_U - v[q]->wslot;
+          L.it[q] = v[q]->wslot;
+          L.pa[q] = 1.0 / v[q]->wnorm;
+        }
+        HUB_TRY(launch_arnoldi_dots(d_desc_, L, j, plain, st_));
       }
-      if (!gw.empty()) {
-        WgList W;
-        std::memset(&W, 0, sizeof(W));
-        W.nsys = (int)gw.size();
-        for (size_t q = 0; q < gw.size(); ++q) W.sys[q] = gw[q]->slot;
-        HUB_TRY(launch_arnoldi_wg(d_desc_, W, j, st_));
-      }
-      HUB_TRY(read_scal(g));
+      LaunchList L = list(g);
+      for (size_t q = 0; q < g.size(); ++q) L.it[q] = g[q]->wslot;
+      const Publish pub = publication(g);
+      HUB_TRY(launch_cgs(d_desc_, L, j, pub, st_));
+      HUB_TRY(wait_publication(pub));
       for (System* s : g) {
         const int m = s->opts.restart_m;
         s->info.applies++;
@@ -762,8 +779,9 @@ hipError_t Engine::group_phase(int phase, const std::vector<System*>& g) {
         HUB_TRY(flush_y());
         HUB_TRY(launch_xupdate(d_desc_, L, d_y_, k, false, st_));
       }
-      HUB_TRY(launch_normal_slot(d_desc_, L, S_X, false, S_B, S_R, RED_STORE, 0, st_));
-      HUB_TRY(read_scal(g));
+      const Publish pub = publication(g);
+      HUB_TRY(launch_normal_slot(d_desc_, L, S_X, S_B, S_R, RED_STORE, 0, false, pub, st_));
+      HUB_TRY(wait_publication(pub));
       for (System* s : g) {
         const hub_solve_opts& o = s->opts;
         s->info.applies++;
@@ -777,6 +795,7 @@ hipError_t Engine::group_phase(int phase, const std::vector<System*>& g) {
           finish(s, HUB_ERR_NOCONV);
         } else {
           s->j = 0;
+          s->wslot = S_R;
           s->wnorm = s->err;
           s->rnorm_cycle = s->err;
           std::fill(s->H.begin(), s->H.end(), std::complex<double>(0.0));
@@ -800,8 +819,9 @@ hipError_t Engine::confirm(const std::vector<System*>& g) {
     L.pr[q] = 0.0;
     L.pi[q] = std::max(1, s->opts.max_iter - s->cg_total);
   }
-  HUB_TRY(launch_normal_slot(d_desc_, L, S_X, false, S_B, S_R, RED_CG_SETUP, 1, st_));
-  HUB_TRY(read_scal(g));
+  const Publish pub = publication(g);
+  HUB_TRY(launch_normal_slot(d_desc_, L, S_X, S_B, S_R, RED_CG_SETUP, 1, false, pub, st_));
+  HUB_TRY(wait_publication(pub));
   for (System* s : g) {
     const hub_solve_opts& o = s->opts;
     s->info.applies++;
@@ -1016,7 +1036,13 @@ hipError_t Engine::launch_block(bool single, bool& launched) {
   // event, it adds no barrier packet, so the next block's kernels follow at once.
   Scal* dst = h_flags_ + (size_t)((single ? 2 : 0) + b.buf) * kMaxSys;
   b.seq = ++blk_seq_;
-  HUB_TRY(launch_publish(d_scal_ + lo, dst + lo, hi - lo + 1, h_blk_flag_, b.seq, st_));
+  Publish pub;
+  pub.d = d_scal_ + lo;
+  pub.h = dst + lo;
+  pub.cnt = hi - lo + 1;
+  pub.seq = b.seq;
+  pub.flag = h_blk_flag_;
+  HUB_TRY(launch_publish(pub, st_));
   inflight_[single ? 1 : 0].push_back(std::move(b));
   launched = true;
   return hipSuccess;

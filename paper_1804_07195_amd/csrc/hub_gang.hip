@@ -132,34 +132,6 @@ template <> struct Tagged<double2> {
   }
 };
 
-// Sums within a wave by data-parallel primitives (row shifts, then row broadcasts): a few
-// cycles per step where a shuffle through LDS takes some sixty.  dpp_row leaves the sum of
-// lanes 0..15 in lane 15 (of each row of 16), dpp_wave the sum of all in lane 63.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ float dpp_add(float v) {
-  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROWS, 0xf, false));
-}
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_add(double v) {
-  const long long b = __double_as_longlong(v);
-  const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, ROWS, 0xf, false);
-  const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, ROWS, 0xf, false);
-  return v + __longlong_as_double((long long)(((u64)hi << 32) | lo));
-}
-template <typename T>
-__device__ __forceinline__ T dpp_row(T v) {
-  v = dpp_add<0x111, 0xf>(v);
-  v = dpp_add<0x112, 0xf>(v);
-  v = dpp_add<0x114, 0xf>(v);
-  return dpp_add<0x118, 0xf>(v);
-}
-template <typename T>
-__device__ __forceinline__ T dpp_wave(T v) {
-  v = dpp_row(v);
-  v = dpp_add<0x142, 0xa>(v);
-  return dpp_add<0x143, 0xc>(v);
-}
-
 // Workgroups of the gangs of this process that are on the device or on their way to it.  A
 // gang that would not fit beside the others is refused before it holds CUs that they wait
 // for, so that two streams cannot each hold half of what both need.

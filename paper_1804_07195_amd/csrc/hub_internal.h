@@ -163,21 +163,6 @@ struct CgList {
 };
 constexpr int kSmallCg = 4;
 
-// Systems whose FGMRES Arnoldi step runs as one fused single-workgroup launch instead of
-// the tiled kernels: one CU streams the basis twice, which beats the tiled path's launches
-// up to about this size (6x6x32: 7% faster per solve, 6x6x64 and 8x8x36: 2-4%, 12x12x32:
-// 5% slower).
-constexpr int kWgBlock = 1024;
-constexpr int kWgPerThread = 5;
-constexpr int kArnWgMaxSites = 4608;
-static_assert(kArnWgMaxSites <= kWgBlock * kWgPerThread, "sites per thread");
-inline bool arn_wg_of(int n) { return n <= kArnWgMaxSites; }
-// Systems of one fused Arnoldi launch: workgroup k runs system sys[k].
-struct WgList {
-  int nsys;
-  int sys[kMaxSys];
-};
-
 // Systems of one gang launch: system sys[k], iterating into solution slot pi[k]; tag[k]:
 // exchange tags used so far, seq[k]: the number of this launch of the system (from 1).
 // Block b of the launch is workgroup wg[b] of system list[b] (kGangNone: of none).
@@ -259,7 +244,6 @@ static_assert(S_Z0 + kMaxRestart <= kMaxSlots, "slot layout");
 
 // What a reduction finalisation does with its sums.
 enum RedMode : int {
-  RED_NONE = 0,
   RED_STORE = 1,     // sc->red[off..] = results
   RED_CG_SETUP = 2   // also CG (re)start: rrv[0] = result[0], stop2 = pa + pr*rr, iters 0, active
 };
@@ -346,7 +330,14 @@ hipError_t launch_md_kick(double* pi, const double* phi, const double* G, double
 // *flag (host-coherent) with a system-scope release, so that the host can poll the
 // flag instead of synchronising the stream.  One workgroup.
 static_assert(sizeof(Scal) % 8 == 0, "Scal is copied in 8-byte words");
-hipError_t launch_publish(const Scal* d, Scal* h, int cnt, unsigned* flag, unsigned seq, hipStream_t st);
+struct Publish {
+  const Scal* d = nullptr;
+  Scal* h = nullptr;
+  int cnt = 0;
+  unsigned seq = 0;
+  unsigned* flag = nullptr;  // NULL: nothing to publish
+};
+hipError_t launch_publish(const Publish& pub, hipStream_t st);
 hipError_t launch_cg_iter(const SysDesc* sys, const LaunchList& L, bool single, hipStream_t st);
 // One stage (1 or 2) of the CG iteration.  With events, the launch records the
 // kernel's own start and end timestamps into them (hipExtLaunchKernel).
@@ -361,9 +352,6 @@ hipError_t launch_gang(const SysDesc* sys, const GangList& L, int K, bool single
 hipError_t launch_gang_leave(const SysDesc* sys, const GangList& L, int ntiles, bool single, hipStream_t st);
 // Exchange memory starts from zero (no tag is 0).
 hipError_t launch_gang_clear(unsigned long long* mem, size_t words, hipStream_t st);
-// Arnoldi step j (w = A z_j, Gram-Schmidt against v_0 .. v_j, |w|^2 into the Scal records)
-// of every system of L, one workgroup per system (small systems, see kArnWgMaxSites).
-hipError_t launch_arnoldi_wg(const SysDesc* sys, const WgList& L, int j, hipStream_t st);
 // Multi-shift CG: start (r = b, x = 0, x_s = 0, p_s = b, partial |b|^2), setup (one
 // workgroup: scalars), and the two stages of iteration `it` (shifted updates of step
 // it-1 ride in stage 1, where beta_{it-1} is known).
@@ -377,25 +365,34 @@ constexpr double kCgBytes[2][3] = {{80.0, 80.0, 128.0}, {36.0, 36.0, 60.0}};  //
 inline double cg_bytes(bool single, int stage, int it) {
   return kCgBytes[single ? 1 : 0][stage == 1 ? 0 : 1 + (it & 1)];
 }
-// Every reduction below leaves per-tile partials; a finalisation kernel (one
-// workgroup per system and value) sums them in a fixed order into sc->red[red_off..] and,
-// with RED_CG_SETUP, starts a CG on the result (pa, pr, pi of the launch list).
-// out = [b -] (M M^dagger + mu2) in, in one pass of the 12-point form (in: an FP64
-// slot or, with in_c64, a complex64 slot), |out|^2 (mode RED_NONE: no reduction).
-hipError_t launch_normal_slot(const SysDesc* sys, const LaunchList& L, int s_in, bool in_c64, int s_b, int s_out,
-                              RedMode mode, int red_off, hipStream_t st);
+// Every reduction below leaves per-tile partials; the workgroup that finishes a system's
+// last tile sums them in a fixed order into sc->red[red_off..] and, with RED_CG_SETUP,
+// starts a CG on the result (pa, pr, pi of the launch list).  The workgroup that finishes
+// the launch's last system publishes `pub`, if given.  The counters that find the last
+// ones lie behind the engine's Scal array, kScalCounters unsigned, zero between launches.
+constexpr int kCounterFan = 32;     // groups that a system's workgroups count in, if there are more
+constexpr int kCounterStride = 16;  // unsigned: a cache line each
+constexpr int kCountersPerSys = (1 + kCounterFan) * kCounterStride;
+constexpr int kScalCounters = kMaxSys * kCountersPerSys + kCounterStride;
+static_assert(sizeof(Scal) * kMaxSys % (kCounterStride * sizeof(unsigned)) == 0, "counters on lines of their own");
+// out = [b -] (M M^dagger + mu2) in, in one pass of the 12-point form, of FP64 slots;
+// red[red_off] = |out|^2.  with_bb: the CG starts from a given x, red[0] = |b|^2 too
+// (red_off >= 1) and pa multiplies |b|^2.
+hipError_t launch_normal_slot(const SysDesc* sys, const LaunchList& L, int s_in, int s_b, int s_out, RedMode mode,
+                              int red_off, bool with_bb, const Publish& pub, hipStream_t st);
 // x = 0, r = b, |b|^2 -> red[0]; with RED_CG_SETUP also the FP64 CG start.
-hipError_t launch_cg_init_zero(const SysDesc* sys, const LaunchList& L, RedMode mode, hipStream_t st);
-// red[off + 2i, 2i+1] = <v_i, w>, i < cnt.
-hipError_t launch_multidot(const SysDesc* sys, const LaunchList& L, int s_w, int s_v0, int cnt, int red_off,
-                           hipStream_t st);
-// w -= sum_i h_i v_i with h = red[h_off..]; |w|^2 -> red[red_off].
-hipError_t launch_cgs(const SysDesc* sys, const LaunchList& L, int s_w, int s_v0, int cnt, int h_off,
-                      int red_off, hipStream_t st);
-// v = pa*src (FP64, stored if s_v >= 0) and the single-precision CG start on it:
-// pi = maxit > 0: r32 = c64(v), z = 0, |r32|^2 -> setup with stop2 = pr*rr;
-// pi = 0 (no preconditioning): z = c64(v).  z is the slot pj.
-hipError_t launch_prep_inner(const SysDesc* sys, const LaunchList& L, int s_src, int s_v, hipStream_t st);
+hipError_t launch_cg_init_zero(const SysDesc* sys, const LaunchList& L, RedMode mode, const Publish& pub,
+                               hipStream_t st);
+// First half of Arnoldi step j: w = A z_j into the slot it[], red[2i], red[2i+1] = <v_i, w>,
+// i <= j.  from_w: the step has no inner solve, and z_j = c64(v_j), v_j = pa * w_old with
+// w_old the other of the slots S_R and S_U; both are stored here too.
+hipError_t launch_arnoldi_dots(const SysDesc* sys, const LaunchList& L, int j, bool from_w, hipStream_t st);
+// Second half: w -= sum_i h_i v_i, i <= j, h_i = red[2i], red[2i+1]; |w|^2 -> red[2j+2].
+hipError_t launch_cgs(const SysDesc* sys, const LaunchList& L, int j, const Publish& pub, hipStream_t st);
+// The start of an inner solve: v = pa * src (FP64, stored if s_v >= 0; src the slot it[]),
+// r32 = c64(v), z = 0 (the slot pj) and the single-precision CG's setup with stop2 = pr*rr,
+// maxit = pi.
+hipError_t launch_prep_inner(const SysDesc* sys, const LaunchList& L, int s_v, hipStream_t st);
 // x = (set ? 0 : x) + sum_{i<cnt} y_i z_i, z the C64 slots from S_Z0 and y of the system in
 // slot k at ys + k * kYStride (re, im interleaved).
 constexpr int kYStride = 2 * kMaxRestart;

@@ -1035,6 +1035,7 @@ __device__ __forceinline__ TileRange tile_range(int tile, int nb, int bsz, int s
   const int t_lo = t_r.lo, t_hi = t_r.hi;                               \
   const int base = t_lo + threadIdx.x;                                  \
   (void)t_hi;                                                           \
+  (void)g;                                                              \
   static_assert((TILE) > 0, "tile size");
 
 // CG stage 1 of iteration it = L.it[kk]:
@@ -1265,21 +1266,6 @@ __global__ __launch_bounds__(kBlock) void k_cg2(const SysDesc* __restrict__ sys,
   if (threadIdx.x == 0) Real<double>(d->part2).set(tile, tot);
 }
 
-// Sum over the workgroup in a fixed order; every thread gets the value.  `buf` holds one
-// double per wave; callers alternate two buffers, so that the one barrier here also
-// guarantees that the previous sum over the same buffer has been read by every thread
-// (another barrier always separates two sums over one buffer).
-template <typename T>
-__device__ __forceinline__ double wg_sum(T v, double* buf) {
-  v = wave_sum(v);
-  if ((threadIdx.x & 63) == 0) buf[threadIdx.x >> 6] = (double)v;
-  __syncthreads();
-  double s = 0.0;
-#pragma unroll
-  for (int k = 0; k < kWgBlock / 64; ++k) s += buf[k];
-  return s;
-}
-
 // ---------------------------------------------------------------------------
 // Multi-shift CG (FP64).  Base CG on A_0 as k_cg1 / k_cg2; every shifted system s
 // follows with x_s += alpha^s_k p^s_k, p^s_{k+1} = zeta^s_{k+1} r_{k+1} + beta^s_k p^s_k,
@@ -1505,11 +1491,103 @@ template <> __device__ __forceinline__ double2 to_c128<float2>(float2 v) {
 
 
 
-__device__ __forceinline__ void store_partials(const SysDesc* d, int tile, const double* vals, int nv) {
+// Scal records to host-coherent memory in 8-byte words, every store arrived there before the
+// flag is written.
+__device__ __forceinline__ void publish(const Publish& pub) {
+  const unsigned long long* src = reinterpret_cast<const unsigned long long*>(pub.d);
+  unsigned long long* dst = reinterpret_cast<unsigned long long*>(pub.h);
+  const int nw = pub.cnt * (int)(sizeof(Scal) / 8);
+  for (int k = threadIdx.x; k < nw; k += kBlock)
+    __hip_atomic_store(dst + k, __hip_atomic_load(src + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  drain();
+  __syncthreads();
+  if (threadIdx.x == 0) __hip_atomic_store(pub.flag, pub.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// True in the workgroup that counts to n; the counter is zero again then.
+__device__ __forceinline__ bool count_last(unsigned* c, unsigned n) {
+  __shared__ int last;
   if (threadIdx.x == 0) {
-    const Real<double> p(d->part + (size_t)tile * kMaxRed);
-    for (int q = 0; q < nv; ++q) p.set(q, vals[q]);
+    last = __hip_atomic_fetch_add(c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n - 1;
+    if (last) __hip_atomic_store(c, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
+  __syncthreads();
+  return last != 0;
+}
+
+// The same over n workgroups, this one being number k of them, on the counters c + 0,
+// kCounterStride, ..: increments of one word take about 25 ns each, one after the other, so
+// more than kCounterFan workgroups count in kCounterFan groups first.
+__device__ __forceinline__ bool count_last_of(unsigned* c, unsigned k, unsigned n) {
+  if (n <= kCounterFan) return count_last(c, n);
+  const unsigned g = k % kCounterFan;
+  if (!count_last(c + (1 + g) * kCounterStride, n / kCounterFan + (g < n % kCounterFan ? 1 : 0))) return false;
+  __syncthreads();
+  return count_last(c, kCounterFan);
+}
+
+// The end of a reducing kernel: thread q < nv holds value q of this tile.  The values go out
+// as the tile's partials; the workgroup of the system's last tile sums them over the tiles
+// in a fixed order (16 loads per thread in flight, the values of a tile side by side) into
+// red[off(q)]; the workgroup of the last system publishes.  A kernel that does this by itself
+// saves the launch of a reduction and of a publication, 4 to 6 us each with its gap, for
+// 1 to 2 us of waiting in one workgroup.
+template <int W, typename Off, typename Done>
+__device__ __forceinline__ void close_tile(const LaunchList& L, int kk, const SysDesc* d, int tile, double val, int nv,
+                                           Off off, Done done, const Publish& pub) {
+  static_assert(W <= 64 && kBlock % W == 0, "values side by side");
+  constexpr int G = kBlock / W, U = 16;
+  double* part = d->part;
+  const int nt = d->ntiles;
+  unsigned* cnt = reinterpret_cast<unsigned*>(L.scal + kMaxSys);
+  Scal* sc = L.scal + L.sys[kk];
+  // the values lie in one wave, which waits for its stores before its first thread counts
+  if ((int)threadIdx.x < nv) put_agent(part + (size_t)tile * kMaxRed + threadIdx.x, val);
+  drain();
+  if (!count_last_of(cnt + L.sys[kk] * kCountersPerSys, (unsigned)tile, (unsigned)nt)) return;
+  __shared__ double lds[kBlock];
+  const int q = threadIdx.x % W, grp = threadIdx.x / W;
+  const double* pq = part + (q < nv ? q : 0);
+  double acc = 0.0;
+  for (int k = grp; k < nt; k += G * U) {
+    double v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = get_agent(pq + (size_t)min(k + u * G, nt - 1) * kMaxRed);
+#pragma unroll
+    for (int u = 0; u < U; ++u) acc += k + u * G < nt ? v[u] : 0.0;
+  }
+  double s;
+  if (W == 1) {
+    s = block_sum(acc);
+  } else {
+    lds[threadIdx.x] = acc;
+    __syncthreads();
+    s = lds[q];
+#pragma unroll
+    for (int i = 1; i < G; ++i) s += lds[i * W + q];
+    __syncthreads();
+    if ((int)threadIdx.x < nv) lds[threadIdx.x] = s;
+    __syncthreads();
+  }
+  if ((int)threadIdx.x < nv) {
+    put_agent(sc->red + off(q), s);
+    done(sc, q, s, nv > 1 ? lds[1] : 0.0);
+  }
+  if (!pub.flag) return;
+  drain();
+  if (count_last(cnt + kMaxSys * kCountersPerSys, (unsigned)L.nsys)) publish(pub);
+}
+
+// Start of a CG on |r|^2 = rr.
+__device__ __forceinline__ void cg_setup(Scal* sc, double rr, double stop2, int maxit) {
+  sc->rrv[0] = rr;
+  sc->stop2 = stop2;
+  sc->maxit = maxit;
+  sc->iters = 0;
+  sc->git = 0;
+  sc->gang = 0;
+  store_active(sc, rr > stop2 ? 1 : 0);
 }
 
 // ---------------------------------------------------------------------------
@@ -1605,45 +1683,50 @@ __device__ __forceinline__ double2 normal12(const Geom& g, const PhasePhi<double
   return q;
 }
 
-// out = [b -] (M M^dagger + mu2) in, FP64 arithmetic (in: FP64 or complex64 slot),
-// partial |out|^2 (mode != RED_NONE).  One pass of the 12-point form.
-template <typename Tin, int SPT>
+// out = [b -] (M M^dagger + mu2) in, FP64; |out|^2 into red[red_off], and |b|^2 into red[0]
+// with BB.  One pass of the 12-point form.
+template <int SPT, bool BB>
 __global__ __launch_bounds__(kBlock) void k_normal_slot(const SysDesc* __restrict__ sys, LaunchList L, int s_in,
-                                                        int s_b, int s_out, int mode) {
+                                                        int s_b, int s_out, int mode, int red_off, Publish pub) {
   constexpr int TILE = kBlock * SPT;
   HUB_PROLOGUE_T(TILE)
   (void)sc;
-  const Vec<Tin> in(d->vec[s_in]);
-  const bool has_b = s_b >= 0;
-  const Vec<double2> bv(has_b ? d->vec[s_b] : nullptr), out(d->vec[s_out]);
+  const Vec<double2> in(d->vec[s_in]);
+  const Vec<double2> bv(d->vec[s_b]), out(d->vec[s_out]);
   const PhasePhi<double> ph = phase_of<double>(d);
   const double mu2 = d->mu2;
-  auto ld = [=](int k) { return to_c128<Tin>(in[k]); };
-  double acc = 0.0;
+  auto ld = [=](int k) { return in[k]; };
+  double acc = 0.0, bb = 0.0;
 #pragma unroll 2
   for (int m = 0; m < SPT; ++m) {
     const int n = base + m * kBlock;
     if (n >= t_hi) break;
     double2 q = normal12(g, ph, n, mu2, ld);
-    if (has_b) {
-      const double2 bb = bv[n];
-      q.x = bb.x - q.x;
-      q.y = bb.y - q.y;
-    }
+    const double2 b = bv[n];
+    q.x = b.x - q.x;
+    q.y = b.y - q.y;
+    if (BB) bb += norm2<double>(b);
     out.set(n, q);
     acc += norm2<double>(q);
   }
-  if (mode == RED_NONE) return;
-  const double tot = block_sum(acc);
-  store_partials(d, tile, &tot, 1);
+  double val = block_sum(acc);
+  if (BB) {
+    const double tb = block_sum(bb);
+    if (threadIdx.x == 1) val = tb;
+  }
+  close_tile<BB ? 2 : 1>(
+      L, kk, d, tile, val, BB ? 2 : 1, [=](int q) { return q == 0 ? red_off : 0; },
+      [&](Scal* s, int q, double rr, double b2) {
+        if (q == 0 && mode == RED_CG_SETUP) cg_setup(s, rr, L.pa[kk] * (BB ? b2 : 1.0) + L.pr[kk] * rr, L.pi[kk]);
+      },
+      pub);
 }
 
-
-
-// x = 0, r = b; partial of |b|^2, made NaN where the phase of phi is not finite (so
-// that a non-finite phi or b shows in the first reduction the host reads).
+// x = 0, r = b; |b|^2, made NaN where the phase of phi is not finite (so that a non-finite
+// phi or b shows in the first reduction the host reads).
 template <int SPT>
-__global__ __launch_bounds__(kBlock) void k_cg_init_zero(const SysDesc* __restrict__ sys, LaunchList L) {
+__global__ __launch_bounds__(kBlock) void k_cg_init_zero(const SysDesc* __restrict__ sys, LaunchList L, int mode,
+                                                         Publish pub) {
   constexpr int TILE = kBlock * SPT;
   HUB_PROLOGUE_T(TILE)
   (void)sc;
@@ -1662,17 +1745,57 @@ __global__ __launch_bounds__(kBlock) void k_cg_init_zero(const SysDesc* __restri
     }
   }
   const double tot = block_sum(acc);
-  store_partials(d, tile, &tot, 1);
+  close_tile<1>(
+      L, kk, d, tile, tot, 1, [](int) { return 0; },
+      [&](Scal* s, int, double rr, double) {
+        if (mode == RED_CG_SETUP) cg_setup(s, rr, L.pa[kk] + L.pr[kk] * rr, L.pi[kk]);
+      },
+      pub);
 }
 
-// partials of <v_i, w> = sum conj(v_i) w, i < cnt (re, im interleaved).
-template <int SPT>
-__global__ __launch_bounds__(kBlock) void k_multidot(const SysDesc* __restrict__ sys, LaunchList L, int s_w,
-                                                     int s_v0, int cnt) {
+// First half of an Arnoldi step: w = A z_j (FP64, the 12-point form) and <v_i, w> = sum
+// conj(v_i) w for i <= j, each thread's w fresh in its caches when the basis passes by.  FROM_W: a step
+// without an inner solve, where z_j = c64(pa w_old) is evaluated at the twelve neighbours
+// too, so that neither v_j nor z_j has to be there before the launch; w_old and w are in
+// different slots.  Each wave sums its two values per i by data-parallel primitives; the
+// waves meet once at the end.  With k_cgs this is a step without an inner solve in two
+// launches, 21.3 us of kernels for three 24x24x64 systems where seven launches (scaling,
+// operator, products, their sum, subtraction, its sum, publication) took 32.
+template <int SPT, bool FROM_W>
+__global__ __launch_bounds__(kBlock) void k_arnoldi_dots(const SysDesc* __restrict__ sys, LaunchList L, int j) {
   constexpr int TILE = kBlock * SPT;
   HUB_PROLOGUE_T(TILE)
   (void)sc;
-  const Vec<double2> w(d->vec[s_w]);
+  const int s_w = L.it[kk];
+  const Vec<double2> w(d->vec[s_w]), old(d->vec[S_R + S_U - s_w]), vj(d->vec[S_V0 + j]);
+  const Vec<float2> z(d->vec[S_Z0 + j]);
+  const PhasePhi<double> ph = phase_of<double>(d);
+  const double mu2 = d->mu2, scale = L.pa[kk];
+  auto scaled = [=](int k) {
+    double2 a = old[k];
+    a.x *= scale;
+    a.y *= scale;
+    return a;
+  };
+  auto single = [](double2 a) {
+    float2 f;
+    f.x = (float)a.x;
+    f.y = (float)a.y;
+    return f;
+  };
+  auto ld = [=](int k) { return to_c128<float2>(FROM_W ? single(scaled(k)) : z[k]); };
+#pragma unroll 2
+  for (int m = 0; m < SPT; ++m) {
+    const int n = base + m * kBlock;
+    if (n >= t_hi) break;
+    w.set(n, normal12(g, ph, n, mu2, ld));
+    if (FROM_W) {
+      const double2 own = scaled(n);
+      vj.set(n, own);
+      z.set(n, single(own));
+    }
+  }
+  // each thread reads back its own sites only: no barrier
   double2 wv[SPT];
 #pragma unroll
   for (int m = 0; m < SPT; ++m) {
@@ -1680,9 +1803,11 @@ __global__ __launch_bounds__(kBlock) void k_multidot(const SysDesc* __restrict__
     wv[m] = cz<double2>();
     if (n < t_hi) wv[m] = w[n];
   }
-  __shared__ double tot[kMaxRed];
-  for (int q = 0; q < cnt; ++q) {
-    const Vec<double2> v(d->vec[s_v0 + q]);
+  __shared__ double sums[kBlock / 64][kMaxRed];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+#pragma unroll 2
+  for (int q = 0; q <= j; ++q) {
+    const Vec<double2> v(d->vec[S_V0 + q]);
     double ar = 0.0, ai = 0.0;
 #pragma unroll
     for (int m = 0; m < SPT; ++m) {
@@ -1693,24 +1818,35 @@ __global__ __launch_bounds__(kBlock) void k_multidot(const SysDesc* __restrict__
         ai += vv.x * wv[m].y - vv.y * wv[m].x;
       }
     }
-    const double sr = block_sum(ar);
-    const double si = block_sum(ai);
-    if (threadIdx.x == 0) {
-      tot[2 * q] = sr;
-      tot[2 * q + 1] = si;
+    ar = dpp_wave(ar);
+    ai = dpp_wave(ai);
+    if (lane == 63) {
+      sums[wave][2 * q] = ar;
+      sums[wave][2 * q + 1] = ai;
     }
   }
   __syncthreads();
-  store_partials(d, tile, tot, 2 * cnt);
+  const int nv = 2 * (j + 1);
+  double val = 0.0;
+  if ((int)threadIdx.x < nv)
+    val = (sums[0][threadIdx.x] + sums[1][threadIdx.x]) + (sums[2][threadIdx.x] + sums[3][threadIdx.x]);
+  const Publish none;
+  auto off = [](int q) { return q; };
+  auto done = [](Scal*, int, double, double) {};
+  if (nv <= 8)
+    close_tile<8>(L, kk, d, tile, val, nv, off, done, none);
+  else if (nv <= 32)
+    close_tile<32>(L, kk, d, tile, val, nv, off, done, none);
+  else
+    close_tile<64>(L, kk, d, tile, val, nv, off, done, none);
 }
 
-// w -= sum_i h_i v_i, h_i = red[h_off + 2i] + i red[h_off + 2i + 1]; partial of |w|^2.
+// w -= sum_i h_i v_i, i <= j, h_i = red[2i] + i red[2i+1]; |w|^2 into red[2j+2].
 template <int SPT>
-__global__ __launch_bounds__(kBlock) void k_cgs(const SysDesc* __restrict__ sys, LaunchList L, int s_w, int s_v0,
-                                                int cnt, int h_off) {
+__global__ __launch_bounds__(kBlock) void k_cgs(const SysDesc* __restrict__ sys, LaunchList L, int j, Publish pub) {
   constexpr int TILE = kBlock * SPT;
   HUB_PROLOGUE_T(TILE)
-  const Vec<double2> w(d->vec[s_w]);
+  const Vec<double2> w(d->vec[L.it[kk]]);
   double2 wv[SPT];
 #pragma unroll
   for (int m = 0; m < SPT; ++m) {
@@ -1718,9 +1854,10 @@ __global__ __launch_bounds__(kBlock) void k_cgs(const SysDesc* __restrict__ sys,
     wv[m] = cz<double2>();
     if (n < t_hi) wv[m] = w[n];
   }
-  for (int q = 0; q < cnt; ++q) {
-    const double hr = sc->red[h_off + 2 * q], hi = sc->red[h_off + 2 * q + 1];
-    const Vec<double2> v(d->vec[s_v0 + q]);
+#pragma unroll 2
+  for (int q = 0; q <= j; ++q) {
+    const double hr = sc->red[2 * q], hi = sc->red[2 * q + 1];
+    const Vec<double2> v(d->vec[S_V0 + q]);
 #pragma unroll
     for (int m = 0; m < SPT; ++m) {
       const int n = base + m * kBlock;
@@ -1741,23 +1878,20 @@ __global__ __launch_bounds__(kBlock) void k_cgs(const SysDesc* __restrict__ sys,
     }
   }
   const double tot = block_sum(acc);
-  store_partials(d, tile, &tot, 1);
+  close_tile<1>(
+      L, kk, d, tile, tot, 1, [=](int) { return 2 * (j + 1); }, [](Scal*, int, double, double) {}, pub);
 }
 
-// v = pa*src (FP64, stored to s_v if s_v >= 0).  With pi = maxit > 0 the
-// single-precision CG starts on v: r32 = c64(v), z = 0, partial of |r32|^2 (FP32
-// sums).  With pi = 0 there is no preconditioning: z = c64(v).  The z slot of
-// system k is pj[k].
+// v = pa*src (FP64, stored to s_v if s_v >= 0) and the single-precision CG's start on it:
+// r32 = c64(v), z = 0 (the slot pj), |r32|^2 (FP32 sums within a tile).
 template <int SPT>
-__global__ __launch_bounds__(kBlock) void k_prep_inner(const SysDesc* __restrict__ sys, LaunchList L, int s_src,
-                                                       int s_v) {
+__global__ __launch_bounds__(kBlock) void k_prep_inner(const SysDesc* __restrict__ sys, LaunchList L, int s_v) {
   constexpr int TILE = kBlock * SPT;
   HUB_PROLOGUE_T(TILE)
   (void)sc;
   const double scale = L.pa[kk];
-  const int maxit = L.pi[kk];
   const bool store_v = s_v >= 0;
-  const Vec<double2> src(d->vec[s_src]), v(store_v ? d->vec[s_v] : nullptr);
+  const Vec<double2> src(d->vec[L.it[kk]]), v(store_v ? d->vec[s_v] : nullptr);
   const Vec<float2> z(d->vec[L.pj[kk]]), r32(d->vec[S_R32]);
   float acc = 0.0f;
 #pragma unroll
@@ -1771,57 +1905,19 @@ __global__ __launch_bounds__(kBlock) void k_prep_inner(const SysDesc* __restrict
       float2 a32;
       a32.x = (float)a.x;
       a32.y = (float)a.y;
-      if (maxit > 0) {
-        r32.set(n, a32);
-        z.set(n, cz<float2>());
-        acc += norm2<float>(a32);
-      } else {
-        z.set(n, a32);
-      }
+      r32.set(n, a32);
+      z.set(n, cz<float2>());
+      acc += norm2<float>(a32);
     }
   }
-  if (maxit <= 0) return;
   const double tot = (double)block_sum(acc);
-  store_partials(d, tile, &tot, 1);
+  const Publish none;
+  close_tile<1>(
+      L, kk, d, tile, tot, 1, [](int) { return 0; },
+      [&](Scal* s, int, double rr, double) { cg_setup(s, rr, L.pr[kk] * rr, L.pi[kk]); }, none);
 }
 
-// One workgroup per system and value (grid nsys x nv): sum the generic partials of
-// value q in a fixed order into red[red_off + q]; with RED_CG_SETUP the q = 0
-// workgroup also starts a CG on rr = result[0]: stop2 = pa + pr*rr, maxit = pi,
-// iters 0, active iff rr > stop2.
-__global__ __launch_bounds__(kBlock) void k_finish(const SysDesc* __restrict__ sys, LaunchList L, int red_off,
-                                                   int mode) {
-  const int kk = blockIdx.x, q = blockIdx.y;
-  const SysDesc* __restrict__ d = sys + L.sys[kk];
-  Scal* sc = d->sc;
-  const double s = sum_partials(d->part + q, d->ntiles, kMaxRed);
-  if (threadIdx.x == 0) {
-    sc->red[red_off + q] = s;
-    if (q == 0 && mode == RED_CG_SETUP) {
-      const double stop2 = L.pa[kk] + L.pr[kk] * s;
-      sc->rrv[0] = s;
-      sc->stop2 = stop2;
-      sc->maxit = L.pi[kk];
-      sc->iters = 0;
-      sc->git = 0;
-      sc->gang = 0;
-      store_active(sc, s > stop2 ? 1 : 0);
-    }
-  }
-}
-
-// Scal records to host-coherent memory, every thread's stores made visible at system
-// scope before the barrier, then the flag.
-__global__ __launch_bounds__(kBlock) void k_publish(const Scal* __restrict__ d, Scal* h, int nw, unsigned* flag,
-                                                    unsigned seq) {
-  const unsigned long long* __restrict__ src = reinterpret_cast<const unsigned long long*>(d);
-  unsigned long long* dst = reinterpret_cast<unsigned long long*>(h);
-  for (int k = threadIdx.x; k < nw; k += kBlock) dst[k] = src[k];
-  __threadfence_system();
-  __syncthreads();
-  if (threadIdx.x == 0) __hip_atomic_store(flag, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
+__global__ __launch_bounds__(kBlock) void k_publish(Publish pub) { publish(pub); }
 
 // x = (set ? 0 : x) + sum_{i < cnt} y_i z_i, y from ys (row of the system's slot), z_i the
 // C64 slot S_Z0 + i.
@@ -1859,81 +1955,6 @@ __global__ __launch_bounds__(kBlock) void k_xupdate(const SysDesc* __restrict__ 
     const int n = base + m * kBlock;
     if (n < t_hi) x.set(n, xv[m]);
   }
-}
-
-// One Arnoldi step of small systems (at most kArnWgMaxSites sites), one workgroup per
-// system: w = (M M^dagger + mu2) z_j in FP64 (the 12-point form), the classical
-// Gram-Schmidt coefficients h_i = <v_i, w> against the unmodified w for i <= j, w -= sum_i
-// h_i v_i in the order of i, and |w|^2.  Each reduction is a workgroup sum in a fixed order;
-// the results land where the tiled path's reductions put them (red[2i], red[2i+1]: h_i,
-// red[2(j+1)]: |w|^2).  One launch and one read of the basis replace the tiled path's five
-// launches and two reads.
-__global__ __launch_bounds__(kWgBlock) void k_arnoldi_wg(const SysDesc* __restrict__ sys, WgList L, int j) {
-  const SysDesc* __restrict__ d = sys + L.sys[blockIdx.x];
-  Scal* sc = d->sc;
-  const Geom g = d->g;
-  const int N = g.n;
-  const Vec<float2> z(d->vec[S_Z0 + j]);
-  const Vec<double2> w(d->vec[S_R]);
-  const PhasePhi<double> ph = phase_of<double>(d);
-  const double mu2 = d->mu2;
-  __shared__ double red[2][kWgBlock / 64];
-  auto ld = [=](int k) { return to_c128<float2>(z[k]); };
-  __shared__ double hs[2 * (kMaxRestart + 1)];  // the coefficients, for the subtraction pass
-#pragma unroll 1
-  for (int n = threadIdx.x; n < N; n += kWgBlock) w.set(n, normal12(g, ph, n, mu2, ld));
-  // each thread reads back only its own sites of w: no barrier
-  double2 w0[kWgPerThread];
-#pragma unroll
-  for (int m = 0; m < kWgPerThread; ++m) {
-    const int n = threadIdx.x + m * kWgBlock;
-    w0[m] = cz<double2>();
-    if (n < N) w0[m] = w[n];
-  }
-  int b = 0;
-  for (int q = 0; q <= j; ++q) {
-    const Vec<double2> v(d->vec[S_V0 + q]);
-    double ar = 0.0, ai = 0.0;
-#pragma unroll
-    for (int m = 0; m < kWgPerThread; ++m) {
-      const int n = threadIdx.x + m * kWgBlock;
-      if (n < N) {
-        const double2 vv = v[n];
-        ar += vv.x * w0[m].x + vv.y * w0[m].y;
-        ai += vv.x * w0[m].y - vv.y * w0[m].x;
-      }
-    }
-    const double hr = wg_sum(ar, red[b]);
-    b ^= 1;
-    const double hi = wg_sum(ai, red[b]);
-    b ^= 1;
-    if (threadIdx.x == 0) {
-      hs[2 * q] = hr;
-      hs[2 * q + 1] = hi;
-      sc->red[2 * q] = hr;
-      sc->red[2 * q + 1] = hi;
-    }
-  }
-  __syncthreads();  // hs complete
-  // w -= sum_i h_i v_i, in the order of i at every site
-  double acc = 0.0;
-#pragma unroll
-  for (int m = 0; m < kWgPerThread; ++m) {
-    const int n = threadIdx.x + m * kWgBlock;
-    if (n < N) {
-      double2 wc = w0[m];
-      for (int q = 0; q <= j; ++q) {
-        const double2 vv = Vec<double2>(d->vec[S_V0 + q])[n];
-        const double hr = hs[2 * q], hi = hs[2 * q + 1];
-        wc.x -= hr * vv.x - hi * vv.y;
-        wc.y -= hr * vv.y + hi * vv.x;
-      }
-      w.set(n, wc);
-      acc += norm2<double>(wc);
-    }
-  }
-  const double ww = wg_sum(acc, red[b]);
-  if (threadIdx.x == 0) sc->red[2 * (j + 1)] = ww;
 }
 
 }  // namespace
@@ -2158,25 +2179,11 @@ hipError_t launch_cg_stage(const SysDesc* sys, const LaunchList& L, bool single,
 }
 
 
-hipError_t launch_arnoldi_wg(const SysDesc* sys, const WgList& L, int j, hipStream_t st) {
-  if (L.nsys < 1 || L.nsys > kMaxSys || j < 0 || j >= kMaxRestart) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_arnoldi_wg, dim3(L.nsys), dim3(kWgBlock), 0, st, sys, L, j);
+hipError_t launch_publish(const Publish& pub, hipStream_t st) {
+  if (pub.cnt < 1 || pub.cnt > kMaxSys || !pub.d || !pub.h || !pub.flag) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_publish, dim3(1), dim3(kBlock), 0, st, pub);
   return hipGetLastError();
 }
-
-hipError_t launch_publish(const Scal* d, Scal* h, int cnt, unsigned* flag, unsigned seq, hipStream_t st) {
-  if (cnt < 1 || cnt > kMaxSys || !d || !h || !flag) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_publish, dim3(1), dim3(kBlock), 0, st, d, h, cnt * (int)(sizeof(Scal) / 8), flag, seq);
-  return hipGetLastError();
-}
-
-static hipError_t finish(const SysDesc* sys, const LaunchList& L, int nv, int red_off, RedMode mode,
-                         hipStream_t st) {
-  if (nv < 1 || nv > kMaxRed || red_off < 0 || red_off + nv > kMaxRed) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_finish, dim3(L.nsys, nv), dim3(kBlock), 0, st, sys, L, red_off, (int)mode);
-  return hipGetLastError();
-}
-
 
 // Launch KERNEL<..., SPT> for the tile class of L.
 #define HUB_BY_CLASS(KERNEL, GRID, ...)                                                       \
@@ -2187,64 +2194,45 @@ static hipError_t finish(const SysDesc* sys, const LaunchList& L, int nv, int re
       hipLaunchKernelGGL(KERNEL<kSitesPerThread>, GRID, dim3(kBlock), 0, st, __VA_ARGS__);    \
   } while (0)
 
-hipError_t launch_normal_slot(const SysDesc* sys, const LaunchList& L, int s_in, bool in_c64, int s_b, int s_out,
-                              RedMode mode, int red_off, hipStream_t st) {
-  if (!spt_ok(L)) return hipErrorInvalidValue;
+hipError_t launch_normal_slot(const SysDesc* sys, const LaunchList& L, int s_in, int s_b, int s_out, RedMode mode,
+                              int red_off, bool with_bb, const Publish& pub, hipStream_t st) {
+  if (!spt_ok(L) || red_off < (with_bb ? 1 : 0) || red_off >= kMaxRed) return hipErrorInvalidValue;
   const dim3 grid(L.total_tiles), block(kBlock);
   const bool small = L.spt == kSmallSpt;
-  auto kern = in_c64 ? (small ? k_normal_slot<float2, kSmallSpt> : k_normal_slot<float2, kSitesPerThread>)
-                     : (small ? k_normal_slot<double2, kSmallSpt> : k_normal_slot<double2, kSitesPerThread>);
-  hipLaunchKernelGGL(kern, grid, block, 0, st, sys, L, s_in, s_b, s_out, (int)mode);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || mode == RED_NONE) return e;
-  return finish(sys, L, 1, red_off, mode, st);
+  auto kern = with_bb ? (small ? k_normal_slot<kSmallSpt, true> : k_normal_slot<kSitesPerThread, true>)
+                      : (small ? k_normal_slot<kSmallSpt, false> : k_normal_slot<kSitesPerThread, false>);
+  hipLaunchKernelGGL(kern, grid, block, 0, st, sys, L, s_in, s_b, s_out, (int)mode, red_off, pub);
+  return hipGetLastError();
 }
 
-hipError_t launch_cg_init_zero(const SysDesc* sys, const LaunchList& L, RedMode mode, hipStream_t st) {
+hipError_t launch_cg_init_zero(const SysDesc* sys, const LaunchList& L, RedMode mode, const Publish& pub,
+                               hipStream_t st) {
   if (!spt_ok(L)) return hipErrorInvalidValue;
-  HUB_BY_CLASS(k_cg_init_zero, dim3(L.total_tiles), sys, L);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return finish(sys, L, 1, 0, mode, st);
+  HUB_BY_CLASS(k_cg_init_zero, dim3(L.total_tiles), sys, L, (int)mode, pub);
+  return hipGetLastError();
 }
 
-hipError_t launch_multidot(const SysDesc* sys, const LaunchList& L, int s_w, int s_v0, int cnt, int red_off,
-                           hipStream_t st) {
-  if (!spt_ok(L)) return hipErrorInvalidValue;
-  HUB_BY_CLASS(k_multidot, dim3(L.total_tiles), sys, L, s_w, s_v0, cnt);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return finish(sys, L, 2 * cnt, red_off, RED_STORE, st);
-}
-
-hipError_t launch_cgs(const SysDesc* sys, const LaunchList& L, int s_w, int s_v0, int cnt, int h_off, int red_off,
-                      hipStream_t st) {
-  if (!spt_ok(L)) return hipErrorInvalidValue;
-  HUB_BY_CLASS(k_cgs, dim3(L.total_tiles), sys, L, s_w, s_v0, cnt, h_off);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return finish(sys, L, 1, red_off, RED_STORE, st);
-}
-
-hipError_t launch_prep_inner(const SysDesc* sys, const LaunchList& L, int s_src, int s_v, hipStream_t st) {
-  if (!spt_ok(L)) return hipErrorInvalidValue;
-  HUB_BY_CLASS(k_prep_inner, dim3(L.total_tiles), sys, L, s_src, s_v);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  // only systems that start a single-precision CG (pi > 0) are finalised
-  LaunchList F = L;
-  int m = 0;
+hipError_t launch_arnoldi_dots(const SysDesc* sys, const LaunchList& L, int j, bool from_w, hipStream_t st) {
+  if (!spt_ok(L) || j < 0 || j >= kMaxRestart) return hipErrorInvalidValue;
   for (int k = 0; k < L.nsys; ++k)
-    if (L.pi[k] > 0) {
-      F.sys[m] = L.sys[k];
-      F.pa[m] = 0.0;
-      F.pr[m] = L.pr[k];
-      F.pi[m] = L.pi[k];
-      ++m;
-    }
-  if (m == 0) return hipSuccess;
-  F.nsys = m;
-  return finish(sys, F, 1, 0, RED_CG_SETUP, st);
+    if (L.it[k] != S_R && L.it[k] != S_U) return hipErrorInvalidValue;
+  const bool small = L.spt == kSmallSpt;
+  auto kern = from_w ? (small ? k_arnoldi_dots<kSmallSpt, true> : k_arnoldi_dots<kSitesPerThread, true>)
+                     : (small ? k_arnoldi_dots<kSmallSpt, false> : k_arnoldi_dots<kSitesPerThread, false>);
+  hipLaunchKernelGGL(kern, dim3(L.total_tiles), dim3(kBlock), 0, st, sys, L, j);
+  return hipGetLastError();
+}
+
+hipError_t launch_cgs(const SysDesc* sys, const LaunchList& L, int j, const Publish& pub, hipStream_t st) {
+  if (!spt_ok(L) || j < 0 || j >= kMaxRestart) return hipErrorInvalidValue;
+  HUB_BY_CLASS(k_cgs, dim3(L.total_tiles), sys, L, j, pub);
+  return hipGetLastError();
+}
+
+hipError_t launch_prep_inner(const SysDesc* sys, const LaunchList& L, int s_v, hipStream_t st) {
+  if (!spt_ok(L)) return hipErrorInvalidValue;
+  HUB_BY_CLASS(k_prep_inner, dim3(L.total_tiles), sys, L, s_v);
+  return hipGetLastError();
 }
 
 hipError_t launch_xupdate(const SysDesc* sys, const LaunchList& L, const double* ys, int cnt, bool set,
