@@ -541,7 +541,7 @@ hub_status run_solves(hub_ctx* ctx, std::vector<System>& sys, const hub_solve_op
       if (all) break;
     }
   }
-  for (size_t k = 0; k < added; ++k) eng->remove(&sys[k]);
+  for (size_t k = 0; k < added; ++k) eng->remove(&sys[k], &owned);
   ctx->pool->release_all(owned, stream);
   hipError_t e = hipStreamSynchronize(stream);
   if (result != HUB_OK) return result;

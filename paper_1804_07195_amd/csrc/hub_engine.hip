@@ -53,10 +53,11 @@ Pool::Pool(int device, size_t budget) : device_(device), budget_(budget) {}
 
 Pool::~Pool() {
   (void)hipSetDevice(device_);
-  for (auto& b : free_) {
-    drop_event(b.ev, true);
-    (void)hipFree(b.p);
-  }
+  for (auto& f : free_)
+    for (auto& b : f.second) {
+      drop_event(b.ev, true);
+      (void)hipFree(b.p);
+    }
   for (auto& l : live_) (void)hipFree(l.first);
 }
 
@@ -84,21 +85,27 @@ void* Pool::alloc(size_t bytes, hipStream_t st) {
   std::lock_guard<std::mutex> lk(mu_);
   // reuse a cached block of the same size: at once on the stream that released it,
   // on another stream once the work before the release has finished
-  for (size_t k = 0; k < free_.size(); ++k) {
-    Block& b = free_[k];
-    if (b.bytes != sz) continue;
-    if (b.st != st && b.ev && b.ev->ev && hipEventQuery(b.ev->ev) != hipSuccess) continue;
-    void* p = b.p;
-    drop_event(b.ev, false);
-    free_.erase(free_.begin() + (long)k);
-    live_.emplace_back(p, sz);
-    used_ += sz;
-    return p;
+  auto same = free_.find(sz);
+  if (same != free_.end()) {
+    auto& f = same->second;
+    for (size_t k = 0; k < f.size(); ++k) {
+      Block& b = f[k];
+      if (b.st != st && b.ev && b.ev->ev && hipEventQuery(b.ev->ev) != hipSuccess) continue;
+      void* p = b.p;
+      drop_event(b.ev, false);
+      f.erase(f.begin() + (long)k);
+      if (f.empty()) free_.erase(same);
+      live_.emplace(p, sz);
+      used_ += sz;
+      return p;
+    }
   }
-  // release cached blocks until the new one fits
+  // release cached blocks, the largest first, until the new one fits
   while (reserved_ + sz > budget_ && !free_.empty()) {
-    Block b = free_.back();
-    free_.pop_back();
+    auto last = std::prev(free_.end());
+    Block b = last->second.back();
+    last->second.pop_back();
+    if (last->second.empty()) free_.erase(last);
     drop_event(b.ev, true);
     (void)hipFree(b.p);
     reserved_ -= b.bytes;
@@ -116,7 +123,7 @@ void* Pool::alloc(size_t bytes, hipStream_t st) {
   }
   reserved_ += sz;
   used_ += sz;
-  live_.emplace_back(p, sz);
+  live_.emplace(p, sz);
   return p;
 }
 
@@ -129,24 +136,22 @@ void Pool::release_all(const std::vector<void*>& ps, hipStream_t st) {
   SharedEvent* e = nullptr;
   for (void* p : ps) {
     if (!p) continue;
-    for (size_t k = 0; k < live_.size(); ++k) {
-      if (live_[k].first != p) continue;
-      if (!e) {
-        e = new SharedEvent;
-        if (hipEventCreateWithFlags(&e->ev, hipEventDisableTiming) != hipSuccess ||
-            hipEventRecord(e->ev, st) != hipSuccess) {
-          // no event to order later users after the stream's work: wait for it here
-          if (e->ev) (void)hipEventDestroy(e->ev);
-          e->ev = nullptr;
-          (void)hipStreamSynchronize(st);
-        }
+    const auto l = live_.find(p);
+    if (l == live_.end()) continue;
+    if (!e) {
+      e = new SharedEvent;
+      if (hipEventCreateWithFlags(&e->ev, hipEventDisableTiming) != hipSuccess ||
+          hipEventRecord(e->ev, st) != hipSuccess) {
+        // no event to order later users after the stream's work: wait for it here
+        if (e->ev) (void)hipEventDestroy(e->ev);
+        e->ev = nullptr;
+        (void)hipStreamSynchronize(st);
       }
-      e->refs++;
-      free_.push_back(Block{p, live_[k].second, st, e});
-      used_ -= live_[k].second;
-      live_.erase(live_.begin() + (long)k);
-      break;
     }
+    e->refs++;
+    free_[l->second].push_back(Block{p, l->second, st, e});
+    used_ -= l->second;
+    live_.erase(l);
   }
 }
 
@@ -433,7 +438,7 @@ hipError_t Engine::join_gangs(const std::vector<System*>& v, std::vector<void*>&
   return hipSuccess;
 }
 
-void Engine::remove(System* s) {
+void Engine::remove(System* s, std::vector<void*>* owned) {
   // drain blocks that still reference the system
   for (auto& q : inflight_) {
     bool refs = false;
@@ -445,7 +450,10 @@ void Engine::remove(System* s) {
     q.clear();
   }
   if (s->slot >= 0 && slots_[s->slot] == s) slots_[s->slot] = nullptr;
-  pool_->release_all(s->owned, st_);
+  if (owned)
+    owned->insert(owned->end(), s->owned.begin(), s->owned.end());
+  else
+    pool_->release_all(s->owned, st_);
   s->owned.clear();
   s->slot = -1;
 }
@@ -855,18 +863,17 @@ hipError_t Engine::take_event(std::vector<hipEvent_t>& dst) {
   return hipSuccess;
 }
 
-// System s joins the launch G; false: no room.  Blocks go to the XCDs in turn (block b to
+// System s joins the launch G, of whose blocks `taken` are given away per XCD; false: no room.  Blocks go to the XCDs in turn (block b to
 // XCD b mod 8), so a gang takes its blocks with a stride, consecutive workgroups on one XCD:
 // a reduction among 16 workgroups takes 2.0 us on one XCD and 2.45 us over all.  More than
 // about a dozen of one gang on an XCD get into each other's way (the FP64 iteration of a
 // 48x48x64 system 8.1 us with 28 on each of five XCDs, 7.0 us with 18 on each of eight).
-bool Engine::gang_entry(GangList& G, System* s, bool single) const {
+bool Engine::gang_entry(GangList& G, int (&taken)[kNumXcd], System* s, bool single) const {
   constexpr int kPer = kGangMaxWgs / kNumXcd;  // blocks per XCD
   constexpr int kSpread = 12;                  // workgroups of a gang per XCD, while others are free
   if (G.nsys == 0) std::memset(G.list, kGangNone, sizeof(G.list));
-  int room[kNumXcd] = {0}, total = 0;
-  for (int b = 0; b < kGangMaxWgs; ++b)
-    if (G.list[b] == kGangNone) ++room[b % kNumXcd], ++total;
+  int room[kNumXcd], total = 0;
+  for (int x = 0; x < kNumXcd; ++x) total += room[x] = kPer - taken[x];
   const int g = s->desc.gang.g;
   if (g > total || G.nsys == kMaxSys) return false;
   // the XCDs with the most room, an even share on each
@@ -882,13 +889,12 @@ bool Engine::gang_entry(GangList& G, System* s, bool single) const {
     for (int q = k + 1; q < nx; ++q) later += room[order[q]];
     int n = std::max(std::min((left + nx - k - 1) / (nx - k), room[x]), left - later);
     left -= n;
-    for (int b = x; b < kGangMaxWgs && n > 0; b += kNumXcd)
-      if (G.list[b] == kGangNone) {
-        G.list[b] = (unsigned char)G.nsys;
-        G.wg[b] = (unsigned char)wg++;
-        G.nblock = std::max(G.nblock, b + 1);
-        --n;
-      }
+    for (; n > 0; --n) {
+      const int b = x + kNumXcd * taken[x]++;
+      G.list[b] = (unsigned char)G.nsys;
+      G.wg[b] = (unsigned char)wg++;
+      G.nblock = std::max(G.nblock, b + 1);
+    }
   }
   static_assert(kPer * kNumXcd == kGangMaxWgs && kGangMaxWgs <= 256 && kMaxSys < kGangNone, "block table");
   G.scal = d_scal_;
@@ -906,9 +912,10 @@ hipError_t Engine::launch_gangs(const std::vector<System*>& v, bool single, Bloc
   for (size_t q = 0; q < v.size();) {
     GangList G;
     std::memset(&G, 0, sizeof(G));
+    int taken[kNumXcd] = {0};
     for (; q < v.size(); ++q) {
       System* s = v[q];
-      if (!gang_entry(G, s, single)) break;
+      if (!gang_entry(G, taken, s, single)) break;
       s->gang_tag += kGangIters + 2;  // a launch uses two tags before its iterations'
       s->enq += kGangIters;
     }
@@ -940,7 +947,8 @@ hipError_t Engine::leave_gangs(bool single) {
       s->enq = h_scal_[s->slot].git;
       GangList G;
       std::memset(&G, 0, sizeof(G));
-      gang_entry(G, s, single);
+      int taken[kNumXcd] = {0};
+      gang_entry(G, taken, s, single);
       HUB_TRY(launch_gang_leave(d_desc_, G, s->desc.ntiles, single, st_));
     }
     s->gang = false;
