@@ -67,9 +67,11 @@ class Pool {
 
 // Block length (CG iterations between flag reads) near a system's expected end.
 constexpr int kTailBlock = 4;
-// Iterations of a gang launch (a gang leaves its launch at convergence) and meetings in a
-// row that a gang may miss before its system goes on with the tiled kernels.
-constexpr int kGangIters = 128;
+// Iterations of a gang launch (a gang leaves its launch at convergence): a system that has
+// stopped waits for the others of its launch, and only with others; a launch costs 12 us
+// (6x6x16) to 32 us (102x102x64) before its first iteration.  And meetings in a row that a
+// gang may miss before its system goes on with the tiled kernels.
+constexpr int kGangIters = 128, kGangItersAlone = 512;
 constexpr int kGangMisses = 3;
 
 // Host-side state of one linear system (M M^dagger + mu2) x = b.

@@ -916,8 +916,11 @@ hipError_t Engine::launch_gangs(const std::vector<System*>& v, bool single, Bloc
     for (; q < v.size(); ++q) {
       System* s = v[q];
       if (!gang_entry(G, taken, s, single)) break;
-      s->gang_tag += kGangIters + 2;  // a launch uses two tags before its iterations'
-      s->enq += kGangIters;
+    }
+    const int iters = G.nsys == 1 ? kGangItersAlone : kGangIters;
+    for (size_t k = q - G.nsys; k < q; ++k) {
+      v[k]->gang_tag += iters + 2;  // a launch uses two tags before its iterations'
+      v[k]->enq += iters;
     }
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (profiling_) {
@@ -926,7 +929,7 @@ hipError_t Engine::launch_gangs(const std::vector<System*>& v, bool single, Bloc
       e0 = b.gev[b.gev.size() - 2];
       e1 = b.gev.back();
     }
-    HUB_TRY(launch_gang(d_desc_, G, kGangIters, single, st_, e0, e1));
+    HUB_TRY(launch_gang(d_desc_, G, iters, single, st_, e0, e1));
   }
   return hipSuccess;
 }

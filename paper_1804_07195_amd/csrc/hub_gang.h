@@ -18,6 +18,7 @@ constexpr int kGangHead = 256;
 constexpr int kGangLinks = 65280;
 constexpr int kGangLdsBytes = kGangHead + 2 * kGangLinks;
 constexpr int kGangRecWords = 4;               // 8-byte words of a reduction record
+constexpr int kGangCopies = 8;                 // of every record: workgroup k polls copy k mod 8
 constexpr int kGangCtlWords = 32;              // 8-byte control words in front of the records
 
 // Classes of the kernel: sites (M), halo elements (H) and extra sites (X) per thread.  The
@@ -256,12 +257,12 @@ inline int gang_class(const GangBlock& B) {
   return -1;
 }
 
-// Words of a system's exchange memory: control words, two parities of reduction records,
+// Words of a system's exchange memory: control words, two parities of reduction records (copies),
 // two parities of sites; and of the state its workgroups keep between launches (r, p, s, z
 // in the order of their registers).
 template <typename R>
 __host__ __device__ inline size_t gang_exch_words(int g, int nslot) {
-  return (size_t)kGangCtlWords + 2 * (size_t)g * kGangRecWords + 2 * (size_t)g * nslot * (sizeof(R) / 2);
+  return (size_t)kGangCtlWords + 2 * (size_t)g * kGangCopies * kGangRecWords + 2 * (size_t)g * nslot * (sizeof(R) / 2);
 }
 
 template <typename R>

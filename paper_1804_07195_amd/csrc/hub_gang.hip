@@ -227,6 +227,13 @@ __device__ __forceinline__ void gang_chunks(int half, F f) {
     }
 }
 
+__device__ __forceinline__ double from_lane(double v, int lane) {
+  const long long b = __double_as_longlong(v);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, lane);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b >> 32), lane);
+  return __longlong_as_double((long long)((u64)hi << 32 | lo));
+}
+
 template <typename R, int CLS>
 __device__ __forceinline__ void gang_run(const SysDesc* __restrict__ d, Scal* sc, const int wg, const int zslot,
                                          const unsigned tag0, const unsigned seq, const unsigned arrived, const int K,
@@ -241,6 +248,9 @@ __device__ __forceinline__ void gang_run(const SysDesc* __restrict__ d, Scal* sc
   constexpr bool ZMEM = CLS == GangTab<R>::n - 1;
   // Two bonds of a site share a register where a register per bond would not fit.
   constexpr bool PACK = single ? M > 8 : M > 3;
+  // The small bodies have registers for every address (12x12x32: 3.1 us an iteration when they
+  // work them out anew, 2.9 us when not); the others do not (FP64 at 48x48x64: 6.6, 8.6).
+  constexpr bool KEEP = M <= (single ? 3 : 2);
   constexpr int sR = single ? (int)S_R32 : (int)S_R, sP = single ? (int)S_P32 : (int)S_P0;
   double2* const red = reinterpret_cast<double2*>(lds);        // (gamma, |u|^2) of each wave
   double2* const red2 = red + kGangWaves;                      // of each wave's share of the records
@@ -255,7 +265,8 @@ __device__ __forceinline__ void gang_run(const SysDesc* __restrict__ d, Scal* sc
   C* const F = reinterpret_cast<C*>(lds + kGangHead);               // the field: r, then M^dagger r in its place
   C* const E = reinterpret_cast<C*>(lds + kGangHead + kGangLinks);  // the temporal links
   const Mem mem(d->gang_mem, g > 1 ? gang_exch_words<R>(g, nslot) * 8 : 0);
-  const unsigned rec_base = kGangCtlWords * 8, rec_half = (unsigned)g * (kGangRecWords * 8);
+  const unsigned rec_base = kGangCtlWords * 8, rec_copy = (unsigned)g * (kGangRecWords * 8),
+                 rec_half = kGangCopies * rec_copy;
   const unsigned ex_base = rec_base + 2 * rec_half, ex_half = (unsigned)g * nslot * TW::BYTES;
 
   // This thread's sites: k = k0 + m kGangHalf of sublattice sub (the same in a whole wave).
@@ -493,13 +504,19 @@ __device__ __forceinline__ void gang_run(const SysDesc* __restrict__ d, Scal* sc
       }
     }
   };
+  // Lanes below kGangCopies of a wave store the copies of this workgroup's record.  By
+  // itself a reduction through one copy that all poll takes 0.3 us (16 workgroups) to 0.65 us
+  // (256) longer; in the iteration it is what 256 workgroups wait for (48x48x64: 4.35 us with
+  // one copy, 4.15 us with eight), fewer of them wait for the faces.
   auto post = [&](double a, double b, unsigned tag) {
-    Tagged<double2>::store(mem, (unsigned)wg * (kGangRecWords * 8), rec_base + (tag & 1) * rec_half, double2{a, b}, tag);
+    if (lane < kGangCopies)
+      Tagged<double2>::store(mem, (unsigned)lane * rec_copy + (unsigned)wg * (kGangRecWords * 8),
+                             rec_base + (tag & 1) * rec_half, double2{a, b}, tag);
   };
   // The records of all workgroups, 64 to a wave, in a fixed order, into red2.
   const int nw = g > 1 ? (g + 63) / 64 : 1;
   auto collect = [&](unsigned tag) {
-    const unsigned rec = rec_base + (tag & 1) * rec_half;
+    const unsigned rec = rec_base + (tag & 1) * rec_half + (unsigned)(wg % kGangCopies) * rec_copy;
     const int c = wave * 64 + lane;
     double2 q = cz<double2>();
     if (c < g) {
@@ -571,7 +588,7 @@ __device__ __forceinline__ void gang_run(const SysDesc* __restrict__ d, Scal* sc
     if (it0 > 0) receive(tag0 + 2, [&](int h, C v) { sh[h] = v; });
     // nobody writes over these faces before all have read them
     __syncthreads();
-    if (tid == 0) post(0.0, 0.0, tag0 + 2);
+    if (wave == 0) post(0.0, 0.0, tag0 + 2);
     if (wave < nw) collect(tag0 + 2);
   }
   __syncthreads();
@@ -586,7 +603,7 @@ __device__ __forceinline__ void gang_run(const SysDesc* __restrict__ d, Scal* sc
     // for all passes, once for both passes) and run out of registers.
     auto unseen = [] {
       int o = 0;
-      asm volatile("" : "+v"(o));
+      if (!KEEP) asm volatile("" : "+v"(o));
       return o;
     };
     int o = unseen();
@@ -612,12 +629,10 @@ __device__ __forceinline__ void gang_run(const SysDesc* __restrict__ d, Scal* sc
     if (wave == 0) {
       const double2 q = lane < kGangWaves ? red[lane] : cz<double2>();
       const double sg = dpp_row(q.x), su = dpp_row(q.y);
-      if (lane == 15) {
-        if (g > 1)
-          post(sg, su, tag);
-        else
-          red2[0] = double2{sg, su};
-      }
+      if (g > 1)
+        post(from_lane(sg, 15), from_lane(su, 15), tag);
+      else if (lane == 15)
+        red2[0] = double2{sg, su};
     }
     put_own(v, o);
     if (g > 1) gang_chunks<X, X>(nx, [&](int x) { at(xa[x]) = xv[x]; });

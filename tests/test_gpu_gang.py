@@ -48,11 +48,13 @@ def test_fp64_iterates(hub, shape):
     op = NormalOperator(ol, phi, mu2)
     for k in (1, 2, 6, 129, 259):
         want, its, rel = oracle_cg(op, b.ravel(), tol=1e-13, maxiter=k)
-        x, info, st = hb.hub_solve(hub, hl, dev(phi), [mu2], dev(b[None]),
-                                   opts=hb.default_opts(solver="cg", max_iter=k, tol=1e-13), allow_noconv=True)
-        if its == k:
-            assert info[0]["inner_iters"] == k
-        assert rel2(host(x)[0].ravel(), want) <= 1e-12, k
+        # alone, and with another: the launches are longer for one
+        for rhs in ([b], [b, 2 * b]):
+            x, info, st = hb.hub_solve(hub, hl, dev(phi), [mu2] * len(rhs), dev(np.stack(rhs)),
+                                       opts=hb.default_opts(solver="cg", max_iter=k, tol=1e-13), allow_noconv=True)
+            if its == k:
+                assert info[0]["inner_iters"] == k
+            assert rel2(host(x)[0].ravel(), want) <= 1e-12, k
         if its < k:
             break
 
