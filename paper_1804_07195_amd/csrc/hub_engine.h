@@ -96,6 +96,7 @@ struct System {
   int j = 0;            // Arnoldi step
   int wslot = 0;        // the slot of S_R, S_U that holds the residual or the Arnoldi vector w
   bool plain = false;   // the Arnoldi step runs without an inner solve
+  double rate = 1.0;    // what the last such step left of ERR
   int cycles = 0;
   int cg_total = 0;     // FP64 CG iterations over all restarts
   int enq = 0;          // CG iterations enqueued since the last CG setup
@@ -185,6 +186,7 @@ class Engine {
   hipError_t read_scal(const std::vector<System*>& v);
   // The publication of the Scal records of v at the end of a following launch, and the wait
   // for it (h_scal_ holds the records then).
+  hipError_t launch_arnoldi(const std::vector<System*>& v, int j, Publish& pub);
   Publish publication(const std::vector<System*>& v);
   hipError_t wait_publication(const Publish& pub);
   // Descriptors and FGMRES update coefficients go to pinned staging rows (slot-indexed)
@@ -210,7 +212,7 @@ class Engine {
   int desc_lo_ = kMaxSys, desc_hi_ = -1, y_lo_ = kMaxSys, y_hi_ = -1;  // rows to copy
   Scal* d_scal_ = nullptr;      // kMaxSys records, then kScalCounters counters
   Scal* h_scal_ = nullptr;      // pinned mirror
-  Scal* h_pub_ = nullptr;       // host-coherent copy of published records, followed by its flag
+  Scal* h_pub_ = nullptr;       // host-coherent, two buffers of published records, then their flag
   unsigned* h_pub_flag_ = nullptr;
   unsigned pub_seq_ = 0;
   std::vector<System*> slots_;

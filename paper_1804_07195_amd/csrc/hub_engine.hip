@@ -231,12 +231,12 @@ Engine::Engine(Pool* pool, hipStream_t st) : pool_(pool), st_(st), slots_(kMaxSy
         hipMalloc(&d_scal_, kScalBytes) == hipSuccess &&
         hipHostMalloc(&h_scal_, sizeof(Scal) * kMaxSys, hipHostMallocDefault) == hipSuccess &&
         hipHostMalloc(&h_flags_, sizeof(Scal) * kMaxSys * 4 + 256, hipHostMallocCoherent) == hipSuccess &&
-        hipHostMalloc(&h_pub_, sizeof(Scal) * kMaxSys + 256, hipHostMallocCoherent) == hipSuccess &&
+        hipHostMalloc(&h_pub_, sizeof(Scal) * kMaxSys * 2 + 256, hipHostMallocCoherent) == hipSuccess &&
         hipMemsetAsync(d_scal_, 0, kScalBytes, st_) == hipSuccess;
   if (ok_) {
     std::memset(h_scal_, 0, sizeof(Scal) * kMaxSys);
-    std::memset(h_pub_, 0, sizeof(Scal) * kMaxSys + 256);
-    h_pub_flag_ = reinterpret_cast<unsigned*>(reinterpret_cast<char*>(h_pub_) + sizeof(Scal) * kMaxSys);
+    std::memset(h_pub_, 0, sizeof(Scal) * kMaxSys * 2 + 256);
+    h_pub_flag_ = reinterpret_cast<unsigned*>(reinterpret_cast<char*>(h_pub_) + sizeof(Scal) * kMaxSys * 2);
     std::memset(h_flags_, 0, sizeof(Scal) * kMaxSys * 4 + 256);
     h_blk_flag_ = reinterpret_cast<unsigned*>(reinterpret_cast<char*>(h_flags_) + sizeof(Scal) * kMaxSys * 4);
   }
@@ -522,26 +522,26 @@ Publish Engine::publication(const std::vector<System*>& v) {
   }
   Publish pub;
   pub.d = d_scal_ + lo;
-  pub.h = h_pub_ + lo;
-  pub.cnt = hi - lo + 1;
   pub.seq = ++pub_seq_;
+  pub.h = h_pub_ + (size_t)(pub.seq & 1) * kMaxSys + lo;
+  pub.cnt = hi - lo + 1;
   pub.flag = h_pub_flag_;
   return pub;
 }
 
 // A kernel writes the records and then a sequence number to host-coherent memory and
 // the host polls the number: about half the latency of a copy plus a stream
-// synchronisation.  hipStreamQuery bounds the wait; should the stream drain without
+// synchronisation.  Two publications may be under way, into buffers of their own.  hipStreamQuery bounds the wait; should the stream drain without
 // the number showing, the records are read through a copy instead.
 hipError_t Engine::wait_publication(const Publish& pub) {
   const size_t lo = pub.d - d_scal_;
   for (unsigned spin = 1;; ++spin) {
-    if (__atomic_load_n(h_pub_flag_, __ATOMIC_ACQUIRE) == pub.seq) break;
+    if ((int)(__atomic_load_n(h_pub_flag_, __ATOMIC_ACQUIRE) - pub.seq) >= 0) break;
     if ((spin & 255) == 0) {
       const hipError_t q = hipStreamQuery(st_);
       if (q == hipErrorNotReady) continue;
       if (q != hipSuccess) return q;
-      if (__atomic_load_n(h_pub_flag_, __ATOMIC_ACQUIRE) == pub.seq) break;
+      if ((int)(__atomic_load_n(h_pub_flag_, __ATOMIC_ACQUIRE) - pub.seq) >= 0) break;
       HUB_TRY(hipMemcpyAsync(h_scal_ + lo, pub.d, sizeof(Scal) * pub.cnt, hipMemcpyDeviceToHost, st_));
       return hipStreamSynchronize(st_);
     }
@@ -562,6 +562,34 @@ void Engine::finish(System* s, hub_status st) {
   s->phase = PH_DONE;
   s->done = true;
   s->info.converged = st == HUB_OK ? 1 : 0;
+}
+
+// No further Arnoldi step of this cycle.
+static bool cycle_ends(const System* s) {
+  return s->err < s->opts.tol * s->bnorm || s->wnorm == 0.0 || !std::isfinite(s->wnorm);
+}
+
+// Arnoldi step j of the systems v; `pub` is published at its end.  w stays in its slot after
+// an inner solve (v_j holds the old one) and changes slots in a step that reads the old w at
+// the neighbours.
+hipError_t Engine::launch_arnoldi(const std::vector<System*>& v, int j, Publish& pub) {
+  for (bool plain : {false, true}) {
+    std::vector<System*> u;
+    for (System* s : v)
+      if (s->plain == plain) u.push_back(s);
+    if (u.empty()) continue;
+    LaunchList L = list(u);
+    for (size_t q = 0; q < u.size(); ++q) {
+      if (plain) u[q]->wslot = S_R + S_U - u[q]->wslot;
+      L.it[q] = u[q]->wslot;
+      L.pa[q] = 1.0 / u[q]->wnorm;
+    }
+    HUB_TRY(launch_arnoldi_dots(d_desc_, L, j, plain, st_));
+  }
+  LaunchList L = list(v);
+  for (size_t q = 0; q < v.size(); ++q) L.it[q] = v[q]->wslot;
+  pub = publication(v);
+  return launch_cgs(d_desc_, L, j, pub, st_);
 }
 
 // One host-side transition for a group of systems at the same phase (and, in
@@ -689,6 +717,7 @@ hipError_t Engine::group_phase(int phase, const std::vector<System*>& g) {
         }
         s->j = 0;
         s->wslot = S_R;
+        s->rate = 1.0;
         s->wnorm = s->err;
         s->rnorm_cycle = s->err;
         s->H.assign((size_t)(o.restart_m + 1) * o.restart_m, std::complex<double>(0.0));
@@ -700,7 +729,7 @@ hipError_t Engine::group_phase(int phase, const std::vector<System*>& g) {
       // v_j = w / |w|; z_j from the single-precision CG when TOL a |b| / ERR < 1, else z_j = v_j
       std::vector<System*> act;
       for (System* s : g) {
-        if (s->err < s->opts.tol * s->bnorm || s->wnorm == 0.0 || !std::isfinite(s->wnorm))
+        if (cycle_ends(s))
           s->phase = PH_F_LSQ;
         else
           act.push_back(s);
@@ -738,45 +767,45 @@ hipError_t Engine::group_phase(int phase, const std::vector<System*>& g) {
     }
     case PH_F_POST_ARNOLDI: {
       // w = A z_j, classical Gram-Schmidt against v_0 .. v_j, h_{j+1,j} = |w|, ERR *= |w|.
-      // w stays in its slot after an inner solve (v_j holds the old one) and changes slots
-      // in a step that reads the old w at the neighbours.
-      for (bool plain : {false, true}) {
-        std::vector<System*> v;
-        for (System* s : g)
-          if (s->plain == plain) v.push_back(s);
-        if (v.empty()) continue;
-        LaunchList L = list(v);
-        for (size_t q = 0; q < v.size(); ++q) {
-          if (plain) v[q]->wslot = S_R + S_U - v[q]->wslot;
-          L.it[q] = v[q]->wslot;
-          L.pa[q] = 1.0 / v[q]->wnorm;
+      // Steps without an inner solve follow each other on the device: the next one is
+      // enqueued before the host has this one's result.  It is in vain when this one
+      // converges (its vectors lie past those that the update reads), so it is not enqueued
+      // where the last reduction of ERR suggests that.  (25x23x30 1356 -> 1301 us, a
+      // Hasenbusch force at 24x24x64 7.08 -> 6.84 ms.)
+      std::vector<System*> v = g;
+      Publish pub, next;
+      HUB_TRY(launch_arnoldi(v, j, pub));
+      for (int i = j;; ++i) {
+        bool ahead = i + 1 < v.front()->opts.restart_m;
+        for (System* s : v)
+          ahead = ahead && s->plain && i + 1 < s->opts.restart_m && s->err * s->rate >= s->opts.tol * s->bnorm;
+        if (ahead) HUB_TRY(launch_arnoldi(v, i + 1, next));
+        HUB_TRY(wait_publication(pub));
+        std::vector<System*> on;
+        for (System* s : v) {
+          const int m = s->opts.restart_m;
+          s->info.applies++;
+          const Scal& sc = h_scal_[s->slot];
+          for (int k = 0; k <= i; ++k) s->H[(size_t)i * (m + 1) + k] = {sc.red[2 * k], sc.red[2 * k + 1]};
+          const double hn = std::sqrt(std::max(sc.red[2 * (i + 1)], 0.0));
+          s->H[(size_t)i * (m + 1) + i + 1] = hn;
+          s->wnorm = hn;
+          // ERR: the residual of the best iterate of the cycle so far, the least-squares
+          // residual of the Arnoldi relation (Algorithm A.1's ERR * |w| is this quantity
+          // while every step's inner solve meets its tolerance, and not after an
+          // unpreconditioned step, where it ends cycles that have not converged)
+          double res = s->err;
+          (void)hessenberg_lsq(s->H, m + 1, i + 1, s->rnorm_cycle, &res);
+          s->rate = s->plain && s->err > 0.0 ? res / s->err : 1.0;
+          s->err = res;
+          s->j = i + 1;
+          s->phase = (s->j == m) ? PH_F_LSQ : PH_F_ARNOLDI;
+          if (ahead && !cycle_ends(s)) on.push_back(s);
         }
-        HUB_TRY(launch_arnoldi_dots(d_desc_, L, j, plain, st_));
+        if (on.empty()) return hipSuccess;
+        v = on;
+        pub = next;
       }
-      LaunchList L = list(g);
-      for (size_t q = 0; q < g.size(); ++q) L.it[q] = g[q]->wslot;
-      const Publish pub = publication(g);
-      HUB_TRY(launch_cgs(d_desc_, L, j, pub, st_));
-      HUB_TRY(wait_publication(pub));
-      for (System* s : g) {
-        const int m = s->opts.restart_m;
-        s->info.applies++;
-        const Scal& sc = h_scal_[s->slot];
-        for (int i = 0; i <= j; ++i) s->H[(size_t)j * (m + 1) + i] = {sc.red[2 * i], sc.red[2 * i + 1]};
-        const double hn = std::sqrt(std::max(sc.red[2 * (j + 1)], 0.0));
-        s->H[(size_t)j * (m + 1) + j + 1] = hn;
-        s->wnorm = hn;
-        // ERR: the residual of the best iterate of the cycle so far, the least-squares
-        // residual of the Arnoldi relation (Algorithm A.1's ERR * |w| is this quantity
-        // while every step's inner solve meets its tolerance, and not after an
-        // unpreconditioned step, where it ends cycles that have not converged)
-        double res = s->err;
-        (void)hessenberg_lsq(s->H, m + 1, j + 1, s->rnorm_cycle, &res);
-        s->err = res;
-        s->j = j + 1;
-        s->phase = (s->j == m) ? PH_F_LSQ : PH_F_ARNOLDI;
-      }
-      return hipSuccess;
     }
     case PH_F_LSQ: {
       // y = argmin |(|r|, 0, ..) - H y|, x += sum y_i z_i, true residual, restart or stop
@@ -804,6 +833,7 @@ hipError_t Engine::group_phase(int phase, const std::vector<System*>& g) {
         } else {
           s->j = 0;
           s->wslot = S_R;
+          s->rate = 1.0;
           s->wnorm = s->err;
           s->rnorm_cycle = s->err;
           std::fill(s->H.begin(), s->H.end(), std::complex<double>(0.0));

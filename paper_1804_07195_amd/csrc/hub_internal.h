@@ -384,8 +384,9 @@ hipError_t launch_normal_slot(const SysDesc* sys, const LaunchList& L, int s_in,
 hipError_t launch_cg_init_zero(const SysDesc* sys, const LaunchList& L, RedMode mode, const Publish& pub,
                                hipStream_t st);
 // First half of Arnoldi step j: w = A z_j into the slot it[], red[2i], red[2i+1] = <v_i, w>,
-// i <= j.  from_w: the step has no inner solve, and z_j = c64(v_j), v_j = pa * w_old with
-// w_old the other of the slots S_R and S_U; both are stored here too.
+// i <= j.  from_w: the step has no inner solve, and z_j = c64(v_j), v_j = w_old / |w_old| with
+// w_old the other of the slots S_R and S_U; both are stored here too.  The inverse norm is
+// pa for j = 0, else it comes from step j - 1's |w|^2 in red[2j] (the host may not know it).
 hipError_t launch_arnoldi_dots(const SysDesc* sys, const LaunchList& L, int j, bool from_w, hipStream_t st);
 // Second half: w -= sum_i h_i v_i, i <= j, h_i = red[2i], red[2i+1]; |w|^2 -> red[2j+2].
 hipError_t launch_cgs(const SysDesc* sys, const LaunchList& L, int j, const Publish& pub, hipStream_t st);

@@ -1755,7 +1755,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_init_zero(const SysDesc* __restri
 
 // First half of an Arnoldi step: w = A z_j (FP64, the 12-point form) and <v_i, w> = sum
 // conj(v_i) w for i <= j, each thread's w fresh in its caches when the basis passes by.  FROM_W: a step
-// without an inner solve, where z_j = c64(pa w_old) is evaluated at the twelve neighbours
+// without an inner solve, where z_j = c64(w_old / |w_old|) is evaluated at the twelve neighbours
 // too, so that neither v_j nor z_j has to be there before the launch; w_old and w are in
 // different slots.  Each wave sums its two values per i by data-parallel primitives; the
 // waves meet once at the end.  With k_cgs this is a step without an inner solve in two
@@ -1765,12 +1765,11 @@ template <int SPT, bool FROM_W>
 __global__ __launch_bounds__(kBlock) void k_arnoldi_dots(const SysDesc* __restrict__ sys, LaunchList L, int j) {
   constexpr int TILE = kBlock * SPT;
   HUB_PROLOGUE_T(TILE)
-  (void)sc;
   const int s_w = L.it[kk];
   const Vec<double2> w(d->vec[s_w]), old(d->vec[S_R + S_U - s_w]), vj(d->vec[S_V0 + j]);
   const Vec<float2> z(d->vec[S_Z0 + j]);
   const PhasePhi<double> ph = phase_of<double>(d);
-  const double mu2 = d->mu2, scale = L.pa[kk];
+  const double mu2 = d->mu2, scale = !FROM_W || j == 0 ? L.pa[kk] : 1.0 / sqrt(fmax(sc->red[2 * j], 0.0));
   auto scaled = [=](int k) {
     double2 a = old[k];
     a.x *= scale;
