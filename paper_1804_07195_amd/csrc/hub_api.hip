@@ -433,13 +433,10 @@ hub_status hub_apply_normal(hub_ctx* ctx, const hub_lattice* lat, const double* 
   }
   HUB_HIP(hipSetDevice(ctx->device), "hipSetDevice");
   const Geom g = make_geom(*lat);
-  // two passes, u = M^dagger x then y = M u + mu2 x: faster here than the one-pass
-  // 12-point form, whose extra neighbour loads cost more than the bytes it saves
-  double2* u = (double2*)ctx->pool->alloc((size_t)batch * g.n * 16, stream);
-  if (!u) return fail(HUB_ERR_OOM, "workspace for M^dagger x");
-  hipError_t e = launch_apply(g, phi, (const double2*)x, u, batch, true, stream);
-  if (e == hipSuccess) e = launch_normal2(g, phi, m2, u, (const double2*)x, (double2*)y, batch, stream);
-  ctx->pool->release(u, stream);
+  double2* ph64 = (double2*)ctx->pool->alloc((size_t)g.n * 16, stream);
+  if (!ph64) return fail(HUB_ERR_OOM, "workspace for the phase of phi");
+  const hipError_t e = launch_normal(g, phi, ph64, m2, (const double2*)x, (double2*)y, batch, stream);
+  ctx->pool->release(ph64, stream);
   if (e != hipSuccess) return hip_fail(e, "normal operator launch");
   return HUB_OK;
 }
@@ -465,11 +462,9 @@ hub_status hub_apply_normal_noalloc(hub_ctx* ctx, const hub_lattice* lat, const 
   }
   if (!ctx->scratch) return fail(HUB_ERR_HIP, "no scratch address for this device");
   HUB_HIP(hipSetDevice(ctx->device), "hipSetDevice");
-  // u = M^dagger x into the scratch (every entry written before it is read), then
-  // y = M u + mu2 x: the kernels of hub_apply_normal
-  double2* u = (double2*)ctx->scratch;
-  hipError_t e = launch_apply(g, phi, (const double2*)x, u, batch, true, stream);
-  if (e == hipSuccess) e = launch_normal2(g, phi, m2, u, (const double2*)x, (double2*)y, batch, stream);
+  // the phases into the scratch (every entry written before it is read), then the kernels of
+  // hub_apply_normal
+  const hipError_t e = launch_normal(g, phi, (double2*)ctx->scratch, m2, (const double2*)x, (double2*)y, batch, stream);
   if (e != hipSuccess) return hip_fail(e, "normal operator launch");
   return HUB_OK;
 }

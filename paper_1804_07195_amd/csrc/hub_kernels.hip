@@ -602,72 +602,59 @@ __global__ __launch_bounds__(kBlock) void k_apply_grp(Geom g, const double* __re
 
 struct Mu2Arr { double v[kMaxSys]; };
 
-// y_b = M u_b + mu2_b x_b: the second pass of the public normal operator (u = M^dagger x),
-// one vector per workgroup.
-__global__ __launch_bounds__(kBlock) void k_normal2_pub(Geom g, const double* __restrict__ phi, Mu2Arr mu2,
-                                                        const double2* __restrict__ u,
-                                                        const double2* __restrict__ x, double2* __restrict__ y,
-                                                        int ntiles) {
-  const int l = xcd_remap(blockIdx.x, gridDim.x);
-  const int b = l / ntiles, tile = l - b * ntiles;
-  const size_t off = (size_t)b * g.n;
-  const double m2 = mu2.v[b];
-  const int base = tile * kPubTile + threadIdx.x;
-  auto ld = [=](int k) { return u[off + k]; };
-  auto pre = [=](int n) { return x[off + n]; };
-  auto post = [=](int n, double2 q, double2, double2 xv) {
-    q.x += m2 * xv.x;
-    q.y += m2 * xv.y;
-    y[off + n] = q;
-  };
-  stencil_sites<double, false, kPubSites, kPubSites>(g, AnglePhi<double>(phi), base, g.n, ld, Same{}, pre, NoMid{},
-                                                     post);
-}
-
-// The same for a group of `per` vectors per workgroup.
-__global__ __launch_bounds__(kBlock) void k_normal2_grp(Geom g, const double* __restrict__ phi, Mu2Arr mu2,
-                                                        const double2* __restrict__ u,
-                                                        const double2* __restrict__ x, double2* __restrict__ y,
-                                                        int ntiles, int per, int batch) {
+// The public normal operator on a batch that shares phi: y_b = (M M^dagger + mu2_b) x_b for a
+// group of `per` vectors per workgroup, in one pass after k_phase_pub.  A site's thread
+// evaluates u = M^dagger x at the five sites that M reads, from 15 values of x (the
+// cancelled 12-point form reads 12 but rounds worse: 1.5e-16 against 0.9e-16 of |y|).  That
+// reads x and writes y, where a pass for u and one for y also write u, read it back, read x
+// again and evaluate each phase twice; the neighbours come from the caches.  Two vectors at
+// 102x102x64: 47.6 -> 38.8 us (31 and 7.5 us in the two kernels; 96 MB moved, and the L1
+// loads of the neighbours, 35 of 16 bytes per site, take 19 us of the 31 by themselves).
+__global__ __launch_bounds__(kBlock) void k_normal_pub(Geom g, const double2* __restrict__ ph64, Mu2Arr mu2,
+                                                       const double2* __restrict__ x, double2* __restrict__ y,
+                                                       int ntiles, int per, int batch) {
   const int l = xcd_remap(blockIdx.x, gridDim.x);
   const int grp = l / ntiles, tile = l - grp * ntiles;
-  const int b0 = grp * per, b1 = min(batch, b0 + per);
-  const int base = tile * kPubTile + threadIdx.x;
-  SiteIdx st[kPubSites];
-  bool ok[kPubSites];
-  double ph[kPubSites], c[kPubSites], s[kPubSites];
-#pragma unroll
-  for (int m = 0; m < kPubSites; ++m) {
-    int n = base + m * kBlock;
-    ok[m] = n < g.n;
-    n = ok[m] ? n : g.n - 1;
-    st[m] = site_index<false>(g, n);
-    ph[m] = phi[st[m].pn];
-  }
-  for (int b = b0; b < b1; ++b) {
-    const size_t off = (size_t)b * g.n;
-    const double m2 = mu2.v[b];
-    double2 us[kPubSites], ut[kPubSites], u0[kPubSites], u1[kPubSites], u2[kPubSites], xv[kPubSites];
-#pragma unroll
-    for (int m = 0; m < kPubSites; ++m) {
-      us[m] = u[off + st[m].n];
-      ut[m] = u[off + st[m].tn];
-      u0[m] = u[off + st[m].h0];
-      u1[m] = u[off + st[m].h1];
-      u2[m] = u[off + st[m].h2];
-      xv[m] = x[off + st[m].n];
-    }
-    if (b == b0) {
-#pragma unroll
-      for (int m = 0; m < kPubSites; ++m) cis64(ph[m], c[m], s[m]);
-    }
-#pragma unroll
-    for (int m = 0; m < kPubSites; ++m) {
-      double2 q = stencil_combine<double, false>(g, st[m], c[m], s[m], us[m], ut[m], u0[m], u1[m], u2[m]);
-      q.x += m2 * xv[m].x;
-      q.y += m2 * xv[m].y;
-      if (ok[m]) y[off + st[m].n] = q;
-    }
+  const int v0 = grp * per, v1 = min(batch, v0 + per);
+  const int n = tile * kBlock + threadIdx.x;
+  if (n >= g.n) return;
+  const uint32_t q1 = fdiv((uint32_t)n, g.dL2), q2 = fdiv(q1, g.dL1);
+  const int j = n - (int)q1 * g.L2, i = (int)q1 - (int)q2 * g.L1, t = (int)(q2 >> 1), L2 = g.L2, P = g.P;
+  const bool isA = (q2 & 1u) == 0;
+  const bool first = t == 0, last = t == g.Nt - 1;
+  const int tp = last ? 0 : t + 1, tm = first ? g.Nt - 1 : t - 1;
+  const int ip = i + 1 == g.L1 ? 0 : i + 1, im = i == 0 ? g.L1 - 1 : i - 1;
+  const int jp = j + 1 == L2 ? 0 : j + 1, jm = j == 0 ? L2 - 1 : j - 1;
+  // bonds go to (i, j), (i1, j), (i, j1) of the other sublattice and back to (i, j), (i0, j),
+  // (i, j0); M reads slice tb of the own sublattice, M^dagger slice tf
+  const int i1 = isA ? im : ip, i0 = isA ? ip : im, j1 = isA ? jm : jp, j0 = isA ? jp : jm;
+  const int tb = isA ? tm : tp, tf = isA ? tp : tm;
+  const int c = i * L2 + j, c1 = i1 * L2 + j, c2 = i * L2 + j1;
+  const int own = n - c, ownb = (2 * tb + (isA ? 0 : 1)) * P, ownf = (2 * tf + (isA ? 0 : 1)) * P;
+  const int opp = isA ? own + P : own - P, oppb = isA ? ownb + P : ownb - P;
+  SiteIdx f, b, o;  // u(t) and u(tb) of the own sublattice, u(t) of the other
+  f.isA = b.isA = isA;
+  o.isA = !isA;
+  f.wrap = isA ? last : first;
+  b.wrap = o.wrap = isA ? first : last;
+  const Vec<double2> ph(ph64);
+  const double2 e = ph[n], ef = ph[ownf + c], e0 = ph[oppb + c], e1 = ph[oppb + c1], e2 = ph[oppb + c2];
+  for (int v = v0; v < v1; ++v) {
+    const Vec<double2> xv(x + (size_t)v * g.n);
+    const double2 xs = xv[n], xf = xv[ownf + c], xb = xv[ownb + c];
+    const double2 p0 = xv[opp + c], p1 = xv[opp + c1], p2 = xv[opp + c2];
+    const double2 r0 = xv[oppb + c], r1 = xv[oppb + c1], r2 = xv[oppb + c2];
+    const double2 s1 = xv[own + i0 * L2 + j], s2 = xv[own + i * L2 + j0], s3 = xv[own + c1], s4 = xv[own + i1 * L2 + j0],
+                  s5 = xv[own + c2], s6 = xv[own + i0 * L2 + j1];
+    const double2 uf = stencil_combine<double, true>(g, f, ef.x, ef.y, xs, xf, p0, p1, p2);
+    const double2 ub = stencil_combine<double, true>(g, b, e.x, e.y, xb, xs, r0, r1, r2);
+    const double2 u0 = stencil_combine<double, true>(g, o, e0.x, e0.y, p0, r0, xs, s1, s2);
+    const double2 u1 = stencil_combine<double, true>(g, o, e1.x, e1.y, p1, r1, s3, xs, s4);
+    const double2 u2 = stencil_combine<double, true>(g, o, e2.x, e2.y, p2, r2, s5, s6, xs);
+    double2 q = stencil_combine<double, false>(g, b, e.x, e.y, uf, ub, u0, u1, u2);
+    q.x += mu2.v[v] * xs.x;
+    q.y += mu2.v[v] * xs.y;
+    store_out<true>(y + (size_t)v * g.n + n, q);
   }
 }
 
@@ -981,6 +968,16 @@ __global__ __launch_bounds__(kBlock) void k_phase(const double* __restrict__ phi
                                                   float* __restrict__ p32, int n) {
   const int i = blockIdx.x * kBlock + threadIdx.x;
   if (i < n) phase_site(phi, p64, p32, i);
+}
+
+// The phase as the public operators evaluate it.
+__global__ __launch_bounds__(kBlock) void k_phase_pub(const double* __restrict__ phi, double2* __restrict__ p64,
+                                                      int n) {
+  const int i = blockIdx.x * kBlock + threadIdx.x;
+  if (i >= n) return;
+  double2 v;
+  cis64(phi[i], v.x, v.y);
+  p64[i] = v;
 }
 
 // The same for the fields of a batch, one field per grid row.
@@ -2086,20 +2083,17 @@ hipError_t launch_ms_iter(const MsDesc* d, int ntiles, int it, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_normal2(const Geom& g, const double* phi, const double mu2_host[kMaxSys], const double2* u,
-                          const double2* x, double2* y, int batch, hipStream_t st) {
-  const int nt = (g.n + kPubTile - 1) / kPubTile;
+hipError_t launch_normal(const Geom& g, const double* phi, double2* ph64, const double mu2_host[kMaxSys],
+                         const double2* x, double2* y, int batch, hipStream_t st) {
+  const int nt = (g.n + kBlock - 1) / kBlock;
+  hipLaunchKernelGGL(k_phase_pub, dim3(nt), dim3(kBlock), 0, st, phi, ph64, g.n);
   const int per = pub_group(nt, batch);
   Mu2Arr m;
   for (int b = 0; b < kMaxSys; ++b) m.v[b] = b < batch ? mu2_host[b] : 0.0;
-  const dim3 grid(nt * ((batch + per - 1) / per)), block(kBlock);
-  if (per == 1)
-    hipLaunchKernelGGL(k_normal2_pub, grid, block, 0, st, g, phi, m, u, x, y, nt);
-  else
-    hipLaunchKernelGGL(k_normal2_grp, grid, block, 0, st, g, phi, m, u, x, y, nt, per, batch);
+  hipLaunchKernelGGL(k_normal_pub, dim3(nt * ((batch + per - 1) / per)), dim3(kBlock), 0, st, g, ph64, m, x, y, nt, per,
+                     batch);
   return hipGetLastError();
 }
-
 
 hipError_t launch_phase(const double* phi, double2* p64, float* p32, int n, hipStream_t st) {
   hipLaunchKernelGGL(k_phase, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, st, phi, p64, p32, n);
