@@ -245,6 +245,14 @@ inline GangBlock gang_largest(int L1, int L2, int Nt, int gt, int gi, int gj) {
 // that stands for sites a thread does not have (every neighbour it reads is zero too).
 __host__ __device__ inline int gang_zero(const GangBlock& B) { return gang_entries(B) + B.TS; }
 __host__ __device__ inline int gang_table(const GangBlock& B) { return gang_entries(B) + 2 * B.TS + 1; }
+// A system of one workgroup in which two field tables fit in front of the links (its body is
+// one of the first three classes): the second lies kGangSecond bytes behind the first.
+constexpr int kGangSecond = kGangLinks / 2;
+template <typename R>
+__host__ __device__ inline bool gang_solo(const GangCut& c, int L1, int L2, int Nt) {
+  const size_t entries = (size_t)L1 * L2 * 2 * (Nt + 2) + 2 * (Nt + 2) + 1;
+  return c.g == 1 && c.cls <= 2 && entries * 2 * sizeof(R) <= (size_t)kGangSecond;
+}
 // The first class that holds a block, or -1.
 template <typename R>
 inline int gang_class(const GangBlock& B) {
@@ -271,14 +279,16 @@ __host__ __device__ inline size_t gang_state_words(int g, int cls) {
 }
 
 // Time of one CG iteration of a cut in microseconds, fitted to measurements (complex64 /
-// complex128; one workgroup 1.8 / 2.5 at 6x6x16; 12x12x32 3.25 / 4.7 with 8 workgroups and
-// 2.95 / 3.6 with 16; 24x24x64 3.5 / 5.0 with 64; 48x48x64 4.8 with 128, 4.2 / 6.2 with 256;
-// 102x102x64 8.9 with 256): the arithmetic of the largest block, and with more than one
-// workgroup a reduction and an exchange of faces.
+// complex128; one workgroup 0.95 to 1.3 with one site per thread, 1.5 / 2.2 at 6x6x16;
+// 12x12x32 3.25 / 4.7 with 8 workgroups and 2.95 / 3.6 with 16; 24x24x64 3.5 / 5.0 with 64;
+// 48x48x64 4.8 with 128, 4.2 / 6.2 with 256; 102x102x64 8.9 with 256; several workgroups
+// have become 0.1 to 0.3 faster since): the arithmetic of the largest block, and with more
+// than one workgroup a reduction and an exchange of faces.
 template <typename R>
 inline double gang_cost(const GangBlock& B, int cls, int g) {
   constexpr bool single = sizeof(R) == 4;
   const int M = GangTab<R>::c[cls].M;
+  if (g == 1 && cls <= 2) return single ? 0.68 + 0.27 * M : 0.7 + 0.48 * M;
   if (g == 1) return 0.9 + (single ? (M > 6 ? 0.4 : 0.32) : 0.55) * M;
   double l = 0.0;
   for (int k = 2; k <= g; k *= 2) l += 1.0;

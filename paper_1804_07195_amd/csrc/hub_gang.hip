@@ -234,7 +234,12 @@ __device__ __forceinline__ double from_lane(double v, int lane) {
   return __longlong_as_double((long long)((u64)hi << 32 | lo));
 }
 
-template <typename R, int CLS>
+// SOLO: a system of one workgroup whose two field tables fit: nothing is exchanged, and r and
+// M^dagger r do not share a place, so that an iteration has two barriers instead of four and
+// no wave waits for another one's sum (2x1x64 FP64 1.37 -> 0.99 us, 6x6x16 1.75 -> 1.48 us;
+// bound by the latency of the two barriers, the LDS and the scalars' divisions).  With more
+// workgroups a second table is slower: a record is then stored behind the faces.
+template <typename R, int CLS, bool SOLO>
 __device__ __forceinline__ void gang_run(const SysDesc* __restrict__ d, Scal* sc, const int wg, const int zslot,
                                          const unsigned tag0, const unsigned seq, const unsigned arrived, const int K,
                                          char* const lds) {
@@ -258,7 +263,7 @@ __device__ __forceinline__ void gang_run(const SysDesc* __restrict__ d, Scal* sc
   int &sh_off = flag[0], &sh_bad = flag[1];
   static_assert((kGangWaves + kGangMaxWgs / 64) * 16 + 8 <= kGangHead, "head of the LDS");
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int g = d->gang.g, nslot = d->gang.nslot;
+  const int g = SOLO ? 1 : d->gang.g, nslot = SOLO ? 0 : d->gang.nslot;
   if (tid == 0) sh_bad = 0;
   const GangBlock B = gang_block(d->g.L1, d->g.L2, d->g.Nt, d->gang.gt, d->gang.gi, d->gang.gj, wg);
   const int it0 = sc->git;
@@ -447,6 +452,8 @@ __device__ __forceinline__ void gang_run(const SysDesc* __restrict__ d, Scal* sc
   const R rmu2 = (R)mu2;
   const R ks = sub ? -(R)d->g.kappa : (R)d->g.kappa;
   const int dt1 = sub ? -SZ : SZ;  // M^dagger reads t + 1 on A, t - 1 on B; M the other way
+  if (SOLO)
+    for (int q = gang_entries(B) + tid; q < gang_table(B); q += kGangThreads) F[kGangSecond / SZ + q] = cz<C>();
   if (g > 1) {
     if (tid == 0) sh_off = gang_meet((unsigned*)d->gang_mem, g, seq, arrived);
     __syncthreads();
@@ -546,11 +553,11 @@ __device__ __forceinline__ void gang_run(const SysDesc* __restrict__ d, Scal* sc
       if (dst >> 19 & 1) at(a - wrap) = v;
     }
   };
-  auto put_own = [&](const C* v, int o) {
-    gang_chunks<M, CH>(B.half, [&](int m) { at(a0[m]) = v[m]; });
-    if (B.gt == 1) {
+  auto put_own = [&](const C* v, int o, int behind = 0) {
+    gang_chunks<M, CH>(B.half, [&](int m) { at(a0[m] + behind) = v[m]; });
+    if (SOLO || B.gt == 1) {
       const unsigned en = ends + (unsigned)o;
-      const int up = o + wrap, down = o - wrap;
+      const int up = o + wrap + behind, down = o - wrap + behind;
       gang_chunks<M, CH>(B.half, [&](int m) {
         if (en >> m & 1) at(a0[m] + up) = v[m];
         if (en >> (M + m) & 1) at(a0[m] + down) = v[m];
@@ -569,8 +576,9 @@ __device__ __forceinline__ void gang_run(const SysDesc* __restrict__ d, Scal* sc
   // The two outer bonds of a site (o is zero, see the iteration loop).
   auto low = [&](int b1) -> C { return at(b1 << 3 & 0x7fff8); };
   auto high = [&](int b1) -> C { return at((int)((unsigned)b1 >> 13 & 0x7fff8)); };
-  auto bond1 = [&](int b1, int o) -> C { return PACK ? low(b1 + o) : at(b1); };
-  auto bond2 = [&](int b1, int b2, int o) -> C { return PACK ? high(b1 + o) : at(b2); };
+  static_assert(!(SOLO && (PACK || ZMEM)), "small bodies");
+  auto bond1 = [&](int b1, int o, int behind = 0) -> C { return PACK ? low(b1 + o) : at(b1 + behind); };
+  auto bond2 = [&](int b1, int b2, int o, int behind = 0) -> C { return PACK ? high(b1 + o) : at(b2 + behind); };
 
   // r and s of the halo: sent once per launch, then carried along with the owner's own
   // arithmetic, so that the faces of w can travel while the reduction does.
@@ -595,8 +603,67 @@ __device__ __forceinline__ void gang_run(const SysDesc* __restrict__ d, Scal* sc
   int it = it0;
   bool stopped = false;
   double gamma = 0.0;
+  if constexpr (SOLO) {
+    // waves without a site only take part in the barriers and the stopping test
+    const bool any = __builtin_amdgcn_readfirstlane(k0) < B.half;
+    constexpr int D = kGangSecond;
 #pragma unroll 1
-  for (int step = 0; step < K; ++step, ++it) {
+    for (int step = 0; step < K; ++step, ++it) {
+      C v[M];
+      R acc_g = 0, acc_u = 0;
+      if (any) {
+        gang_chunks<M, CH>(B.half, [&](int m) {
+          v[m] = half_op(link(a0[m] + dt1), std::true_type{}, at(a0[m] + dt1), at(a0[m] + dh), bond1(h1[m], 0),
+                         bond2(h1[m], h2[m], 0), ks, r[m]);
+          acc_g = fma(r[m].x, r[m].x, fma(r[m].y, r[m].y, acc_g));
+          acc_u = fma(v[m].x, v[m].x, fma(v[m].y, v[m].y, acc_u));
+        });
+        put_own(v, 0, D);
+        acc_g = dpp_wave(acc_g);
+        acc_u = dpp_wave(acc_u);
+      }
+      if (lane == 63) red[wave] = double2{(double)acc_g, (double)acc_u};
+      __syncthreads();
+      // every wave sums the waves' shares, in one order
+      double2 q[kGangWaves];
+#pragma unroll
+      for (int k = 0; k < kGangWaves; ++k) q[k] = red[k];
+#pragma unroll
+      for (int n = kGangWaves / 2; n > 0; n /= 2)
+#pragma unroll
+        for (int k = 0; k < n; ++k) q[k].x += q[k + n].x, q[k].y += q[k + n].y;
+      gamma = q[0].x;
+      if (it > 0 && (!(gamma > stop2) || it >= maxit)) {
+        stopped = true;
+        break;
+      }
+      const double beta = it == 0 ? 0.0 : gamma / gamma_prev;
+      const double alpha = gamma / (q[0].y + mu2 * gamma - (it == 0 ? 0.0 : beta * gamma / alpha_prev));
+      const R rb = (R)beta, ra = (R)alpha;
+      if (any) {
+        gang_chunks<M, CH>(B.half, [&](int m) {
+          C w = half_op(link(a0[m]), std::false_type{}, at(a0[m] + D - dt1), at(a0[m] + D + dh), bond1(h1[m], 0, D),
+                        bond2(h1[m], h2[m], 0, D), -ks, v[m]);
+          w.x = fma(rmu2, r[m].x, w.x);
+          w.y = fma(rmu2, r[m].y, w.y);
+          s[m].x = fma(rb, s[m].x, w.x);
+          s[m].y = fma(rb, s[m].y, w.y);
+          p[m].x = fma(rb, p[m].x, r[m].x);
+          p[m].y = fma(rb, p[m].y, r[m].y);
+          r[m].x = fma(-ra, s[m].x, r[m].x);
+          r[m].y = fma(-ra, s[m].y, r[m].y);
+          z[m].x = fma(ra, p[m].x, z[m].x);
+          z[m].y = fma(ra, p[m].y, z[m].y);
+        });
+        put_own(r, 0);
+      }
+      __syncthreads();
+      gamma_prev = gamma;
+      alpha_prev = alpha;
+    }
+  }
+#pragma unroll 1
+  for (int step = 0; !SOLO && step < K; ++step, ++it) {
     const unsigned tag = tag0 + (unsigned)step + 3;
     // A zero in every offset, which the compiler cannot see through: it would work out the
     // address of every neighbour of every site once for all iterations (or, with one zero
@@ -736,14 +803,23 @@ __global__ __launch_bounds__(kGangThreads) void k_gang(const SysDesc* __restrict
   if (load_active(sc) != 1) return;
   static_assert(GangTab<float>::n == 7 && GangTab<double>::n == 4, "the cases below");
   constexpr int last = GangTab<R>::n - 1;
+  const int zslot = L.pi[kk];
+  const unsigned tag = L.tag[kk], seq = L.seq[kk];
+  if (gang_solo<R>(d->gang, d->g.L1, d->g.L2, d->g.Nt)) {
+    switch (d->gang.cls) {
+      case 0: return gang_run<R, 0, true>(d, sc, wg, zslot, tag, seq, arrived, K, gang_mem_lds);
+      case 1: return gang_run<R, 1, true>(d, sc, wg, zslot, tag, seq, arrived, K, gang_mem_lds);
+      default: return gang_run<R, 2, true>(d, sc, wg, zslot, tag, seq, arrived, K, gang_mem_lds);
+    }
+  }
   switch (d->gang.cls) {
-    case 0: return gang_run<R, 0>(d, sc, wg, L.pi[kk], L.tag[kk], L.seq[kk], arrived, K, gang_mem_lds);
-    case 1: return gang_run<R, 1>(d, sc, wg, L.pi[kk], L.tag[kk], L.seq[kk], arrived, K, gang_mem_lds);
-    case 2: return gang_run<R, 2>(d, sc, wg, L.pi[kk], L.tag[kk], L.seq[kk], arrived, K, gang_mem_lds);
-    case 3: return gang_run<R, 3>(d, sc, wg, L.pi[kk], L.tag[kk], L.seq[kk], arrived, K, gang_mem_lds);
-    case 4: return gang_run<R, last < 4 ? last : 4>(d, sc, wg, L.pi[kk], L.tag[kk], L.seq[kk], arrived, K, gang_mem_lds);
-    case 5: return gang_run<R, last < 5 ? last : 5>(d, sc, wg, L.pi[kk], L.tag[kk], L.seq[kk], arrived, K, gang_mem_lds);
-    default: return gang_run<R, last>(d, sc, wg, L.pi[kk], L.tag[kk], L.seq[kk], arrived, K, gang_mem_lds);
+    case 0: return gang_run<R, 0, false>(d, sc, wg, zslot, tag, seq, arrived, K, gang_mem_lds);
+    case 1: return gang_run<R, 1, false>(d, sc, wg, zslot, tag, seq, arrived, K, gang_mem_lds);
+    case 2: return gang_run<R, 2, false>(d, sc, wg, zslot, tag, seq, arrived, K, gang_mem_lds);
+    case 3: return gang_run<R, 3, false>(d, sc, wg, zslot, tag, seq, arrived, K, gang_mem_lds);
+    case 4: return gang_run<R, last < 4 ? last : 4, false>(d, sc, wg, zslot, tag, seq, arrived, K, gang_mem_lds);
+    case 5: return gang_run<R, last < 5 ? last : 5, false>(d, sc, wg, zslot, tag, seq, arrived, K, gang_mem_lds);
+    default: return gang_run<R, last, false>(d, sc, wg, zslot, tag, seq, arrived, K, gang_mem_lds);
   }
 }
 
