@@ -197,7 +197,6 @@ class Engine {
   void upload_y(System* s, const std::vector<std::complex<double>>& y);
   hipError_t flush_desc();
   hipError_t flush_y();
-  LaunchList one(System* s) const;
   // Launch list over v (systems of one tile class).
   LaunchList list(const std::vector<System*>& v) const;
   void finish(System* s, hub_status st);

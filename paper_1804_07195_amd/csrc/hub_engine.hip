@@ -493,8 +493,6 @@ hipError_t Engine::flush_y() {
   return e;
 }
 
-LaunchList Engine::one(System* s) const { return list(std::vector<System*>{s}); }
-
 LaunchList Engine::list(const std::vector<System*>& v) const {
   LaunchList L;
   std::memset(&L, 0, sizeof(L));
