@@ -100,7 +100,7 @@ hub_status hub_apply_Mdag(hub_ctx *ctx, const hub_lattice *lat, const double *ph
 
 /* y_b = (M M^dagger + mu2[b]) x_b: the Hermitian positive-definite normal operator
  * of Sec. 3 with the Hasenbusch shift of Sec. 5.1.  mu2: host float64 [batch], each
- * finite and >= 0.  Uses library workspace for e^{i phi} (HUB_ERR_OOM if over budget). */
+ * finite and >= 0.  Uses library workspace (HUB_ERR_OOM if over budget). */
 hub_status hub_apply_normal(hub_ctx *ctx, const hub_lattice *lat, const double *phi, const double *mu2,
                             const hub_c128 *x, hub_c128 *y, int32_t batch, hipStream_t stream);
 
@@ -109,7 +109,7 @@ hub_status hub_apply_normal(hub_ctx *ctx, const hub_lattice *lat, const double *
 
 /* hub_apply_normal for callers that cannot allocate device memory (code under HIP
  * graph capture, serving loops that must not call hipMalloc): the same kernels and
- * results, with the intermediate e^{i phi} in a scratch array that the library holds
+ * results, with their intermediate values in a scratch array that the library holds
  * on each device from the first hub_create on that device until the process ends,
  * instead of context workspace.  Allocates nothing.  batch * N * 16 bytes must not
  * exceed HUB_NOALLOC_SCRATCH_BYTES (else HUB_ERR_ARG; at 102x102x64 that is a batch

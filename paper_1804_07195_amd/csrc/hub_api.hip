@@ -433,10 +433,10 @@ hub_status hub_apply_normal(hub_ctx* ctx, const hub_lattice* lat, const double* 
   }
   HUB_HIP(hipSetDevice(ctx->device), "hipSetDevice");
   const Geom g = make_geom(*lat);
-  double2* ph64 = (double2*)ctx->pool->alloc((size_t)g.n * 16, stream);
-  if (!ph64) return fail(HUB_ERR_OOM, "workspace for the phase of phi");
-  const hipError_t e = launch_normal(g, phi, ph64, m2, (const double2*)x, (double2*)y, batch, stream);
-  ctx->pool->release(ph64, stream);
+  double2* ws = (double2*)ctx->pool->alloc(normal_scratch(g, batch), stream);
+  if (!ws) return fail(HUB_ERR_OOM, "workspace for the normal operator");
+  const hipError_t e = launch_normal(g, phi, ws, m2, (const double2*)x, (double2*)y, batch, stream);
+  ctx->pool->release(ws, stream);
   if (e != hipSuccess) return hip_fail(e, "normal operator launch");
   return HUB_OK;
 }
@@ -462,8 +462,7 @@ hub_status hub_apply_normal_noalloc(hub_ctx* ctx, const hub_lattice* lat, const 
   }
   if (!ctx->scratch) return fail(HUB_ERR_HIP, "no scratch address for this device");
   HUB_HIP(hipSetDevice(ctx->device), "hipSetDevice");
-  // the phases into the scratch (every entry written before it is read), then the kernels of
-  // hub_apply_normal
+  // the kernels of hub_apply_normal on the scratch (every entry written before it is read)
   const hipError_t e = launch_normal(g, phi, (double2*)ctx->scratch, m2, (const double2*)x, (double2*)y, batch, stream);
   if (e != hipSuccess) return hip_fail(e, "normal operator launch");
   return HUB_OK;

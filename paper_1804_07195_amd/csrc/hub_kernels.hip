@@ -602,14 +602,37 @@ __global__ __launch_bounds__(kBlock) void k_apply_grp(Geom g, const double* __re
 
 struct Mu2Arr { double v[kMaxSys]; };
 
+// y_b = M u_b + mu2_b x_b: the second pass of the public normal operator (u = M^dagger x),
+// one vector per workgroup.
+__global__ __launch_bounds__(kBlock) void k_normal2_pub(Geom g, const double* __restrict__ phi, Mu2Arr mu2,
+                                                        const double2* __restrict__ u,
+                                                        const double2* __restrict__ x, double2* __restrict__ y,
+                                                        int ntiles) {
+  const int l = xcd_remap(blockIdx.x, gridDim.x);
+  const int b = l / ntiles, tile = l - b * ntiles;
+  const size_t off = (size_t)b * g.n;
+  const double m2 = mu2.v[b];
+  const int base = tile * kPubTile + threadIdx.x;
+  auto ld = [=](int k) { return u[off + k]; };
+  auto pre = [=](int n) { return x[off + n]; };
+  auto post = [=](int n, double2 q, double2, double2 xv) {
+    q.x += m2 * xv.x;
+    q.y += m2 * xv.y;
+    y[off + n] = q;
+  };
+  stencil_sites<double, false, kPubSites, kPubSites>(g, AnglePhi<double>(phi), base, g.n, ld, Same{}, pre, NoMid{},
+                                                     post);
+}
+
 // The public normal operator on a batch that shares phi: y_b = (M M^dagger + mu2_b) x_b for a
 // group of `per` vectors per workgroup, in one pass after k_phase_pub.  A site's thread
 // evaluates u = M^dagger x at the five sites that M reads, from 15 values of x (the
 // cancelled 12-point form reads 12 but rounds worse: 1.5e-16 against 0.9e-16 of |y|).  That
 // reads x and writes y, where a pass for u and one for y also write u, read it back, read x
 // again and evaluate each phase twice; the neighbours come from the caches.  Two vectors at
-// 102x102x64: 47.6 -> 38.8 us (31 and 7.5 us in the two kernels; 96 MB moved, and the L1
-// loads of the neighbours, 35 of 16 bytes per site, take 19 us of the 31 by themselves).
+// 102x102x64 with buffers rotated: 47.6 -> 38.8 us (31 and 7.5 us in the two kernels; 96 MB moved, and
+// the L1 loads of the neighbours, 35 of 16 bytes per site, take 19 us of the 31 by
+// themselves); resident 42.2 -> 41.6, four vectors 79.9 -> 60.9.
 __global__ __launch_bounds__(kBlock) void k_normal_pub(Geom g, const double2* __restrict__ ph64, Mu2Arr mu2,
                                                        const double2* __restrict__ x, double2* __restrict__ y,
                                                        int ntiles, int per, int batch) {
@@ -2083,15 +2106,30 @@ hipError_t launch_ms_iter(const MsDesc* d, int ntiles, int it, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_normal(const Geom& g, const double* phi, double2* ph64, const double mu2_host[kMaxSys],
+// One pass pays for the phases' kernel where a workgroup takes two vectors or more; with one
+// (a batch of one, or lattices that need a workgroup per vector to fill the device) two passes
+// are faster: 102x102x64, one vector 25.6 us against 31.2; 48x48x64 11.7 against 13.4;
+// 24x24x64, four vectors 12.0 against 13.4.  Both give the same bits.
+static int normal_group(int n, int batch) { return pub_group((n + kBlock - 1) / kBlock, batch); }
+
+size_t normal_scratch(const Geom& g, int batch) { return (size_t)g.n * 16 * (normal_group(g.n, batch) > 1 ? 1 : batch); }
+
+hipError_t launch_normal(const Geom& g, const double* phi, double2* ws, const double mu2_host[kMaxSys],
                          const double2* x, double2* y, int batch, hipStream_t st) {
-  const int nt = (g.n + kBlock - 1) / kBlock;
-  hipLaunchKernelGGL(k_phase_pub, dim3(nt), dim3(kBlock), 0, st, phi, ph64, g.n);
-  const int per = pub_group(nt, batch);
   Mu2Arr m;
   for (int b = 0; b < kMaxSys; ++b) m.v[b] = b < batch ? mu2_host[b] : 0.0;
-  hipLaunchKernelGGL(k_normal_pub, dim3(nt * ((batch + per - 1) / per)), dim3(kBlock), 0, st, g, ph64, m, x, y, nt, per,
-                     batch);
+  const int per = normal_group(g.n, batch);
+  if (per > 1) {
+    const int nt = (g.n + kBlock - 1) / kBlock;
+    hipLaunchKernelGGL(k_phase_pub, dim3(nt), dim3(kBlock), 0, st, phi, ws, g.n);
+    hipLaunchKernelGGL(k_normal_pub, dim3(nt * ((batch + per - 1) / per)), dim3(kBlock), 0, st, g, ws, m, x, y, nt, per,
+                       batch);
+    return hipGetLastError();
+  }
+  const hipError_t e = launch_apply(g, phi, x, ws, batch, true, st);
+  if (e != hipSuccess) return e;
+  const int nt = (g.n + kPubTile - 1) / kPubTile;
+  hipLaunchKernelGGL(k_normal2_pub, dim3(nt * batch), dim3(kBlock), 0, st, g, phi, m, ws, x, y, nt);
   return hipGetLastError();
 }
 
