@@ -529,8 +529,10 @@ Publish Engine::publication(const std::vector<System*>& v) {
 
 // A kernel writes the records and then a sequence number to host-coherent memory and
 // the host polls the number: about half the latency of a copy plus a stream
-// synchronisation.  Two publications may be under way, into buffers of their own.  hipStreamQuery bounds the wait; should the stream drain without
-// the number showing, the records are read through a copy instead.
+// synchronisation.  Two publications may be under way, into buffers of their own.
+// hipStreamQuery bounds the wait.  Should the stream drain without the number showing, the
+// records are read through a copy where nothing was published after them; where something
+// was, the device holds the later records, and that is an error.
 hipError_t Engine::wait_publication(const Publish& pub) {
   const size_t lo = pub.d - d_scal_;
   for (unsigned spin = 1;; ++spin) {
@@ -540,6 +542,10 @@ hipError_t Engine::wait_publication(const Publish& pub) {
       if (q == hipErrorNotReady) continue;
       if (q != hipSuccess) return q;
       if ((int)(__atomic_load_n(h_pub_flag_, __ATOMIC_ACQUIRE) - pub.seq) >= 0) break;
+      if (pub.seq != pub_seq_) {
+        set_error("results of a solver step not published");
+        return hipErrorUnknown;
+      }
       HUB_TRY(hipMemcpyAsync(h_scal_ + lo, pub.d, sizeof(Scal) * pub.cnt, hipMemcpyDeviceToHost, st_));
       return hipStreamSynchronize(st_);
     }

@@ -1,0 +1,184 @@
+// Host check of the solver engine (csrc/hub_engine.hip) against a device that is played by
+// this file: every launch takes effect at once, with numbers that lead the engine where the
+// scenario wants it.  Usage: engine_host <scenario>; exit 0: the engine did as it should.
+#include <cmath>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <functional>
+#include <map>
+#include <string>
+#include <vector>
+
+#include "hub_engine.h"
+
+using namespace hub;
+
+// ---- the device ---------------------------------------------------------------------
+namespace {
+struct Device {
+  bool lose_flag = false;  // the sequence number of an Arnoldi step's publication does not arrive
+  double resid2 = 9e-20;   // |b - A x|^2 that the next true residuals show (|b| = 1)
+  int cgs = 0;             // second halves of Arnoldi steps so far
+  size_t freed = 0;        // hipFree calls
+  std::function<void(const GangList&, int, bool)> gang;
+} dev;
+
+void publish(const Publish& pub, bool lose = false) {
+  if (!pub.flag) return;
+  std::memcpy((void*)pub.h, (const void*)pub.d, sizeof(Scal) * pub.cnt);
+  if (!lose) *pub.flag = pub.seq;
+}
+void start(Scal& sc, int maxit) {
+  sc.active = 1;
+  sc.iters = sc.git = sc.gang = 0;
+  sc.maxit = maxit;
+}
+}  // namespace
+
+extern "C" {
+hipError_t hipMalloc(void** p, size_t n) { return (*p = std::calloc(1, n)) ? hipSuccess : hipErrorOutOfMemory; }
+hipError_t hipFree(void* p) { return std::free(p), ++dev.freed, hipSuccess; }
+hipError_t hipHostMalloc(void** p, size_t n, unsigned) { return hipMalloc(p, n); }
+hipError_t hipHostFree(void* p) { return std::free(p), hipSuccess; }
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { return std::memcpy(d, s, n), hipSuccess; }
+hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t) { return std::memset(d, v, n), hipSuccess; }
+hipError_t hipStreamQuery(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t* e) { return *e = (hipEvent_t)std::malloc(1), hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return hipEventCreate(e); }
+hipError_t hipEventDestroy(hipEvent_t e) { return std::free((void*)e), hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventQuery(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { return *ms = 0.0f, hipSuccess; }
+}
+
+namespace hub {
+hipError_t launch_apply(const Geom&, const double*, const double2*, double2*, int, bool, hipStream_t, bool) { return hipSuccess; }
+hipError_t launch_force(const Geom&, const double*, const double2*, const double2*, double, int, double*, int, hipStream_t) {
+  return hipSuccess;
+}
+hipError_t launch_dot_re(const Geom&, const double2*, const double2*, int, double*, double*, hipStream_t) { return hipSuccess; }
+hipError_t launch_phase(const double*, double2*, float*, int, hipStream_t) { return hipSuccess; }
+hipError_t launch_publish(const Publish& pub, hipStream_t) { return publish(pub), hipSuccess; }
+hipError_t launch_xupdate(const SysDesc*, const LaunchList&, const double*, int, bool, hipStream_t) { return hipSuccess; }
+hipError_t launch_gang_clear(unsigned long long*, size_t, hipStream_t) { return hipSuccess; }
+hipError_t launch_gang_leave(const SysDesc*, const GangList&, int, bool, hipStream_t) { return hipSuccess; }
+hipError_t launch_cg_init_zero(const SysDesc*, const LaunchList& L, RedMode mode, const Publish& pub, hipStream_t) {
+  for (int k = 0; k < L.nsys; ++k) {
+    L.scal[L.sys[k]].red[0] = 1.0;
+    if (mode == RED_CG_SETUP) start(L.scal[L.sys[k]], L.pi[k]);
+  }
+  return publish(pub), hipSuccess;
+}
+hipError_t launch_normal_slot(const SysDesc*, const LaunchList& L, int, int, int, RedMode mode, int off, bool, const Publish& pub,
+                              hipStream_t) {
+  for (int k = 0; k < L.nsys; ++k) {
+    L.scal[L.sys[k]].red[off] = dev.resid2;
+    if (mode == RED_CG_SETUP) start(L.scal[L.sys[k]], L.pi[k]);
+  }
+  return publish(pub), hipSuccess;
+}
+hipError_t launch_prep_inner(const SysDesc*, const LaunchList& L, int, hipStream_t) {
+  for (int k = 0; k < L.nsys; ++k) start(L.scal[L.sys[k]], L.pi[k]);
+  return hipSuccess;
+}
+hipError_t launch_arnoldi_dots(const SysDesc*, const LaunchList& L, int j, bool, hipStream_t) {
+  for (int k = 0; k < L.nsys; ++k)
+    for (int i = 0; i <= 2 * j + 1; ++i) L.scal[L.sys[k]].red[i] = i == 2 * j ? 1.0 : 0.0;
+  return hipSuccess;
+}
+hipError_t launch_cgs(const SysDesc*, const LaunchList& L, int j, const Publish& pub, hipStream_t) {
+  ++dev.cgs;
+  for (int k = 0; k < L.nsys; ++k) L.scal[L.sys[k]].red[2 * j + 2] = 0.9;
+  return publish(pub, dev.lose_flag), hipSuccess;
+}
+hipError_t launch_gang(const SysDesc*, const GangList& L, int K, bool single, hipStream_t, hipEvent_t, hipEvent_t) {
+  if (dev.gang) return dev.gang(L, K, single), hipSuccess;
+  for (int k = 0; k < L.nsys; ++k) {
+    L.scal[L.sys[k]].active = 0;
+    L.scal[L.sys[k]].iters = 10;
+  }
+  return hipSuccess;
+}
+static void tiled(const LaunchList& L) {
+  for (int k = 0; k < L.nsys; ++k) {
+    L.scal[L.sys[k]].active = 0;
+    L.scal[L.sys[k]].iters = 10;
+  }
+}
+hipError_t launch_cg_iter(const SysDesc*, const LaunchList& L, bool, hipStream_t) { return tiled(L), hipSuccess; }
+hipError_t launch_cg_stage(const SysDesc*, const LaunchList& L, bool, int, hipStream_t, hipEvent_t, hipEvent_t) {
+  return tiled(L), hipSuccess;
+}
+}  // namespace hub
+
+// ---- scenarios ----------------------------------------------------------------------
+namespace {
+#define CHECK(c)                                                    \
+  do {                                                              \
+    if (!(c)) {                                                     \
+      std::printf("line %d: %s does not hold\n", __LINE__, #c);     \
+      std::exit(1);                                                 \
+    }                                                               \
+  } while (0)
+
+hub_solve_opts options(hub_solver solver) {
+  hub_solve_opts o{};
+  o.solver = solver;
+  o.max_iter = solver == HUB_CG_FP64 ? 20000 : 3;
+  o.restart_m = 10;
+  o.inner_max_iter = 4000;
+  o.tol = 1e-10;
+  o.inner_a = 5.0;
+  o.inner_floor = 1e-5;
+  o.check_every = 8;
+  return o;
+}
+System system_of(int L1, int L2, int Nt, hub_solver solver) {
+  static double field;
+  hub_lattice lat{};
+  lat.L1 = L1, lat.L2 = L2, lat.Nt = Nt, lat.kappa_t = 0.2;
+  System s;
+  s.g = make_geom(lat);
+  s.phi = &field;
+  s.opts = options(solver);
+  return s;
+}
+constexpr size_t kPlenty = (size_t)8 << 30;
+
+// A publication whose number does not arrive while the next Arnoldi step is on the device
+// already: the records there are the next step's, and must not pass for the ones waited for.
+// Where nothing came after it, they are the right ones.
+void lost_publication() {
+  for (bool next_on_the_way : {true, false}) {
+    dev = Device{};
+    Pool pool(0, kPlenty);
+    Engine eng(&pool, nullptr);
+    System s = system_of(6, 6, 8, HUB_FGMRES_MIXED);
+    if (!next_on_the_way) s.opts.restart_m = 1;
+    CHECK(eng.add(&s) == Engine::ADD_OK);
+    dev.lose_flag = true;
+    bool failed = false;
+    for (int k = 0; k < 50 && !s.done && !failed; ++k) failed = eng.step() != hipSuccess;
+    CHECK(dev.cgs > 0);
+    CHECK(failed == next_on_the_way);
+    CHECK(failed || s.done);
+    eng.remove(&s);
+  }
+}
+
+const std::map<std::string, void (*)()> scenarios = {
+    {"lost_publication", lost_publication},
+};
+}  // namespace
+
+int main(int argc, char** argv) {
+  const auto it = argc > 1 ? scenarios.find(argv[1]) : scenarios.end();
+  if (it == scenarios.end()) return std::printf("no such scenario\n"), 2;
+  it->second();
+  return 0;
+}
