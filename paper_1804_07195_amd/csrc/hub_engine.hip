@@ -100,7 +100,13 @@ void* Pool::alloc(size_t bytes, hipStream_t st) {
       return p;
     }
   }
-  // release cached blocks, the largest first, until the new one fits
+  // release cached blocks, the largest first, until the new one fits; none where even all
+  // of them would not make room
+  if (used_ + sz > budget_) {
+    set_error("workspace of " + std::to_string(sz) + " bytes exceeds the HBM budget (" +
+              std::to_string(used_) + " of " + std::to_string(budget_) + " bytes in use)");
+    return nullptr;
+  }
   while (reserved_ + sz > budget_ && !free_.empty()) {
     auto last = std::prev(free_.end());
     Block b = last->second.back();
@@ -109,11 +115,6 @@ void* Pool::alloc(size_t bytes, hipStream_t st) {
     drop_event(b.ev, true);
     (void)hipFree(b.p);
     reserved_ -= b.bytes;
-  }
-  if (reserved_ + sz > budget_) {
-    set_error("workspace of " + std::to_string(sz) + " bytes exceeds the HBM budget (" +
-              std::to_string(reserved_) + " of " + std::to_string(budget_) + " bytes reserved)");
-    return nullptr;
   }
   void* p = nullptr;
   if (hipMalloc(&p, sz) != hipSuccess) {

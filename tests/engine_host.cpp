@@ -171,7 +171,24 @@ void lost_publication() {
   }
 }
 
+// A block that does not fit beside those in use is refused with the cached blocks kept: none
+// of them would make room for it.
+void refusal_keeps_cache() {
+  constexpr size_t MB = (size_t)1 << 20;
+  Pool pool(0, 10 * MB);
+  void *held = pool.alloc(4 * MB, nullptr), *cached = pool.alloc(4 * MB, nullptr);
+  CHECK(held && cached);
+  pool.release(cached, nullptr);
+  CHECK(!pool.alloc(8 * MB, nullptr));
+  CHECK(dev.freed == 0 && pool.reserved() == 8 * MB);
+  void* fits = pool.alloc(6 * MB, nullptr);  // in the place of the cached one
+  CHECK(fits && dev.freed == 1 && pool.reserved() == 10 * MB);
+  pool.release(held, nullptr);
+  pool.release(fits, nullptr);
+}
+
 const std::map<std::string, void (*)()> scenarios = {
+    {"refusal_keeps_cache", refusal_keeps_cache},
     {"lost_publication", lost_publication},
 };
 }  // namespace
