@@ -486,17 +486,34 @@ hub_status run_solves(hub_ctx* ctx, std::vector<System>& sys, const hub_solve_op
   const size_t N = sys.empty() ? 0 : (size_t)sys[0].g.n;  // one lattice size per call
   for (const System& sy : sys)
     if (phase.emplace(sy.phi, PhaseJob{sy.phi, nullptr, nullptr}).second) ++nj;
+  // one block for all tables, unless the pool's block sizes make it larger than a block each
   const size_t b64 = (N * 16 + 255) / 256 * 256, b32 = want32 ? (N * 4 + 255) / 256 * 256 : 0;
-  char* mem = (char*)ctx->pool->alloc((size_t)nj * (b64 + b32), stream);
-  if (mem)
-    owned.push_back(mem);
-  else
-    result = fail(HUB_ERR_OOM, "workspace for the phase of phi");
+  const size_t apart = Pool::rounded(b64) + (want32 ? Pool::rounded(b32) : 0);
+  const bool together = Pool::rounded((size_t)nj * (b64 + b32)) <= (size_t)nj * apart;
+  char* block = nullptr;
+  auto table = [&](size_t bytes) -> char* {
+    char* p = together ? block : (char*)ctx->pool->alloc(bytes, stream);
+    if (together)
+      block += bytes;
+    else if (p)
+      owned.push_back(p);
+    return p;
+  };
+  if (together) {
+    block = (char*)ctx->pool->alloc((size_t)nj * (b64 + b32), stream);
+    if (block)
+      owned.push_back(block);
+    else
+      result = fail(HUB_ERR_OOM, "workspace for the phase of phi");
+  }
   nj = 0;
   for (auto it = phase.begin(); it != phase.end() && result == HUB_OK;) {
-    it->second.p64 = (double2*)mem;
-    it->second.p32 = want32 ? (float*)(mem + b64) : nullptr;
-    mem += b64 + b32;
+    it->second.p64 = (double2*)table(b64);
+    it->second.p32 = want32 ? (float*)table(b32) : nullptr;
+    if (!it->second.p64 || (want32 && !it->second.p32)) {
+      result = fail(HUB_ERR_OOM, "workspace for the phase of phi");
+      break;
+    }
     J.j[nj++] = it->second;
     if (++it == phase.end() || nj == kMaxSys) {
       const hipError_t e = launch_phase_jobs(J, nj, (int)N, stream);

@@ -1,5 +1,5 @@
-// Host check of the solver engine (csrc/hub_engine.hip) against a device that is played by
-// this file: every launch takes effect at once, with numbers that lead the engine where the
+// Host check of the solver engine (csrc/hub_engine.hip) and the C ABI's drivers
+// (csrc/hub_api.hip) against a device that is played by this file: every launch takes effect at once, with numbers that lead the engine where the
 // scenario wants it.  Usage: engine_host <scenario>; exit 0: the engine did as it should.
 #include <cmath>
 #include <cstdio>
@@ -43,6 +43,12 @@ hipError_t hipHostMalloc(void** p, size_t n, unsigned) { return hipMalloc(p, n);
 hipError_t hipHostFree(void* p) { return std::free(p), hipSuccess; }
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { return std::memcpy(d, s, n), hipSuccess; }
 hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t) { return std::memset(d, v, n), hipSuccess; }
+hipError_t hipGetDeviceCount(int* n) { return *n = 1, hipSuccess; }
+hipError_t hipMemGetInfo(size_t* f, size_t* t) { return *f = *t = (size_t)8 << 30, hipSuccess; }
+hipError_t hipGetSymbolAddress(void** p, const void* s) { return *p = (void*)s, hipSuccess; }
+const char* hipGetErrorString(hipError_t) { return "an error"; }
+hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { return *s = (hipStream_t)std::malloc(1), hipSuccess; }
+hipError_t hipStreamDestroy(hipStream_t s) { return std::free((void*)s), hipSuccess; }
 hipError_t hipStreamQuery(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipSetDevice(int) { return hipSuccess; }
@@ -63,6 +69,16 @@ hipError_t launch_force(const Geom&, const double*, const double2*, const double
 }
 hipError_t launch_dot_re(const Geom&, const double2*, const double2*, int, double*, double*, hipStream_t) { return hipSuccess; }
 hipError_t launch_phase(const double*, double2*, float*, int, hipStream_t) { return hipSuccess; }
+hipError_t launch_phase_jobs(const PhaseJobs&, int, int, hipStream_t) { return hipSuccess; }
+hipError_t launch_normal(const Geom&, const double*, double2*, const double*, const double2*, double2*, int, hipStream_t) {
+  return hipSuccess;
+}
+size_t normal_scratch(const Geom& g, int batch) { return (size_t)g.n * 16 * batch; }
+hipError_t launch_force_sum(const Geom&, const double*, const double2*, const double2*, const double*, int, double*, int,
+                            hipStream_t) {
+  return hipSuccess;
+}
+hipError_t launch_stream_bytes(const double*, const double2*, double2*, int, int, hipStream_t) { return hipSuccess; }
 hipError_t launch_publish(const Publish& pub, hipStream_t) { return publish(pub), hipSuccess; }
 hipError_t launch_xupdate(const SysDesc*, const LaunchList&, const double*, int, bool, hipStream_t) { return hipSuccess; }
 hipError_t launch_gang_clear(unsigned long long*, size_t, hipStream_t) { return hipSuccess; }
@@ -187,7 +203,33 @@ void refusal_keeps_cache() {
   pool.release(fits, nullptr);
 }
 
+// What the tables of several fields may take: a workspace of one block each for the tables and
+// the vectors of every system is enough, also where blocks of a power of two would not be.
+void tables_of_fields() {
+  for (hub_solver solver : {HUB_CG_FP64, HUB_FGMRES_MIXED})
+    for (int fields : {1, 3, 5, 33, 64})
+      for (int Nt : {3, 16, 64, 100}) {
+        dev = Device{};
+        dev.resid2 = 0.0;
+        const System s = system_of(4, 2, Nt, solver);
+        const size_t n = s.g.n;
+        hub_ctx* ctx = nullptr;
+        CHECK(hub_create(&ctx, 0, fields * Engine::workspace_bytes(s.g, s.opts)) == HUB_OK);
+        std::vector<double> phi(fields * n), mu2(fields);
+        std::vector<hub_c128> b(fields * n), x(fields * n);
+        std::vector<hub_solve_info> info(fields);
+        hub_lattice lat{};
+        lat.L1 = 4, lat.L2 = 2, lat.Nt = Nt, lat.kappa_t = 0.2;
+        const hub_status st = hub_solve_fields(ctx, &lat, phi.data(), 1, mu2.data(), fields, b.data(), x.data(), &s.opts,
+                                               info.data(), nullptr);
+        if (st != HUB_OK) std::printf("solver %d, %d fields, Nt %d: %s\n", solver, fields, Nt, hub_last_error());
+        CHECK(st == HUB_OK);
+        CHECK(hub_destroy(ctx) == HUB_OK);
+      }
+}
+
 const std::map<std::string, void (*)()> scenarios = {
+    {"tables_of_fields", tables_of_fields},
     {"refusal_keeps_cache", refusal_keeps_cache},
     {"lost_publication", lost_publication},
 };
