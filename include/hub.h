@@ -68,7 +68,7 @@ typedef enum {
   HUB_ERR_ARG = 1,       /* invalid argument; nothing was enqueued                  */
   HUB_ERR_OOM = 2,       /* workspace beyond the context's HBM budget               */
   HUB_ERR_NOCONV = 3,    /* iteration limit reached; x holds the last iterate       */
-  HUB_ERR_HIP = 4,       /* a HIP runtime call failed                               */
+  HUB_ERR_HIP = 4,       /* a HIP runtime call failed, or a kernel gave up          */
   HUB_ERR_BUSY = 5,      /* request can never fit the serving budget                */
   HUB_ERR_NOTFOUND = 6   /* unknown ticket                                          */
 } hub_status;
@@ -373,7 +373,8 @@ hub_status hub_submit(hub_ctx *ctx, const hub_request *req, uint64_t *ticket);
  * *done = 1, info (if not NULL) is filled, the ticket is released and the return
  * value is the request's own final status: HUB_OK; HUB_ERR_NOCONV if it missed its
  * tolerance (x_out, S and the force then come from its last iterate); HUB_ERR_ARG if
- * phi or chi held a non-finite value; HUB_ERR_HIP if a HIP call failed while it ran.
+ * phi or chi held a non-finite value; HUB_ERR_HIP if a HIP call failed, or its kernel
+ * gave up waiting for one of its workgroups, while it ran.
  * Unknown tickets: HUB_ERR_NOTFOUND with *done = 0. */
 hub_status hub_poll(hub_ctx *ctx, uint64_t ticket, int32_t *done, hub_solve_info *info);
 

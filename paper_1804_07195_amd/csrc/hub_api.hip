@@ -173,7 +173,7 @@ class Server {
     tickets_.erase(it);
     if (st == HUB_ERR_NOCONV) set_error("iteration limit reached before the tolerance");
     if (st == HUB_ERR_ARG) set_error("non-finite value in phi, chi or the initial guess");
-    if (st == HUB_ERR_HIP) set_error("a HIP runtime call failed while the request ran");
+    if (st == HUB_ERR_HIP) set_error("a HIP runtime call failed, or a kernel gave up, while the request ran");
     return st;
   }
 
@@ -557,13 +557,13 @@ hub_status run_solves(hub_ctx* ctx, std::vector<System>& sys, const hub_solve_op
   hipError_t e = hipStreamSynchronize(stream);
   if (result != HUB_OK) return result;
   if (e != hipSuccess) return hip_fail(e, "solve");
-  // the first failure in this order of severity: non-finite input, then non-convergence
-  for (const System& sy : sys)
-    if (sy.status == HUB_ERR_ARG) result = HUB_ERR_ARG;
-  for (const System& sy : sys)
-    if (sy.status != HUB_OK && result == HUB_OK) result = sy.status;
+  // the first failure in this order of severity: a system given up, non-finite input, non-convergence
+  for (hub_status st : {HUB_ERR_NOCONV, HUB_ERR_ARG, HUB_ERR_HIP})
+    for (const System& sy : sys)
+      if (sy.status == st) result = st;
   if (result == HUB_ERR_ARG) set_error("non-finite value in phi, the right-hand side or the initial guess");
   if (result == HUB_ERR_NOCONV) set_error("iteration limit reached before the tolerance");
+  if (result == HUB_ERR_HIP) set_error("a workgroup of a system's CG did not answer");
   return result;
 }
 

@@ -213,6 +213,7 @@ enum Phase : int {
   PH_F_ARNOLDI,
   PH_F_POST_ARNOLDI,
   PH_F_LSQ,
+  PH_LOST,  // a workgroup of the system's gang did not answer
   PH_DONE
 };
 
@@ -702,6 +703,10 @@ hipError_t Engine::group_phase(int phase, const std::vector<System*>& g) {
       if (ok.empty()) return hipSuccess;
       return confirm(ok);
     }
+    case PH_LOST: {
+      for (System* s : g) finish(s, HUB_ERR_HIP);
+      return hipSuccess;
+    }
     case PH_F_POST_INIT: {
       // x = z_0 (or x0 + z_0), r = b - A x, ERR = |r|
       for (System* s : g) upload_y(s, {std::complex<double>(1.0, 0.0)});
@@ -1163,8 +1168,9 @@ hipError_t Engine::finish_block(Block& b) {
     const Scal& sc = flags[s->slot];
     if (s->gang) {
       if (sc.gang == 2) {
-        set_error("a workgroup of the CG did not answer");
-        return hipErrorUnknown;
+        // its iterate is not whole; the systems beside it have exchanged nothing with it
+        s->phase = PH_LOST;
+        continue;
       }
       if (sc.gang != 3) s->gang_missed = sc.gang == 1 ? s->gang_missed + 1 : 0;
       if (s->gang_missed >= kGangMisses) s->gang_leave = true;
@@ -1207,7 +1213,7 @@ hipError_t Engine::step() {
   bool progressed = true;
   while (progressed) {
     progressed = false;
-    for (int ph : {(int)PH_NEW, (int)PH_CG_CONFIRM, (int)PH_F_POST_INIT, (int)PH_F_LSQ, (int)PH_F_POST_ARNOLDI,
+    for (int ph : {(int)PH_LOST, (int)PH_NEW, (int)PH_CG_CONFIRM, (int)PH_F_POST_INIT, (int)PH_F_LSQ, (int)PH_F_POST_ARNOLDI,
                    (int)PH_F_ARNOLDI}) {
       // key: Arnoldi step, solver, whether x0 is used (the start's and the first
       // update's kernels depend on them) and tile class (one per launch)

@@ -21,7 +21,7 @@ struct Device {
   double resid2 = 9e-20;   // |b - A x|^2 that the next true residuals show (|b| = 1)
   int cgs = 0;             // second halves of Arnoldi steps so far
   size_t freed = 0;        // hipFree calls
-  std::function<void(const GangList&, int, bool)> gang;
+  std::function<void(const SysDesc*, const GangList&, int, bool)> gang;
 } dev;
 
 void publish(const Publish& pub, bool lose = false) {
@@ -33,6 +33,10 @@ void start(Scal& sc, int maxit) {
   sc.active = 1;
   sc.iters = sc.git = sc.gang = 0;
   sc.maxit = maxit;
+}
+void stop(Scal& sc) {
+  sc.active = 0;
+  sc.iters = 10;
 }
 }  // namespace
 
@@ -112,19 +116,13 @@ hipError_t launch_cgs(const SysDesc*, const LaunchList& L, int j, const Publish&
   for (int k = 0; k < L.nsys; ++k) L.scal[L.sys[k]].red[2 * j + 2] = 0.9;
   return publish(pub, dev.lose_flag), hipSuccess;
 }
-hipError_t launch_gang(const SysDesc*, const GangList& L, int K, bool single, hipStream_t, hipEvent_t, hipEvent_t) {
-  if (dev.gang) return dev.gang(L, K, single), hipSuccess;
-  for (int k = 0; k < L.nsys; ++k) {
-    L.scal[L.sys[k]].active = 0;
-    L.scal[L.sys[k]].iters = 10;
-  }
+hipError_t launch_gang(const SysDesc* sys, const GangList& L, int K, bool single, hipStream_t, hipEvent_t, hipEvent_t) {
+  if (dev.gang) return dev.gang(sys, L, K, single), hipSuccess;
+  for (int k = 0; k < L.nsys; ++k) stop(L.scal[L.sys[k]]);
   return hipSuccess;
 }
 static void tiled(const LaunchList& L) {
-  for (int k = 0; k < L.nsys; ++k) {
-    L.scal[L.sys[k]].active = 0;
-    L.scal[L.sys[k]].iters = 10;
-  }
+  for (int k = 0; k < L.nsys; ++k) stop(L.scal[L.sys[k]]);
 }
 hipError_t launch_cg_iter(const SysDesc*, const LaunchList& L, bool, hipStream_t) { return tiled(L), hipSuccess; }
 hipError_t launch_cg_stage(const SysDesc*, const LaunchList& L, bool, int, hipStream_t, hipEvent_t, hipEvent_t) {
@@ -228,7 +226,62 @@ void tables_of_fields() {
       }
 }
 
+// A gang whose wait runs out ends its own system; the others, of the same call or of other
+// requests, are solved.
+void gang_without_an_answer() {
+  for (hub_solver solver : {HUB_CG_FP64, HUB_FGMRES_MIXED}) {
+    dev = Device{};
+    dev.resid2 = 0.0;
+    dev.gang = [](const SysDesc* sys, const GangList& L, int, bool) {
+      for (int k = 0; k < L.nsys; ++k) {
+        Scal& sc = L.scal[L.sys[k]];
+        if (sc.active == 1 && sys[L.sys[k]].mu2 == 0.5) sc.gang = 2;
+        stop(sc);
+      }
+    };
+    Pool pool(0, kPlenty);
+    {
+      Engine eng(&pool, nullptr);
+      std::vector<System> s{system_of(6, 6, 8, solver), system_of(6, 6, 8, solver)};
+      std::vector<void*> owned;
+      s[0].mu2 = 0.5;
+      for (System& q : s) CHECK(eng.add(&q) == Engine::ADD_OK);
+      CHECK(eng.join_gangs({&s[0], &s[1]}, owned) == hipSuccess);
+      int ended = 0;
+      for (System& q : s) q.on_done = [&](System*) { ++ended; };
+      for (int k = 0; k < 50 && !(s[0].done && s[1].done); ++k) CHECK(eng.step() == hipSuccess);
+      CHECK(s[0].status == HUB_ERR_HIP && s[1].status == HUB_OK && ended == 2);
+      for (System& q : s) eng.remove(&q, &owned);
+      pool.release_all(owned, nullptr);
+    }
+    // requests, of other lattices too
+    hub_ctx* ctx = nullptr;
+    CHECK(hub_create(&ctx, 0, 0) == HUB_OK);
+    std::vector<std::vector<hub_c128>> x(6);
+    std::vector<double> phi(100000);
+    std::vector<hub_c128> chi(100000);
+    std::vector<uint64_t> ticket(6);
+    for (int k = 0; k < 6; ++k) {
+      hub_request r{};
+      r.lat.L1 = 4 + k, r.lat.L2 = 5, r.lat.Nt = 8, r.lat.kappa_t = 0.2;
+      r.mu2 = k == 2 ? 0.5 : 0.1;
+      x[k].resize(2 * r.lat.L1 * r.lat.L2 * r.lat.Nt);
+      r.phi = phi.data(), r.chi = chi.data(), r.x_out = x[k].data();
+      r.opts = options(solver);
+      CHECK(hub_submit(ctx, &r, &ticket[k]) == HUB_OK);
+    }
+    for (int k = 0; k < 6; ++k) {
+      int32_t done = 0;
+      hub_status st = HUB_OK;
+      while (!done) st = hub_poll(ctx, ticket[k], &done, nullptr);
+      CHECK(st == (k == 2 ? HUB_ERR_HIP : HUB_OK));
+    }
+    CHECK(hub_destroy(ctx) == HUB_OK);
+  }
+}
+
 const std::map<std::string, void (*)()> scenarios = {
+    {"gang_without_an_answer", gang_without_an_answer},
     {"tables_of_fields", tables_of_fields},
     {"refusal_keeps_cache", refusal_keeps_cache},
     {"lost_publication", lost_publication},
