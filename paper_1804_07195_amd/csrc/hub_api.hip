@@ -121,6 +121,7 @@ class Server {
     }
     engine_.reset(new Engine(ctx->pool.get(), st_));
     if (!engine_->ok()) return;
+    engine_->deny_meetings(ctx->deny);
     thread_ = std::thread([this] { run(); });
   }
   // False if the stream, the engine or the thread could not be set up.
@@ -298,6 +299,7 @@ Engine* engine_for(hub_ctx* ctx, hipStream_t st) {
     return nullptr;
   }
   e->set_profiling(ctx->profiling);
+  e->deny_meetings(ctx->deny);
   Engine* p = e.get();
   ctx->engines[st] = std::move(e);
   return p;
@@ -766,6 +768,15 @@ hub_status hub_profile_enable(hub_ctx* ctx, int32_t enable) {
   std::lock_guard<std::mutex> lk(ctx->mu);
   ctx->profiling = enable != 0;
   for (auto& kv : ctx->engines) kv.second->set_profiling(ctx->profiling);
+  return HUB_OK;
+}
+
+hub_status hub_test_deny_meetings(hub_ctx* ctx, uint32_t mask) {
+  set_error("");
+  if (!ctx) return fail(HUB_ERR_ARG, "ctx is NULL");
+  std::lock_guard<std::mutex> lk(ctx->mu);
+  ctx->deny = mask;
+  for (auto& kv : ctx->engines) kv.second->deny_meetings(mask);
   return HUB_OK;
 }
 

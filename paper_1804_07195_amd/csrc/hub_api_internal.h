@@ -26,7 +26,12 @@ struct hub_ctx {
   std::unique_ptr<hub::api::Server> server;
   std::mutex server_mu;
   bool profiling = false;
+  unsigned deny = 0;  // Engine::deny_meetings of its engines (tests)
 };
+
+// For tests, not part of hub.h: Engine::deny_meetings of every engine of the context, before
+// its first served request.
+extern "C" hub_status hub_test_deny_meetings(hub_ctx* ctx, uint32_t mask);
 
 namespace hub {
 namespace api {

@@ -69,10 +69,12 @@ class Pool {
 constexpr int kTailBlock = 4;
 // Iterations of a gang launch (a gang leaves its launch at convergence): a system that has
 // stopped waits for the others of its launch, and only with others; a launch costs 12 us
-// (6x6x16) to 32 us (102x102x64) before its first iteration.  And meetings in a row that a
-// gang may miss before its system goes on with the tiled kernels.
+// (6x6x16) to 32 us (102x102x64) before its first iteration.
 constexpr int kGangIters = 128, kGangItersAlone = 512;
-constexpr int kGangMisses = 3;
+// Meetings in a row that a gang may miss (or be refused) before it goes on in steps; and how:
+// blocks of so many iterations, one of them before the next attempt to meet, twice as many
+// after each attempt that fails, up to kGangStepBlocks.
+constexpr int kGangMisses = 3, kGangSteps = 16, kGangStepBlocks = 64;
 
 // Host-side state of one linear system (M M^dagger + mu2) x = b.
 struct System {
@@ -105,7 +107,9 @@ struct System {
   bool gang = false;    // CG iterations by a gang of workgroups (desc.gang, desc.gang_mem)
   unsigned gang_tag = 0, gang_seq = 0;  // exchange tags handed out, launches so far
   int gang_missed = 0;  // meetings missed in a row
-  bool gang_leave = false;  // to the tiled kernels once no launch of the gang is in flight
+  int gang_steps = 0;   // blocks in steps before the gang tries to meet again
+  int gang_backoff = 0; // of them after the last attempts failed
+  unsigned gang_decided = 0;  // launches made when that was decided
   double bnorm = 0.0, err = 0.0, wnorm = 0.0, rnorm_cycle = 0.0, bb = -1.0;
   std::vector<std::complex<double>> H;  // (m+1) x m, column-major
   std::vector<void*> owned;             // workspace blocks of this system
@@ -150,6 +154,9 @@ class Engine {
     double bytes = 0.0;
   };
   void set_profiling(bool on);
+  // For tests: launch n of a gang of several workgroups, counted on the engine, is refused as
+  // by a full device where bit n mod 32 of the mask is set.
+  void deny_meetings(unsigned mask) { deny_ = mask; gang_launches_ = 0; }
   // [single][kernel]: stage 1, stage 2 of the tiled CG; the gang launches
   KernelStat stat[2][3];
   // Serving epilogue of a converged system: S = Re chi^dagger x (host), and
@@ -171,6 +178,7 @@ class Engine {
     std::vector<int> cls_end;           // end of each tile class in v
     std::vector<hipEvent_t> gev;        // start/stop of the gang launches (profiling)
     std::vector<int> gen;               // System::gen of each system at enqueue
+    std::vector<unsigned> gang_seq;     // its gang launches so far
     std::vector<std::vector<int>> its;  // iteration index per launch and system (profiling)
     std::vector<hipEvent_t> kev;        // kernel start/stop events (profiling)
     unsigned seq = 0;                   // the block's flags are home once *h_blk_flag_ reaches seq
@@ -180,7 +188,6 @@ class Engine {
   hipError_t wait_block(unsigned seq);
   hipError_t launch_gangs(const std::vector<System*>& v, bool single, Block& b);
   bool gang_entry(GangList& G, int (&taken)[kNumXcd], System* s, bool single) const;
-  hipError_t leave_gangs(bool single);
   hipError_t take_event(std::vector<hipEvent_t>& dst);
   GangCut cut_of(const Geom& g, bool single);
   hipError_t read_scal(const std::vector<System*>& v);
@@ -223,6 +230,11 @@ class Engine {
   unsigned blk_seq_ = 0;
   GangCut cut_[2] = {};                 // the last cut computed per precision, of extents cut_ext_
   int cut_ext_[2][3] = {};
+  // The smallest gang that went on in steps lately, and for how many blocks: where the CUs are
+  // taken for long, the systems of the next solve begin with that.
+  int tight_g_ = kGangMaxWgs + 1, tight_backoff_ = 0;
+  unsigned gang_launches_ = 0;
+  unsigned deny_ = 0;
   int next_buf_[2] = {0, 0};
 };
 

@@ -424,9 +424,12 @@ hipError_t Engine::join_gangs(const std::vector<System*>& v, std::vector<void*>&
     const bool single = is_fgmres(s->opts);
     const GangCut c = s->desc.gang;
     s->gang = c.g > 0 && mem;
-    s->gang_tag = s->gang_seq = 0;
-    s->gang_missed = 0;
-    s->gang_leave = false;
+    s->gang_tag = s->gang_seq = s->gang_decided = 0;
+    s->gang_missed = s->gang_steps = s->gang_backoff = 0;
+    if (c.g > 1 && c.g >= tight_g_) {
+      s->gang_missed = kGangMisses - 1;  // one more and it is back there
+      s->gang_steps = s->gang_backoff = tight_backoff_;
+    }
     if (s->gang) {
       if (c.g > 1) {
         s->desc.gang_mem = mem;
@@ -941,60 +944,48 @@ bool Engine::gang_entry(GangList& G, int (&taken)[kNumXcd], System* s, bool sing
   G.sys[G.nsys] = s->slot;
   G.pi[G.nsys] = single ? S_Z0 + s->j : S_X;
   G.tag[G.nsys] = s->gang_tag;
-  G.seq[G.nsys] = ++s->gang_seq;
+  G.seq[G.nsys] = s->gang_seq + 1;
   ++G.nsys;
   return true;
 }
 
 // Gang launches over the systems of v, as many systems to a launch as the device has CUs
-// for: every workgroup of a launch has to be on the device for its gang to meet.
+// for: every workgroup of a launch has to be on the device for its gang to meet.  Systems
+// whose gang keeps missing its meetings come first, in steps, which need no meeting.
 hipError_t Engine::launch_gangs(const std::vector<System*>& v, bool single, Block& b) {
-  for (size_t q = 0; q < v.size();) {
-    GangList G;
-    std::memset(&G, 0, sizeof(G));
-    int taken[kNumXcd] = {0};
-    for (; q < v.size(); ++q) {
-      System* s = v[q];
-      if (!gang_entry(G, taken, s, single)) break;
-    }
-    const int iters = G.nsys == 1 ? kGangItersAlone : kGangIters;
-    for (size_t k = q - G.nsys; k < q; ++k) {
-      v[k]->gang_tag += iters + 2;  // a launch uses two tags before its iterations'
-      v[k]->enq += iters;
-    }
-    hipEvent_t e0 = nullptr, e1 = nullptr;
-    if (profiling_) {
-      HUB_TRY(take_event(b.gev));
-      HUB_TRY(take_event(b.gev));
-      e0 = b.gev[b.gev.size() - 2];
-      e1 = b.gev.back();
-    }
-    HUB_TRY(launch_gang(d_desc_, G, iters, single, st_, e0, e1));
-  }
-  return hipSuccess;
-}
-
-// Systems whose gang keeps missing its meetings (other work holds the CUs) go on with the
-// tiled kernels, from the iteration that the gang has reached.
-hipError_t Engine::leave_gangs(bool single) {
-  bool any = false;
-  for (System* s : slots_) any = any || (s && !s->done && s->gang && s->gang_leave && is_fgmres(s->opts) == single);
-  if (!any) return hipSuccess;
-  auto& q = inflight_[single ? 1 : 0];
-  for (auto& b : q) HUB_TRY(finish_block(b));
-  q.clear();
-  for (System* s : slots_) {
-    if (!s || s->done || !s->gang || !s->gang_leave || is_fgmres(s->opts) != single) continue;
-    if (s->phase == (single ? (int)PH_F_INNER : (int)PH_CG_ITER)) {
-      HUB_TRY(read_scal({s}));
-      s->enq = h_scal_[s->slot].git;
+  std::vector<System*> meet, step;
+  for (System* s : v) (s->gang_steps > 0 ? step : meet).push_back(s);
+  for (int steps = 1; steps >= 0; --steps) {
+    const std::vector<System*>& w = steps ? step : meet;
+    for (size_t q = 0; q < w.size();) {
       GangList G;
       std::memset(&G, 0, sizeof(G));
       int taken[kNumXcd] = {0};
-      gang_entry(G, taken, s, single);
-      HUB_TRY(launch_gang_leave(d_desc_, G, s->desc.ntiles, single, st_));
+      for (; q < w.size(); ++q)
+        if (!gang_entry(G, taken, w[q], single)) break;
+      const int iters = steps ? kGangSteps : G.nsys == 1 ? kGangItersAlone : kGangIters;
+      for (size_t k = q - G.nsys; k < q; ++k) {
+        w[k]->gang_tag += iters + 2;  // a launch uses two tags before its iterations'
+        w[k]->enq += iters;
+        if (steps)
+          --w[k]->gang_steps;
+        else
+          ++w[k]->gang_seq;
+      }
+      if (steps) {
+        HUB_TRY(launch_gang_steps(d_desc_, G, iters, single, st_));
+        continue;
+      }
+      G.deny = (int)(deny_ >> (gang_launches_++ & 31) & 1);
+      hipEvent_t e0 = nullptr, e1 = nullptr;
+      if (profiling_) {
+        HUB_TRY(take_event(b.gev));
+        HUB_TRY(take_event(b.gev));
+        e0 = b.gev[b.gev.size() - 2];
+        e1 = b.gev.back();
+      }
+      HUB_TRY(launch_gang(d_desc_, G, iters, single, st_, e0, e1));
     }
-    s->gang = false;
   }
   return hipSuccess;
 }
@@ -1003,7 +994,6 @@ hipError_t Engine::leave_gangs(bool single) {
 // given precision, followed by an asynchronous read-back of their flags.
 hipError_t Engine::launch_block(bool single, bool& launched) {
   launched = false;
-  HUB_TRY(leave_gangs(single));
   std::vector<System*> v, gangs;
   int k = 1 << 30;
   for (System* s : slots_) {
@@ -1059,6 +1049,7 @@ hipError_t Engine::launch_block(bool single, bool& launched) {
   if (profiling_)
     for (int e = 0; e < 4 * k * ncls; ++e) HUB_TRY(take_event(b.kev));
   HUB_TRY(launch_gangs(gangs, single, b));
+  for (System* s : b.v) b.gang_seq.push_back(s->gang_seq);
   for (int it = 0; it < k && ntile > 0; ++it) {
     std::vector<int> its(ntile);
     for (int q = 0; q < ntile; ++q) its[q] = v[q]->enq++;
@@ -1172,8 +1163,19 @@ hipError_t Engine::finish_block(Block& b) {
         s->phase = PH_LOST;
         continue;
       }
-      if (sc.gang != 3) s->gang_missed = sc.gang == 1 ? s->gang_missed + 1 : 0;
-      if (s->gang_missed >= kGangMisses) s->gang_leave = true;
+      const int g = s->desc.gang.g;
+      if (sc.gang == 1 || sc.gang == 3) {
+        // (a launch that was on its way when steps were decided on counts for nothing)
+        if (b.gang_seq[q] > s->gang_decided && ++s->gang_missed >= kGangMisses) {
+          s->gang_decided = s->gang_seq;
+          s->gang_steps = s->gang_backoff = std::min(std::max(1, 2 * s->gang_backoff), kGangStepBlocks);
+          tight_g_ = std::min(tight_g_, g);
+          tight_backoff_ = s->gang_backoff;
+        }
+      } else if (sc.gang == 0 && g > 1) {
+        s->gang_missed = s->gang_backoff = 0;
+        if (g >= tight_g_) tight_g_ = kGangMaxWgs + 1;
+      }
     }
     if (sc.active) continue;
     s->pred = sc.iters;

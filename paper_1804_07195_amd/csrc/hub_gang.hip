@@ -29,8 +29,10 @@
 // A gang needs all its workgroups on the device at once.  They meet at the start of a
 // launch before they change anything; a gang that does not fit beside others is refused
 // there and launched again, a meeting that does not happen in time (other work holds the
-// CUs) is called off by one atomic decision and, should that go on, the host carries on
-// with the tiled kernels.  Every later wait is bounded too.
+// CUs) is called off by one atomic decision.  Should that go on, the host carries on with
+// k_gang_step: the same iteration cut into launches where the workgroups would wait for each
+// other, so that none of them has to be there with another one.  It gives the same bits.
+// Every wait after a meeting is bounded too.
 #include <hip/hip_ext.h>
 
 #include <type_traits>
@@ -44,6 +46,7 @@ namespace {
 typedef unsigned long long u64;
 
 constexpr int kGangWaves = kGangThreads / 64;
+enum GangPart : int { kGangShare, kGangSums, kGangUpdate };  // of an iteration in k_gang_step
 constexpr long long kGangMeetTicks = 200 * 1000;  // 2 ms of the 100 MHz wall clock
 constexpr int kGangSpins = 1 << 20;               // polls of one wait (seconds)
 
@@ -160,7 +163,7 @@ __device__ __forceinline__ void gang_release(int g) {
 // its place among g_gang_wgs (given back by whoever takes the word back to 0); [48] seq if it
 // was refused one.  The first to arrive asks for the place, the last decides to go, and
 // anybody who has waited too long decides to leave.
-__device__ int gang_meet(unsigned* ctl, int g, unsigned seq, unsigned arrived) {
+__device__ int gang_meet(unsigned* ctl, int g, unsigned seq, unsigned arrived, int deny) {
   gang_word *dec = (gang_word*)(ctl + 16), *place = (gang_word*)(ctl + 32), *refused = (gang_word*)(ctl + 48);
   auto decide = [&](unsigned what) {
     unsigned cur = word_load(dec);
@@ -178,7 +181,7 @@ __device__ int gang_meet(unsigned* ctl, int g, unsigned seq, unsigned arrived) {
     gang_word* all = (gang_word*)&g_gang_wgs;
     unsigned cur = word_load(all);
     bool room;
-    do room = cur + (unsigned)g <= kGangMaxWgs;
+    do room = !deny && cur + (unsigned)g <= kGangMaxWgs;
     while (room && !word_swap(all, cur, cur + (unsigned)g));
     if (room) {
       unsigned old = word_load(place);
@@ -246,10 +249,15 @@ __device__ __forceinline__ double from_lane(double v, int lane) {
 // no wave waits for another one's sum (2x1x64 FP64 1.37 -> 0.99 us, 6x6x16 1.75 -> 1.48 us;
 // bound by the latency of the two barriers, the LDS and the scalars' divisions).  With more
 // workgroups a second table is slower: a record is then stored behind the faces.
-template <typename R, int CLS, bool SOLO>
+// STEP: one part of one iteration (K is a GangPart), everything that another workgroup has to
+// have done in an earlier launch: r's faces sent; then u and this workgroup's record; then,
+// from the records, the rest of the iteration and the faces of the new r.  The state passes
+// through memory, and r of the halo is received anew where the whole loop carries it along
+// with its owner's arithmetic: the operations on every value are the same ones.
+template <typename R, int CLS, bool SOLO, bool STEP>
 __device__ __forceinline__ void gang_run(const SysDesc* __restrict__ d, Scal* sc, const int wg, const int zslot,
-                                         const unsigned tag0, const unsigned seq, const unsigned arrived, const int K,
-                                         char* const lds) {
+                                         const unsigned tag0, const unsigned seq, const unsigned arrived, const int deny,
+                                         const int K, char* const lds) {
   using C = typename V2<R>::T;
   using TW = Tagged<C>;
   constexpr int M = GangTab<R>::c[CLS].M, H = GangTab<R>::c[CLS].H, X = GangTab<R>::c[CLS].X;
@@ -263,7 +271,7 @@ __device__ __forceinline__ void gang_run(const SysDesc* __restrict__ d, Scal* sc
   // The small bodies have registers for every address (12x12x32: 3.1 us an iteration when they
   // work them out anew, 2.9 us when not); the others do not (FP64 at 48x48x64: 6.6, 8.6).
   constexpr bool KEEP = M <= (single ? 3 : 2);
-  constexpr int sR = single ? (int)S_R32 : (int)S_R, sP = single ? (int)S_P32 : (int)S_P0;
+  constexpr int sR = single ? (int)S_R32 : (int)S_R;
   double2* const red = reinterpret_cast<double2*>(lds);        // (gamma, |u|^2) of each wave
   double2* const red2 = red + kGangWaves;                      // of each wave's share of the records
   int* const flag = reinterpret_cast<int*>(red2 + kGangMaxWgs / 64);
@@ -273,7 +281,8 @@ __device__ __forceinline__ void gang_run(const SysDesc* __restrict__ d, Scal* sc
   const int g = SOLO ? 1 : d->gang.g, nslot = SOLO ? 0 : d->gang.nslot;
   if (tid == 0) sh_bad = 0;
   const GangBlock B = gang_block(d->g.L1, d->g.L2, d->g.Nt, d->gang.gt, d->gang.gi, d->gang.gj, wg);
-  const int it0 = sc->git;
+  // a part reads the count that no workgroup of its launch writes
+  const int it0 = !STEP || K == kGangShare ? sc->git : K == kGangSums ? sc->sit : sc->git - 1;
   C* const F = reinterpret_cast<C*>(lds + kGangHead);               // the field: r, then M^dagger r in its place
   C* const E = reinterpret_cast<C*>(lds + kGangHead + kGangLinks);  // the temporal links
   const Mem mem(d->gang_mem, g > 1 ? gang_exch_words<R>(g, nslot) * 8 : 0);
@@ -432,7 +441,7 @@ __device__ __forceinline__ void gang_run(const SysDesc* __restrict__ d, Scal* sc
     load(r, 0, 0);
     load(p, 1, 0);
     load(s, 2, 0);
-    if (!ZMEM || K == 0) load(z, 3, 0);
+    if (!ZMEM) load(z, 3, 0);
     __syncthreads();
   } else {
     take(r, d->vec[sR]);
@@ -444,14 +453,6 @@ __device__ __forceinline__ void gang_run(const SysDesc* __restrict__ d, Scal* sc
     }
     if (ZMEM) save(z, 3);
   }
-  if (K == 0) {  // the system goes on with the tiled kernels
-    if (it0 > 0) {
-      give(r, d->vec[sR]);
-      give(p, d->vec[sP + (it0 & 1)]);
-      give(z, d->vec[zslot]);
-    }
-    return;
-  }
   double gamma_prev = it0 > 0 ? sc->rrv[(it0 - 1) & 1] : 1.0;
   double alpha_prev = it0 > 0 ? sc->alpha[(it0 - 1) & 1] : 1.0;
   const double mu2 = d->mu2, stop2 = sc->stop2;
@@ -461,8 +462,8 @@ __device__ __forceinline__ void gang_run(const SysDesc* __restrict__ d, Scal* sc
   const int dt1 = sub ? -SZ : SZ;  // M^dagger reads t + 1 on A, t - 1 on B; M the other way
   if (SOLO)
     for (int q = gang_entries(B) + tid; q < gang_table(B); q += kGangThreads) F[kGangSecond / SZ + q] = cz<C>();
-  if (g > 1) {
-    if (tid == 0) sh_off = gang_meet((unsigned*)d->gang_mem, g, seq, arrived);
+  if (!STEP && g > 1) {
+    if (tid == 0) sh_off = gang_meet((unsigned*)d->gang_mem, g, seq, arrived, deny);
     __syncthreads();
     if (sh_off) {
       if (wg == 0 && tid == 0) sc->gang = sh_off;
@@ -587,6 +588,149 @@ __device__ __forceinline__ void gang_run(const SysDesc* __restrict__ d, Scal* sc
   auto bond1 = [&](int b1, int o, int behind = 0) -> C { return PACK ? low(b1 + o) : at(b1 + behind); };
   auto bond2 = [&](int b1, int b2, int o, int behind = 0) -> C { return PACK ? high(b1 + o) : at(b2 + behind); };
 
+  // The parts of an iteration.  A zero in every offset, which the compiler cannot see through:
+  // it would work out the address of every neighbour of every site once for all iterations
+  // (or, with one zero for all passes, once for both passes) and run out of registers.
+  auto unseen = [] {
+    int o = 0;
+    if (!KEEP) asm volatile("" : "+v"(o));
+    return o;
+  };
+  // v = M^dagger r (times -1 on A) here and at the extra sites; gamma, |u|^2 of each wave
+  auto first_half = [&](C* v, C* xv) {
+    const int o = unseen(), o_h = o + dh, o_t = o + dt1;
+    R acc_g = 0, acc_u = 0;
+    gang_chunks<M, CH>(B.half, [&](int m) {
+      v[m] = half_op(link(a0[m] + o_t), std::true_type{}, at(a0[m] + o_t), at(a0[m] + o_h), bond1(h1[m], o),
+                     bond2(h1[m], h2[m], o), ks, r[m]);
+      acc_g = fma(r[m].x, r[m].x, fma(r[m].y, r[m].y, acc_g));
+      acc_u = fma(v[m].x, v[m].x, fma(v[m].y, v[m].y, acc_u));
+    });
+    gang_chunks<X, X>(nx, [&](int x) {
+      xv[x] = half_op(link(xa[x] + o_t), std::true_type{}, at(xa[x] + o_t), at(xa[x] + o_h), bond1(x1[x], o),
+                      bond2(x1[x], x2[x], o), ks, at(xa[x]));
+    });
+    acc_g = dpp_wave(acc_g);
+    acc_u = dpp_wave(acc_u);
+    if (lane == 63) red[wave] = double2{(double)acc_g, (double)acc_u};
+    __syncthreads();
+    return o;
+  };
+  // the sums of the waves: this workgroup's record
+  auto record = [&](unsigned tag) {
+    if (wave == 0) {
+      const double2 q = lane < kGangWaves ? red[lane] : cz<double2>();
+      const double sg = dpp_row(q.x), su = dpp_row(q.y);
+      if (g > 1)
+        post(from_lane(sg, 15), from_lane(su, 15), tag);
+      else if (lane == 15)
+        red2[0] = double2{sg, su};
+    }
+  };
+  // w = M u + mu^2 r, in v
+  auto second_half = [&](C* v, C* xv, int o) {
+    put_own(v, o);
+    if (g > 1) gang_chunks<X, X>(nx, [&](int x) { at(xa[x]) = xv[x]; });
+    __syncthreads();
+    o = unseen();
+    const int o_h = o + dh, o_t = o - dt1;
+    gang_chunks<M, CH>(B.half, [&](int m) {
+      v[m] = half_op(link(a0[m]), std::false_type{}, at(a0[m] + o_t), at(a0[m] + o_h), bond1(h1[m], o),
+                     bond2(h1[m], h2[m], o), -ks, v[m]);
+      v[m].x = fma(rmu2, r[m].x, v[m].x);
+      v[m].y = fma(rmu2, r[m].y, v[m].y);
+    });
+    return o;
+  };
+  // gamma and |u|^2 from the waves' shares of the records
+  auto totals = [&](double& gamma, double& uu) {
+    gamma = red2[0].x;
+    uu = red2[0].y;
+    for (int k = 1; k < nw; ++k) {
+      gamma += red2[k].x;
+      uu += red2[k].y;
+    }
+  };
+  auto step_of = [&](int it, double gamma, double uu, double& beta, double& alpha) {
+    beta = it == 0 ? 0.0 : gamma / gamma_prev;
+    alpha = gamma / (fma(mu2, gamma, uu) - (it == 0 ? 0.0 : beta * gamma / alpha_prev));
+  };
+  auto advance = [&](const C* v, R rb, R ra) {
+    const int o = unseen();
+    gang_chunks<M, CH>(B.half, [&](int m) {
+      s[m].x = fma(rb, s[m].x, v[m].x);
+      s[m].y = fma(rb, s[m].y, v[m].y);
+      p[m].x = fma(rb, p[m].x, r[m].x);
+      p[m].y = fma(rb, p[m].y, r[m].y);
+      r[m].x = fma(-ra, s[m].x, r[m].x);
+      r[m].y = fma(-ra, s[m].y, r[m].y);
+      z[m].x = fma(ra, p[m].x, z[m].x);
+      z[m].y = fma(ra, p[m].y, z[m].y);
+      if (ZMEM) state.set(3 * svec + sown + (unsigned)o + m * kGangThreads * SZ, z[m]);
+    });
+    return o;
+  };
+
+  if constexpr (STEP) {
+    const bool mark = wg == 0 && tid == 0;
+    auto lost = [&] {
+      if (sh_bad && tid == 0) {
+        sc->gang = 2;
+        store_active(sc, 0);
+      }
+      return sh_bad != 0;
+    };
+    put_own(r, 0);
+    if (K == kGangShare) {
+      publish(r, tag0 + 1, 0);
+      if (mark) {
+        sc->sit = it0;
+        sc->gang = 4;
+      }
+      return;
+    }
+    receive(tag0 + 1, [&](int h, C v) { put(hdst[h], v, 0); });
+    __syncthreads();
+    if (lost()) return;
+    C v[M], xv[X];
+    int o = first_half(v, xv);
+    if (K == kGangSums) {
+      record(tag0 + 1);
+      if (mark) sc->git = it0 + 1;  // the rest of the iteration follows
+      return;
+    }
+    o = second_half(v, xv, o);
+    if (ZMEM) load(z, 3, o);
+    if (wave < nw) collect(tag0 + 1);
+    __syncthreads();
+    if (lost()) return;
+    double gamma, uu, beta, alpha;
+    totals(gamma, uu);
+    if (it0 > 0 && (!(gamma > stop2) || it0 >= maxit)) {
+      __syncthreads();
+      give(z, d->vec[zslot]);
+      if (mark) {
+        sc->rrv[it0 & 1] = gamma;
+        sc->iters = it0;
+        store_active(sc, 2);  // the next launch makes it 0: others of this one have yet to read it
+      }
+      return;
+    }
+    step_of(it0, gamma, uu, beta, alpha);
+    o = advance(v, (R)beta, (R)alpha);
+    save(r, 0);
+    save(p, 1);
+    save(s, 2);
+    if (!ZMEM) save(z, 3);
+    publish(r, tag0 + 2, o);
+    if (mark) {
+      sc->rrv[it0 & 1] = gamma;
+      sc->alpha[it0 & 1] = alpha;
+      sc->sit = it0 + 1;
+    }
+    return;
+  }
+
   // r and s of the halo: sent once per launch, then carried along with the owner's own
   // arithmetic, so that the faces of w can travel while the reduction does.
   C rh[H], sh[H];
@@ -644,8 +788,8 @@ __device__ __forceinline__ void gang_run(const SysDesc* __restrict__ d, Scal* sc
         stopped = true;
         break;
       }
-      const double beta = it == 0 ? 0.0 : gamma / gamma_prev;
-      const double alpha = gamma / (q[0].y + mu2 * gamma - (it == 0 ? 0.0 : beta * gamma / alpha_prev));
+      double beta, alpha;
+      step_of(it, gamma, q[0].y, beta, alpha);
       const R rb = (R)beta, ra = (R)alpha;
       if (any) {
         gang_chunks<M, CH>(B.half, [&](int m) {
@@ -672,54 +816,11 @@ __device__ __forceinline__ void gang_run(const SysDesc* __restrict__ d, Scal* sc
 #pragma unroll 1
   for (int step = 0; !SOLO && step < K; ++step, ++it) {
     const unsigned tag = tag0 + (unsigned)step + 3;
-    // A zero in every offset, which the compiler cannot see through: it would work out the
-    // address of every neighbour of every site once for all iterations (or, with one zero
-    // for all passes, once for both passes) and run out of registers.
-    auto unseen = [] {
-      int o = 0;
-      if (!KEEP) asm volatile("" : "+v"(o));
-      return o;
-    };
-    int o = unseen();
-    int o_h = o + dh, o_t = o + dt1;
-    // v = M^dagger r (times -1 on A) here and at the extra sites; gamma, |u|^2
     C v[M], xv[X];
-    R acc_g = 0, acc_u = 0;
-    gang_chunks<M, CH>(B.half, [&](int m) {
-      v[m] = half_op(link(a0[m] + o_t), std::true_type{}, at(a0[m] + o_t), at(a0[m] + o_h), bond1(h1[m], o),
-                     bond2(h1[m], h2[m], o), ks, r[m]);
-      acc_g = fma(r[m].x, r[m].x, fma(r[m].y, r[m].y, acc_g));
-      acc_u = fma(v[m].x, v[m].x, fma(v[m].y, v[m].y, acc_u));
-    });
-    gang_chunks<X, X>(nx, [&](int x) {
-      xv[x] = half_op(link(xa[x] + o_t), std::true_type{}, at(xa[x] + o_t), at(xa[x] + o_h), bond1(x1[x], o),
-                      bond2(x1[x], x2[x], o), ks, at(xa[x]));
-    });
-    acc_g = dpp_wave(acc_g);
-    acc_u = dpp_wave(acc_u);
-    if (lane == 63) red[wave] = double2{(double)acc_g, (double)acc_u};
-    __syncthreads();
-    // the sums of the waves: this workgroup's record
-    if (wave == 0) {
-      const double2 q = lane < kGangWaves ? red[lane] : cz<double2>();
-      const double sg = dpp_row(q.x), su = dpp_row(q.y);
-      if (g > 1)
-        post(from_lane(sg, 15), from_lane(su, 15), tag);
-      else if (lane == 15)
-        red2[0] = double2{sg, su};
-    }
-    put_own(v, o);
-    if (g > 1) gang_chunks<X, X>(nx, [&](int x) { at(xa[x]) = xv[x]; });
-    __syncthreads();
-    // w = M u + mu^2 r, in v; its faces out
-    o = unseen();
-    o_h = o + dh, o_t = o - dt1;
-    gang_chunks<M, CH>(B.half, [&](int m) {
-      v[m] = half_op(link(a0[m]), std::false_type{}, at(a0[m] + o_t), at(a0[m] + o_h), bond1(h1[m], o),
-                     bond2(h1[m], h2[m], o), -ks, v[m]);
-      v[m].x = fma(rmu2, r[m].x, v[m].x);
-      v[m].y = fma(rmu2, r[m].y, v[m].y);
-    });
+    int o = first_half(v, xv);
+    record(tag);
+    // w; its faces out
+    o = second_half(v, xv, o);
     if (g > 1) publish(v, tag, o);
     if (ZMEM) load(z, 3, o);
     if (g > 1 && wave < nw) collect(tag);
@@ -732,32 +833,16 @@ __device__ __forceinline__ void gang_run(const SysDesc* __restrict__ d, Scal* sc
       }
       return;
     }
-    gamma = red2[0].x;
-    double uu = red2[0].y;
-    for (int k = 1; k < nw; ++k) {
-      gamma += red2[k].x;
-      uu += red2[k].y;
-    }
+    double uu, beta, alpha;
+    totals(gamma, uu);
     // the stopping test of iteration it (at it = 0 the CG setup decided)
     if (it > 0 && (!(gamma > stop2) || it >= maxit)) {
       stopped = true;
       break;
     }
-    const double beta = it == 0 ? 0.0 : gamma / gamma_prev;
-    const double alpha = gamma / (uu + mu2 * gamma - (it == 0 ? 0.0 : beta * gamma / alpha_prev));
+    step_of(it, gamma, uu, beta, alpha);
     const R rb = (R)beta, ra = (R)alpha;
-    o = unseen();
-    gang_chunks<M, CH>(B.half, [&](int m) {
-      s[m].x = fma(rb, s[m].x, v[m].x);
-      s[m].y = fma(rb, s[m].y, v[m].y);
-      p[m].x = fma(rb, p[m].x, r[m].x);
-      p[m].y = fma(rb, p[m].y, r[m].y);
-      r[m].x = fma(-ra, s[m].x, r[m].x);
-      r[m].y = fma(-ra, s[m].y, r[m].y);
-      z[m].x = fma(ra, p[m].x, z[m].x);
-      z[m].y = fma(ra, p[m].y, z[m].y);
-      if (ZMEM) state.set(3 * svec + sown + (unsigned)o + m * kGangThreads * SZ, z[m]);
-    });
+    o = advance(v, rb, ra);
     put_own(r, o);
     if (g > 1)
       receive(tag, [&](int h, C w) {
@@ -796,6 +881,23 @@ __device__ __forceinline__ void gang_run(const SysDesc* __restrict__ d, Scal* sc
   }
 }
 
+// The body of the system's class.
+template <typename R, bool STEP>
+__device__ __forceinline__ void gang_bodies(const SysDesc* __restrict__ d, Scal* sc, int wg, int zslot, unsigned tag,
+                                            unsigned seq, unsigned arrived, int deny, int K, char* lds) {
+  static_assert(GangTab<float>::n == 7 && GangTab<double>::n == 4, "the cases below");
+  constexpr int last = GangTab<R>::n - 1;
+  switch (d->gang.cls) {
+    case 0: return gang_run<R, 0, false, STEP>(d, sc, wg, zslot, tag, seq, arrived, deny, K, lds);
+    case 1: return gang_run<R, 1, false, STEP>(d, sc, wg, zslot, tag, seq, arrived, deny, K, lds);
+    case 2: return gang_run<R, 2, false, STEP>(d, sc, wg, zslot, tag, seq, arrived, deny, K, lds);
+    case 3: return gang_run<R, 3, false, STEP>(d, sc, wg, zslot, tag, seq, arrived, deny, K, lds);
+    case 4: return gang_run<R, last < 4 ? last : 4, false, STEP>(d, sc, wg, zslot, tag, seq, arrived, deny, K, lds);
+    case 5: return gang_run<R, last < 5 ? last : 5, false, STEP>(d, sc, wg, zslot, tag, seq, arrived, deny, K, lds);
+    default: return gang_run<R, last, false, STEP>(d, sc, wg, zslot, tag, seq, arrived, deny, K, lds);
+  }
+}
+
 template <typename R>
 __global__ __launch_bounds__(kGangThreads) void k_gang(const SysDesc* __restrict__ sys, GangList L, int K) {
   extern __shared__ __attribute__((aligned(16))) char gang_mem_lds[];
@@ -808,52 +910,37 @@ __global__ __launch_bounds__(kGangThreads) void k_gang(const SysDesc* __restrict
   if (d->gang.g > 1 && threadIdx.x == 0)
     arrived = __hip_atomic_fetch_add((HUB_GAS unsigned*)d->gang_mem, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
   if (load_active(sc) != 1) return;
-  static_assert(GangTab<float>::n == 7 && GangTab<double>::n == 4, "the cases below");
-  constexpr int last = GangTab<R>::n - 1;
   const int zslot = L.pi[kk];
   const unsigned tag = L.tag[kk], seq = L.seq[kk];
   if (gang_solo<R>(d->gang, d->g.L1, d->g.L2, d->g.Nt)) {
     switch (d->gang.cls) {
-      case 0: return gang_run<R, 0, true>(d, sc, wg, zslot, tag, seq, arrived, K, gang_mem_lds);
-      case 1: return gang_run<R, 1, true>(d, sc, wg, zslot, tag, seq, arrived, K, gang_mem_lds);
-      default: return gang_run<R, 2, true>(d, sc, wg, zslot, tag, seq, arrived, K, gang_mem_lds);
+      case 0: return gang_run<R, 0, true, false>(d, sc, wg, zslot, tag, seq, arrived, 0, K, gang_mem_lds);
+      case 1: return gang_run<R, 1, true, false>(d, sc, wg, zslot, tag, seq, arrived, 0, K, gang_mem_lds);
+      default: return gang_run<R, 2, true, false>(d, sc, wg, zslot, tag, seq, arrived, 0, K, gang_mem_lds);
     }
   }
-  switch (d->gang.cls) {
-    case 0: return gang_run<R, 0, false>(d, sc, wg, zslot, tag, seq, arrived, K, gang_mem_lds);
-    case 1: return gang_run<R, 1, false>(d, sc, wg, zslot, tag, seq, arrived, K, gang_mem_lds);
-    case 2: return gang_run<R, 2, false>(d, sc, wg, zslot, tag, seq, arrived, K, gang_mem_lds);
-    case 3: return gang_run<R, 3, false>(d, sc, wg, zslot, tag, seq, arrived, K, gang_mem_lds);
-    case 4: return gang_run<R, last < 4 ? last : 4, false>(d, sc, wg, zslot, tag, seq, arrived, K, gang_mem_lds);
-    case 5: return gang_run<R, last < 5 ? last : 5, false>(d, sc, wg, zslot, tag, seq, arrived, K, gang_mem_lds);
-    default: return gang_run<R, last, false>(d, sc, wg, zslot, tag, seq, arrived, K, gang_mem_lds);
-  }
+  gang_bodies<R, false>(d, sc, wg, zslot, tag, seq, arrived, L.deny, K, gang_mem_lds);
 }
 
-// After the vectors of a system that leaves its gang are back in their slots: the per-tile
-// partials of |r_it|^2 that stage 1 of the tiled iteration sums, and no pending solution
-// update (z is complete).
+// One part of an iteration of every system of L (all of several workgroups).
 template <typename R>
-__global__ __launch_bounds__(kBlock) void k_gang_leave(const SysDesc* __restrict__ sys, int slot) {
-  using C = typename V2<R>::T;
-  const SysDesc* __restrict__ d = sys + slot;
-  const int tile = blockIdx.x, it = d->sc->git;
-  const int sg = tile / d->tnb, lo = sg * d->tseg + (tile - sg * d->tnb) * d->tbsz;
-  const int hi = min(lo + d->tbsz, (sg + 1) * d->tseg);
-  const Vec<C> r(d->vec[sizeof(R) == 4 ? (int)S_R32 : (int)S_R]);
-  R acc = 0;
-  for (int n = lo + threadIdx.x; n < hi; n += kBlock) {
-    const C v = r[n];
-    acc += v.x * v.x + v.y * v.y;
-  }
-  __shared__ R w[kBlock / 64];
-  acc = dpp_wave(acc);
-  if ((threadIdx.x & 63) == 63) w[threadIdx.x >> 6] = acc;
+__global__ __launch_bounds__(kGangThreads) void k_gang_step(const SysDesc* __restrict__ sys, GangList L, int part) {
+  extern __shared__ __attribute__((aligned(16))) char gang_mem_lds[];
+  const int kk = L.list[blockIdx.x], wg = L.wg[blockIdx.x];
+  if (kk == kGangNone) return;
+  const SysDesc* __restrict__ d = sys + L.sys[kk];
+  Scal* sc = L.scal + L.sys[kk];
+  // read once for the whole workgroup: others of the launch may write it
+  int* const active = reinterpret_cast<int*>(gang_mem_lds);
+  if (threadIdx.x == 0) *active = load_active(sc);
   __syncthreads();
-  if (threadIdx.x == 0) {
-    Real<double>(d->part2).set(tile, (double)((w[0] + w[1]) + (w[2] + w[3])));
-    if (tile == 0 && it > 0) d->sc->alpha[(it - 1) & 1] = 0.0;
+  const int a = *active;
+  __syncthreads();
+  if (part == kGangUpdate ? a == 0 : a != 1) {
+    if (a == 2 && wg == 0 && threadIdx.x == 0) store_active(sc, 0);
+    return;
   }
+  gang_bodies<R, true>(d, sc, wg, L.pi[kk], L.tag[kk], 0, 0, 0, part, gang_mem_lds);
 }
 
 __global__ __launch_bounds__(kBlock) void k_gang_clear(u64* p, size_t n) {
@@ -882,17 +969,26 @@ hipError_t launch_gang(const SysDesc* sys, const GangList& L, int K, bool single
   return single ? gang_launch<float>(sys, L, K, st, e0, e1) : gang_launch<double>(sys, L, K, st, e0, e1);
 }
 
-hipError_t launch_gang_leave(const SysDesc* sys, const GangList& L, int ntiles, bool single, hipStream_t st) {
-  if (L.nsys != 1 || L.nblock < 1 || L.nblock > kGangMaxWgs || ntiles < 1) return hipErrorInvalidValue;
-  // zero iterations: the state back to the slots (no workgroup waits for another)
-  const hipError_t e = single ? gang_launch<float>(sys, L, 0, st, nullptr, nullptr)
-                              : gang_launch<double>(sys, L, 0, st, nullptr, nullptr);
+template <typename R>
+static hipError_t gang_steps(const SysDesc* sys, GangList L, int K, hipStream_t st) {
+  const dim3 grid(L.nblock), block(kGangThreads);
+  const hipError_t e =
+      hipFuncSetAttribute((const void*)k_gang_step<R>, hipFuncAttributeMaxDynamicSharedMemorySize, kGangLdsBytes);
   if (e != hipSuccess) return e;
-  if (single)
-    hipLaunchKernelGGL(k_gang_leave<float>, dim3(ntiles), dim3(kBlock), 0, st, sys, L.sys[0]);
-  else
-    hipLaunchKernelGGL(k_gang_leave<double>, dim3(ntiles), dim3(kBlock), 0, st, sys, L.sys[0]);
+  hipLaunchKernelGGL(k_gang_step<R>, grid, block, kGangLdsBytes, st, sys, L, (int)kGangShare);
+  for (int k = 0; k < K; ++k) {
+    hipLaunchKernelGGL(k_gang_step<R>, grid, block, kGangLdsBytes, st, sys, L, (int)kGangSums);
+    hipLaunchKernelGGL(k_gang_step<R>, grid, block, kGangLdsBytes, st, sys, L, (int)kGangUpdate);
+    for (int q = 0; q < L.nsys; ++q) ++L.tag[q];
+  }
+  // also ends a system that the last update has stopped
+  hipLaunchKernelGGL(k_gang_step<R>, grid, block, kGangLdsBytes, st, sys, L, (int)kGangShare);
   return hipGetLastError();
+}
+
+hipError_t launch_gang_steps(const SysDesc* sys, const GangList& L, int K, bool single, hipStream_t st) {
+  if (L.nsys < 1 || L.nsys > kMaxSys || K < 1 || L.nblock < 1 || L.nblock > kGangMaxWgs) return hipErrorInvalidValue;
+  return single ? gang_steps<float>(sys, L, K, st) : gang_steps<double>(sys, L, K, st);
 }
 
 hipError_t launch_gang_clear(unsigned long long* mem, size_t words, hipStream_t st) {

@@ -68,8 +68,8 @@ struct Scal {
   int maxit;
   int active;     // CG: 1 iterating, 2 stopped by the last stage 1 (the next stage 2 sets 0), 0 stopped
   int git;        // gang CG: iterations done so far
-  int gang;       // gang CG, last launch: 0 ran, 1 nobody met in time, 2 a wait ran out, 3 refused (no room)
-  int pad;
+  int gang;       // gang CG, last launch: 0 ran, 1 nobody met in time, 2 a wait ran out, 3 refused (no room), 4 steps
+  int sit;        // gang CG in steps: iterations done when its current one began
 };
 
 // Per-system descriptor (device memory, written by the host when a system joins).
@@ -177,6 +177,7 @@ struct GangList {
   unsigned seq[kMaxSys];
   unsigned char list[kGangMaxWgs];
   unsigned char wg[kGangMaxWgs];
+  int deny;  // for tests: every gang of several workgroups is refused
 };
 
 // Tile class of a system: sites per thread of all its solver kernels.  Large systems
@@ -348,9 +349,9 @@ hipError_t launch_cg_stage(const SysDesc* sys, const LaunchList& L, bool single,
 // optional start/stop events.  At most kGangMaxWgs workgroups in all.
 hipError_t launch_gang(const SysDesc* sys, const GangList& L, int K, bool single, hipStream_t st,
                        hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
-// The one system of L goes on with the tiled kernels at the iteration its gang has reached:
-// the vectors back to their slots, and what stage 1 of the tiled iteration expects.
-hipError_t launch_gang_leave(const SysDesc* sys, const GangList& L, int ntiles, bool single, hipStream_t st);
+// K iterations of the CG of every system of L (gangs of several workgroups), cut into launches
+// in which no workgroup waits for another: the bits of launch_gang.  Uses K + 2 tags.
+hipError_t launch_gang_steps(const SysDesc* sys, const GangList& L, int K, bool single, hipStream_t st);
 // Exchange memory starts from zero (no tag is 0).
 hipError_t launch_gang_clear(unsigned long long* mem, size_t words, hipStream_t st);
 // Multi-shift CG: start (r = b, x = 0, x_s = 0, p_s = b, partial |b|^2), setup (one

@@ -20,6 +20,7 @@ struct Device {
   bool lose_flag = false;  // the sequence number of an Arnoldi step's publication does not arrive
   double resid2 = 9e-20;   // |b - A x|^2 that the next true residuals show (|b| = 1)
   int cgs = 0;             // second halves of Arnoldi steps so far
+  int steps = 0;           // blocks of a system in steps
   size_t freed = 0;        // hipFree calls
   std::function<void(const SysDesc*, const GangList&, int, bool)> gang;
 } dev;
@@ -86,7 +87,17 @@ hipError_t launch_stream_bytes(const double*, const double2*, double2*, int, int
 hipError_t launch_publish(const Publish& pub, hipStream_t) { return publish(pub), hipSuccess; }
 hipError_t launch_xupdate(const SysDesc*, const LaunchList&, const double*, int, bool, hipStream_t) { return hipSuccess; }
 hipError_t launch_gang_clear(unsigned long long*, size_t, hipStream_t) { return hipSuccess; }
-hipError_t launch_gang_leave(const SysDesc*, const GangList&, int, bool, hipStream_t) { return hipSuccess; }
+hipError_t launch_gang_steps(const SysDesc*, const GangList& L, int K, bool, hipStream_t) {
+  for (int k = 0; k < L.nsys; ++k) {
+    Scal& sc = L.scal[L.sys[k]];
+    if (sc.active != 1) continue;
+    sc.git += K;
+    sc.gang = 4;
+    ++dev.steps;
+    if (sc.git >= 100) stop(sc);
+  }
+  return hipSuccess;
+}
 hipError_t launch_cg_init_zero(const SysDesc*, const LaunchList& L, RedMode mode, const Publish& pub, hipStream_t) {
   for (int k = 0; k < L.nsys; ++k) {
     L.scal[L.sys[k]].red[0] = 1.0;
@@ -280,7 +291,39 @@ void gang_without_an_answer() {
   }
 }
 
+// A gang that is never met, or always refused, goes on in steps after a bounded number of
+// attempts, tries again ever more rarely, and its place in the next solve begins there.
+void gangs_that_never_meet() {
+  for (int outcome : {1, 3}) {
+    dev = Device{};
+    dev.resid2 = 0.0;
+    int tries = 0;
+    dev.gang = [&](const SysDesc*, const GangList& L, int, bool) {
+      for (int k = 0; k < L.nsys; ++k)
+        if (L.scal[L.sys[k]].active == 1) L.scal[L.sys[k]].gang = outcome, ++tries;
+    };
+    Pool pool(0, kPlenty);
+    Engine eng(&pool, nullptr);
+    for (int solve = 0; solve < 2; ++solve) {
+      System s = system_of(12, 12, 32, HUB_CG_FP64);
+      std::vector<void*> owned;
+      tries = dev.steps = 0;
+      CHECK(eng.add(&s) == Engine::ADD_OK);
+      CHECK(eng.join_gangs({&s}, owned) == hipSuccess);
+      CHECK(s.desc.gang.g > 1);
+      for (int k = 0; k < 100 && !s.done; ++k) CHECK(eng.step() == hipSuccess);
+      CHECK(s.done && s.status == HUB_OK);
+      CHECK(dev.steps == 7);  // 16 iterations each
+      // three and one on its way, then two after 1, 2 and 4 blocks; later fewer
+      CHECK(solve == 0 ? tries > kGangMisses && tries <= 10 : tries <= 4);
+      eng.remove(&s, &owned);
+      pool.release_all(owned, nullptr);
+    }
+  }
+}
+
 const std::map<std::string, void (*)()> scenarios = {
+    {"gangs_that_never_meet", gangs_that_never_meet},
     {"gang_without_an_answer", gang_without_an_answer},
     {"tables_of_fields", tables_of_fields},
     {"refusal_keeps_cache", refusal_keeps_cache},
