@@ -350,7 +350,9 @@ hub_status hub_hmc_trajectories(hub_ctx *ctx, const hub_lattice *lat, int32_t nc
  * dS/dphi, for its own lattice, phi and shift.  Requests are admitted by workspace
  * footprint against the budget as earlier ones retire and run batched with every
  * other request in flight, whatever their lattice sizes (continuous batching).  The
- * result of a request does not depend on which others share its launches.
+ * result of a request does not depend on which others share its launches or hold
+ * workspace: a request that fits in the budget together with the memory of its gang
+ * (its vectors on the chip) waits for both, one that does not never has a gang.
  * phi, chi, x_out, dSdphi_out: device memory that must stay valid and untouched
  * until hub_poll reports done.  S_out: host, written before done is reported.
  * dSdphi_out may be NULL (no force). */

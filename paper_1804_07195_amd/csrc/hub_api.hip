@@ -207,30 +207,18 @@ class Server {
           std::lock_guard<std::mutex> lk(mu_);
           t = tickets_[id];
         }
-        System& s = t->sys;
-        Ticket* tp = t.get();
-        s.on_done = [this, tp](System* sp) { complete(tp, sp); };
-        const Engine::AddResult ar = engine_->add(&s);
+        const AddResult ar = admit_one(t.get());
         if (ar == Engine::ADD_NO_ROOM) {
           back.push_back(id);  // retried once running requests release workspace or slots
-          continue;
-        }
-        if (ar != Engine::ADD_OK) {
+        } else if (ar != Engine::ADD_OK) {
           // a HIP failure while joining: the request ends with that status
           t->status = HUB_ERR_HIP;
           t->info = hub_solve_info{};
           t->state = 2;
-          continue;
+        } else {
+          t->state = 1;
+          running_.push_back(t);
         }
-        if (engine_->join_gangs({&s}, s.owned) != hipSuccess) {
-          engine_->remove(&s);
-          t->status = HUB_ERR_HIP;
-          t->info = hub_solve_info{};
-          t->state = 2;
-          continue;
-        }
-        t->state = 1;
-        running_.push_back(t);
       }
       if (!back.empty()) {
         std::lock_guard<std::mutex> lk(mu_);
@@ -244,11 +232,12 @@ class Server {
       if (engine_->step() != hipSuccess) {
         // a HIP failure: fail every running request
         for (auto& t : running_) {
+          if (t->state == 2) continue;
           t->sys.status = HUB_ERR_HIP;
           t->status = HUB_ERR_HIP;
           t->info = t->sys.info;
           t->info.converged = 0;
-          engine_->remove(&t->sys);
+          give_up(&t->sys);
           t->state = 2;
         }
         running_.clear();
@@ -273,8 +262,40 @@ class Server {
     if (r.S_out) *r.S_out = S;
     t->status = st;
     t->info = s->info;
-    engine_->remove(s);
+    give_up(s);
     t->state = 2;
+  }
+
+  // A request takes all that it iterates with, its gang's memory too, or waits: where both fit
+  // in the budget by themselves the gang iterates, whatever else is in flight.
+  using AddResult = Engine::AddResult;
+  AddResult admit_one(Ticket* t) {
+    Pool& pool = *ctx_->pool;
+    System& s = t->sys;
+    s.on_done = [this, t](System* sp) { complete(t, sp); };
+    s.ph64 = nullptr;
+    s.ph32 = nullptr;
+    const size_t ws = Engine::workspace_bytes(s.g, s.opts), gang = engine_->gang_bytes(s);
+    const bool by_gang = gang > 0 && ws + gang <= pool.budget();
+    ++pool.requests;
+    if (pool.waiting > 0 || pool.in_use() + ws + (by_gang ? gang : 0) > pool.budget()) {
+      --pool.requests;
+      return Engine::ADD_NO_ROOM;
+    }
+    AddResult ar = engine_->add(&s);
+    if (ar != Engine::ADD_OK) {
+      --pool.requests;
+      return ar;
+    }
+    bool room = true;
+    if (by_gang && engine_->join_gangs({&s}, s.owned, room) != hipSuccess) ar = Engine::ADD_HIP;
+    if (ar == Engine::ADD_OK && !room) ar = Engine::ADD_NO_ROOM;  // taken in between
+    if (ar != Engine::ADD_OK) give_up(&s);
+    return ar;
+  }
+  void give_up(System* s) {
+    engine_->remove(s);
+    --ctx_->pool->requests;
   }
 
   hub_ctx* ctx_;
@@ -539,8 +560,16 @@ hub_status run_solves(hub_ctx* ctx, std::vector<System>& sys, const hub_solve_op
   if (result == HUB_OK) {
     std::vector<System*> all;
     for (System& sy : sys) all.push_back(&sy);
-    const hipError_t e = eng->join_gangs(all, owned);
-    if (e != hipSuccess) result = hip_fail(e, "solve");
+    // room that served requests hold is waited for: they end without anything of this call
+    Pool& pool = *ctx->pool;
+    ++pool.waiting;
+    for (bool room = false, others = true; !room && others && result == HUB_OK;) {
+      others = pool.requests > 0;
+      const hipError_t e = eng->join_gangs(all, owned, room);
+      if (e != hipSuccess) result = hip_fail(e, "solve");
+      if (!room && others) std::this_thread::sleep_for(std::chrono::microseconds(50));
+    }
+    --pool.waiting;
   }
   if (result == HUB_OK) {
     for (;;) {

@@ -1,6 +1,7 @@
 // Host side of libhub: workspace pool and the batched solver engine.
 #pragma once
 
+#include <atomic>
 #include <complex>
 #include <cstdint>
 #include <deque>
@@ -34,6 +35,10 @@ class Pool {
   void release_all(const std::vector<void*>& ps, hipStream_t st);
   size_t budget() const { return budget_; }
   size_t in_use() const;
+  bool fits(size_t bytes) const;  // within the budget, now
+  // Served requests that hold workspace or are about to, and synchronous calls that wait for
+  // them to give it back; no request is admitted while one waits.
+  std::atomic<int> requests{0}, waiting{0};
   size_t reserved() const;
   // Bytes a request of this size takes from the budget (granularity rounding).
   static size_t rounded(size_t bytes);
@@ -131,10 +136,16 @@ class Engine {
   // the workspace is over budget; ADD_HIP: a HIP call failed while joining.
   enum AddResult { ADD_OK = 0, ADD_NO_ROOM = 1, ADD_HIP = 2 };
   AddResult add(System* s);
-  // Let the systems of v that have just been added iterate by gangs, where their lattice
-  // has a cut and the exchange memory (one block for all of v, appended to `owned`) fits in
-  // the budget; the others keep the tiled kernels.
-  hipError_t join_gangs(const std::vector<System*>& v, std::vector<void*>& owned);
+  // Bytes of the budget that a system like s takes for its gang (0: its lattice has no cut).
+  size_t gang_bytes(const System& s);
+  // Let the systems of v that have just been added iterate by gangs, where their lattice has a
+  // cut; their memory is one block, appended to `owned`.  room = false: the budget has none
+  // just now, nothing was done and the systems keep the tiled kernels.  They also do should
+  // the device be out of memory within the budget.  The kernels that iterate on a system, and
+  // with them its bits, must not depend on what else is in flight: the callers wait for room
+  // that others hold, and settle for the tiled kernels only where the system or the call does
+  // not fit by itself.
+  hipError_t join_gangs(const std::vector<System*>& v, std::vector<void*>& owned, bool& room);
   // Remove a finished system and return its workspace to the pool.
   // Takes s out; its workspace blocks go to `owned` if given (the caller releases them,
   // those of all its systems after one event), else back to the pool.

@@ -75,6 +75,11 @@ size_t Pool::in_use() const {
   return used_;
 }
 
+bool Pool::fits(size_t bytes) const {
+  std::lock_guard<std::mutex> lk(mu_);
+  return used_ + rounded(bytes) <= budget_;
+}
+
 size_t Pool::reserved() const {
   std::lock_guard<std::mutex> lk(mu_);
   return reserved_;
@@ -376,7 +381,7 @@ Engine::AddResult Engine::add(System* s) {
   }
   s->slot = slot;
   s->phase = PH_NEW;
-  s->done = false;
+  s->done = s->gang = false;
   s->info = hub_solve_info{};
   slots_[slot] = s;
   upload_desc(s);
@@ -393,19 +398,26 @@ GangCut Engine::cut_of(const Geom& g, bool single) {
   return cut_[k];
 }
 
-hipError_t Engine::join_gangs(const std::vector<System*>& v, std::vector<void*>& owned) {
-  auto exch = [](const GangCut& c, bool single) {
-    return single ? gang_exch_words<float>(c.g, c.nslot) : gang_exch_words<double>(c.g, c.nslot);
-  };
-  auto state = [](const GangCut& c, bool single) {
-    return single ? gang_state_words<float>(c.g, c.cls) : gang_state_words<double>(c.g, c.cls);
-  };
+// 8-byte words of a gang's exchange memory and of its state.
+static size_t exch(const GangCut& c, bool single) {
+  return single ? gang_exch_words<float>(c.g, c.nslot) : gang_exch_words<double>(c.g, c.nslot);
+}
+static size_t state(const GangCut& c, bool single) {
+  return single ? gang_state_words<float>(c.g, c.cls) : gang_state_words<double>(c.g, c.cls);
+}
+
+size_t Engine::gang_bytes(const System& s) {
+  const bool single = is_fgmres(s.opts);
+  const GangCut c = cut_of(s.g, single);
+  return c.g > 0 ? Pool::rounded((state(c, single) + (c.g > 1 ? exch(c, single) : 0)) * 8) : 0;
+}
+
+hipError_t Engine::join_gangs(const std::vector<System*>& v, std::vector<void*>& owned, bool& room) {
+  room = true;
   size_t words = 0, clear = 0;
   for (System* s : v) {
     const bool single = is_fgmres(s->opts);
     const GangCut c = cut_of(s->g, single);
-    s->desc.gang = c;
-    s->desc.gang_mem = s->desc.gang_state = nullptr;
     if (c.g > 1) clear += exch(c, single);
     if (c.g > 0) words += state(c, single);
   }
@@ -416,13 +428,17 @@ hipError_t Engine::join_gangs(const std::vector<System*>& v, std::vector<void*>&
       owned.push_back(mem);
       if (clear > 0) HUB_TRY(launch_gang_clear(mem, clear, st_));
     } else {
-      set_error("");  // over budget: these systems keep the tiled kernels
+      set_error("");
+      room = pool_->fits((clear + words) * 8);
+      if (!room) return hipSuccess;
     }
   }
   unsigned long long* st = mem + clear;
   for (System* s : v) {
     const bool single = is_fgmres(s->opts);
-    const GangCut c = s->desc.gang;
+    const GangCut c = cut_of(s->g, single);
+    s->desc.gang = c;
+    s->desc.gang_mem = s->desc.gang_state = nullptr;
     s->gang = c.g > 0 && mem;
     s->gang_tag = s->gang_seq = s->gang_decided = 0;
     s->gang_missed = s->gang_steps = s->gang_backoff = 0;

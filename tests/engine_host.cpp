@@ -1,13 +1,16 @@
 // Host check of the solver engine (csrc/hub_engine.hip) and the C ABI's drivers
 // (csrc/hub_api.hip) against a device that is played by this file: every launch takes effect at once, with numbers that lead the engine where the
 // scenario wants it.  Usage: engine_host <scenario>; exit 0: the engine did as it should.
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <functional>
 #include <map>
+#include <mutex>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "hub_engine.h"
@@ -23,6 +26,7 @@ struct Device {
   int steps = 0;           // blocks of a system in steps
   size_t freed = 0;        // hipFree calls
   std::function<void(const SysDesc*, const GangList&, int, bool)> gang;
+  std::function<void(const SysDesc&, Scal&)> tiled;  // a block of one system
 } dev;
 
 void publish(const Publish& pub, bool lose = false) {
@@ -132,12 +136,15 @@ hipError_t launch_gang(const SysDesc* sys, const GangList& L, int K, bool single
   for (int k = 0; k < L.nsys; ++k) stop(L.scal[L.sys[k]]);
   return hipSuccess;
 }
-static void tiled(const LaunchList& L) {
-  for (int k = 0; k < L.nsys; ++k) stop(L.scal[L.sys[k]]);
+hipError_t launch_cg_iter(const SysDesc* sys, const LaunchList& L, bool, hipStream_t) {
+  for (int k = 0; k < L.nsys; ++k) {
+    if (dev.tiled) dev.tiled(sys[L.sys[k]], L.scal[L.sys[k]]);
+    stop(L.scal[L.sys[k]]);
+  }
+  return hipSuccess;
 }
-hipError_t launch_cg_iter(const SysDesc*, const LaunchList& L, bool, hipStream_t) { return tiled(L), hipSuccess; }
-hipError_t launch_cg_stage(const SysDesc*, const LaunchList& L, bool, int, hipStream_t, hipEvent_t, hipEvent_t) {
-  return tiled(L), hipSuccess;
+hipError_t launch_cg_stage(const SysDesc* sys, const LaunchList& L, bool single, int, hipStream_t st, hipEvent_t, hipEvent_t) {
+  return launch_cg_iter(sys, L, single, st);
 }
 }  // namespace hub
 
@@ -237,6 +244,29 @@ void tables_of_fields() {
       }
 }
 
+// One request on buffers of its own.
+struct Request {
+  hub_request r{};
+  std::vector<double> phi;
+  std::vector<hub_c128> chi, x;
+  uint64_t ticket = 0;
+  Request(int L1, int L2, int Nt, double mu2, hub_solver solver) {
+    r.lat.L1 = L1, r.lat.L2 = L2, r.lat.Nt = Nt, r.lat.kappa_t = 0.2;
+    r.mu2 = mu2;
+    const size_t n = 2 * (size_t)L1 * L2 * Nt;
+    phi.resize(n), chi.resize(n), x.resize(n);
+    r.phi = phi.data(), r.chi = chi.data(), r.x_out = x.data();
+    r.opts = options(solver);
+  }
+  void submit(hub_ctx* ctx) { CHECK(hub_submit(ctx, &r, &ticket) == HUB_OK); }
+  hub_status wait(hub_ctx* ctx) {
+    int32_t done = 0;
+    hub_status st = HUB_OK;
+    while (!done) st = hub_poll(ctx, ticket, &done, nullptr);
+    return st;
+  }
+};
+
 // A gang whose wait runs out ends its own system; the others, of the same call or of other
 // requests, are solved.
 void gang_without_an_answer() {
@@ -257,7 +287,8 @@ void gang_without_an_answer() {
       std::vector<void*> owned;
       s[0].mu2 = 0.5;
       for (System& q : s) CHECK(eng.add(&q) == Engine::ADD_OK);
-      CHECK(eng.join_gangs({&s[0], &s[1]}, owned) == hipSuccess);
+      bool room = false;
+      CHECK(eng.join_gangs({&s[0], &s[1]}, owned, room) == hipSuccess && room);
       int ended = 0;
       for (System& q : s) q.on_done = [&](System*) { ++ended; };
       for (int k = 0; k < 50 && !(s[0].done && s[1].done); ++k) CHECK(eng.step() == hipSuccess);
@@ -268,25 +299,10 @@ void gang_without_an_answer() {
     // requests, of other lattices too
     hub_ctx* ctx = nullptr;
     CHECK(hub_create(&ctx, 0, 0) == HUB_OK);
-    std::vector<std::vector<hub_c128>> x(6);
-    std::vector<double> phi(100000);
-    std::vector<hub_c128> chi(100000);
-    std::vector<uint64_t> ticket(6);
-    for (int k = 0; k < 6; ++k) {
-      hub_request r{};
-      r.lat.L1 = 4 + k, r.lat.L2 = 5, r.lat.Nt = 8, r.lat.kappa_t = 0.2;
-      r.mu2 = k == 2 ? 0.5 : 0.1;
-      x[k].resize(2 * r.lat.L1 * r.lat.L2 * r.lat.Nt);
-      r.phi = phi.data(), r.chi = chi.data(), r.x_out = x[k].data();
-      r.opts = options(solver);
-      CHECK(hub_submit(ctx, &r, &ticket[k]) == HUB_OK);
-    }
-    for (int k = 0; k < 6; ++k) {
-      int32_t done = 0;
-      hub_status st = HUB_OK;
-      while (!done) st = hub_poll(ctx, ticket[k], &done, nullptr);
-      CHECK(st == (k == 2 ? HUB_ERR_HIP : HUB_OK));
-    }
+    std::vector<Request> rs;
+    for (int k = 0; k < 6; ++k) rs.emplace_back(4 + k, 5, 8, k == 2 ? 0.5 : 0.1, solver);
+    for (Request& r : rs) r.submit(ctx);
+    for (int k = 0; k < 6; ++k) CHECK(rs[k].wait(ctx) == (k == 2 ? HUB_ERR_HIP : HUB_OK));
     CHECK(hub_destroy(ctx) == HUB_OK);
   }
 }
@@ -309,7 +325,8 @@ void gangs_that_never_meet() {
       std::vector<void*> owned;
       tries = dev.steps = 0;
       CHECK(eng.add(&s) == Engine::ADD_OK);
-      CHECK(eng.join_gangs({&s}, owned) == hipSuccess);
+      bool room = false;
+      CHECK(eng.join_gangs({&s}, owned, room) == hipSuccess && room);
       CHECK(s.desc.gang.g > 1);
       for (int k = 0; k < 100 && !s.done; ++k) CHECK(eng.step() == hipSuccess);
       CHECK(s.done && s.status == HUB_OK);
@@ -322,7 +339,83 @@ void gangs_that_never_meet() {
   }
 }
 
+// Which kernels iterate on a request depends on the request and the budget, not on what else
+// is in flight: it is the same alone and in company, for budgets from one workspace to plenty.
+void kernels_by_request() {
+  std::mutex mu;
+  std::map<double, std::string> path;  // of the request with that shift
+  std::map<double, int> launches;
+  auto note = [&](double mu2, const char* what) {
+    std::lock_guard<std::mutex> lk(mu);
+    if (path[mu2].find(what) == std::string::npos) path[mu2] += what;
+  };
+  for (hub_solver solver : {HUB_CG_FP64, HUB_FGMRES_MIXED}) {
+    const System s = system_of(12, 12, 32, solver);
+    const size_t ws = Engine::workspace_bytes(s.g, s.opts);
+    Pool pool(0, kPlenty);
+    const size_t gang = Engine(&pool, nullptr).gang_bytes(s);
+    bool seen[2] = {false, false};
+    for (double part : {1.0, 1.2, 1.5, 2.0, 2.5, 3.0, 3.7, 4.0, 5.0, 100.0}) {
+      dev = Device{};
+      dev.resid2 = 0.0;
+      dev.tiled = [&](const SysDesc& d, Scal& sc) {
+        if (sc.active) note(d.mu2, "tiled ");
+      };
+      dev.gang = [&](const SysDesc* sys, const GangList& L, int, bool) {
+        for (int k = 0; k < L.nsys; ++k) {
+          const double m = sys[L.sys[k]].mu2;
+          if (L.scal[L.sys[k]].active) note(m, "gang ");
+          if (++launches[m] % 20 == 0) stop(L.scal[L.sys[k]]);  // in flight for some while
+        }
+      };
+      std::string alone;
+      for (int company : {1, 4}) {
+        path.clear();
+        hub_ctx* ctx = nullptr;
+        CHECK(hub_create(&ctx, 0, (size_t)(part * (double)ws)) == HUB_OK);
+        std::vector<Request> rs;
+        for (int k = 0; k < company; ++k) rs.emplace_back(12, 12, 32, 0.1 + k, solver);
+        for (Request& r : rs) r.submit(ctx);
+        for (Request& r : rs) CHECK(r.wait(ctx) == HUB_OK);
+        CHECK(hub_destroy(ctx) == HUB_OK);
+        if (company == 1) alone = path[0.1];
+        CHECK(alone == "gang " || alone == "tiled ");
+        for (const Request& r : rs) CHECK(path[r.r.mu2] == alone);
+      }
+      seen[alone == "gang "] = true;
+    }
+    CHECK(seen[0] && seen[1]);
+    // a call beside a served request that holds most of the budget
+    dev = Device{};
+    dev.resid2 = 0.0;
+    path.clear();
+    std::atomic<int> served{0};
+    dev.tiled = [&](const SysDesc& d, Scal& sc) {
+      if (sc.active) note(d.mu2, "tiled ");
+    };
+    dev.gang = [&](const SysDesc* sys, const GangList& L, int, bool) {
+      for (int k = 0; k < L.nsys; ++k) {
+        const double m = sys[L.sys[k]].mu2;
+        note(m, "gang ");
+        if (m == 0.7 || ++served > 2000) stop(L.scal[L.sys[k]]);
+      }
+    };
+    hub_ctx* ctx = nullptr;
+    CHECK(hub_create(&ctx, 0, 2 * ws + gang) == HUB_OK);
+    Request r(12, 12, 32, 0.1, solver);
+    r.submit(ctx);
+    while (served == 0) std::this_thread::yield();
+    Request c(12, 12, 32, 0.7, solver);
+    hub_solve_info info;
+    CHECK(hub_solve(ctx, &c.r.lat, c.r.phi, &c.r.mu2, 1, c.r.chi, c.r.x_out, &c.r.opts, &info, nullptr) == HUB_OK);
+    CHECK(path[0.7] == "gang ");
+    CHECK(r.wait(ctx) == HUB_OK);
+    CHECK(hub_destroy(ctx) == HUB_OK);
+  }
+}
+
 const std::map<std::string, void (*)()> scenarios = {
+    {"kernels_by_request", kernels_by_request},
     {"gangs_that_never_meet", gangs_that_never_meet},
     {"gang_without_an_answer", gang_without_an_answer},
     {"tables_of_fields", tables_of_fields},
