@@ -3,11 +3,13 @@
 
 #include <atomic>
 #include <complex>
+#include <condition_variable>
 #include <cstdint>
 #include <deque>
 #include <functional>
 #include <map>
 #include <mutex>
+#include <set>
 #include <string>
 #include <unordered_map>
 #include <vector>
@@ -34,6 +36,7 @@ class Pool {
   // Release several blocks after the same stream work: one event orders all of them.
   void release_all(const std::vector<void*>& ps, hipStream_t st);
   size_t budget() const { return budget_; }
+  int device() const { return device_; }
   size_t in_use() const;
   bool fits(size_t bytes) const;  // within the budget, now
   // Served requests that hold workspace or are about to, and synchronous calls that wait for
@@ -68,6 +71,27 @@ class Pool {
   std::map<size_t, std::deque<Block>> free_;
   std::unordered_map<void*, size_t> live_;
   mutable std::mutex mu_;
+};
+
+// The workgroups of gangs that the engines of this process may have on one device at a time,
+// handed out in the order of asking.  An engine holds its share from before a block of gang
+// launches to the last of them that was read back; while another one waits it launches none
+// ahead and asks anew for each block.  (Left to the refusals on the device, a gang of all
+// CUs gets in only where a launch of another context happens not to follow the last one.)
+class GangTurns {
+ public:
+  static GangTurns& of(int device);
+  // False after a second: whoever holds the others has other troubles, the device decides.
+  bool take(int wgs);
+  void give(int wgs);
+  bool wanted() const { return asked_.load() != served_.load(); }
+
+ private:
+  std::mutex mu_;
+  std::condition_variable cv_;
+  int held_ = 0;
+  std::atomic<unsigned> asked_{0}, served_{0};
+  std::set<unsigned> left_;  // askers that gave up before their turn
 };
 
 // Block length (CG iterations between flag reads) near a system's expected end.
@@ -152,7 +176,11 @@ class Engine {
   void remove(System* s, std::vector<void*>* owned = nullptr);
   // Advance every system: host-side phases, then one block of CG iterations.
   // Returns the HIP error if any.
-  hipError_t step();
+  hipError_t step() {
+    const hipError_t e = advance();
+    if (e != hipSuccess || (inflight_[0].empty() && inflight_[1].empty())) end_turn();
+    return e;
+  }
   bool idle() const;
   int count() const;
   hipStream_t stream() const { return st_; }
@@ -199,6 +227,9 @@ class Engine {
   hipError_t wait_block(unsigned seq);
   hipError_t launch_gangs(const std::vector<System*>& v, bool single, Block& b);
   bool gang_entry(GangList& G, int (&taken)[kNumXcd], System* s, bool single) const;
+  hipError_t advance();
+  hipError_t begin_turn(bool single);
+  void end_turn();
   hipError_t take_event(std::vector<hipEvent_t>& dst);
   GangCut cut_of(const Geom& g, bool single);
   hipError_t read_scal(const std::vector<System*>& v);
@@ -244,6 +275,8 @@ class Engine {
   // The smallest gang that went on in steps lately, and for how many blocks: where the CUs are
   // taken for long, the systems of the next solve begin with that.
   int tight_g_ = kGangMaxWgs + 1, tight_backoff_ = 0;
+  GangTurns& turns_;
+  int turn_ = 0;  // workgroups it holds there
   unsigned gang_launches_ = 0;
   unsigned deny_ = 0;
   int next_buf_[2] = {0, 0};

@@ -3,6 +3,7 @@
 // of Appendix A (Algorithm A.1) for many systems at once, and the small Hessenberg
 // least-squares problem of the FGMRES update.
 #include <algorithm>
+#include <chrono>
 #include <map>
 #include <cmath>
 #include <cstring>
@@ -230,7 +231,40 @@ enum Phase : int {
 
 constexpr size_t kScalBytes = sizeof(Scal) * kMaxSys + sizeof(unsigned) * kScalCounters;
 
-Engine::Engine(Pool* pool, hipStream_t st) : pool_(pool), st_(st), slots_(kMaxSys, nullptr) {
+GangTurns& GangTurns::of(int device) {
+  static std::mutex& mu = *new std::mutex;  // never destroyed: engines may outlive statics
+  static auto& all = *new std::map<int, GangTurns>;
+  std::lock_guard<std::mutex> lk(mu);
+  return all[device];
+}
+
+bool GangTurns::take(int wgs) {
+  std::unique_lock<std::mutex> lk(mu_);
+  const unsigned my = asked_++;
+  auto mine = [&] {
+    while (left_.erase(served_)) ++served_;
+    return served_ == my && held_ + wgs <= kGangMaxWgs;
+  };
+  const bool got = cv_.wait_for(lk, std::chrono::seconds(1), mine);
+  if (got) {
+    held_ += wgs;
+    ++served_;
+  } else {
+    left_.insert(my);
+    while (left_.erase(served_)) ++served_;
+  }
+  cv_.notify_all();
+  return got;
+}
+
+void GangTurns::give(int wgs) {
+  std::lock_guard<std::mutex> lk(mu_);
+  held_ -= wgs;
+  cv_.notify_all();
+}
+
+Engine::Engine(Pool* pool, hipStream_t st)
+    : pool_(pool), st_(st), slots_(kMaxSys, nullptr), turns_(GangTurns::of(pool->device())) {
   ok_ = hipMalloc(&d_desc_, sizeof(SysDesc) * kMaxSys) == hipSuccess &&
         hipHostMalloc(&h_desc_, sizeof(SysDesc) * kMaxSys, hipHostMallocDefault) == hipSuccess &&
         hipMalloc(&d_y_, sizeof(double) * kYStride * kMaxSys) == hipSuccess &&
@@ -260,6 +294,7 @@ Engine::~Engine() {
   for (hipEvent_t e : events_) (void)hipEventDestroy(e);
   for (System* s : slots_)
     if (s) remove(s);
+  end_turn();
   if (d_desc_) (void)hipFree(d_desc_);
   if (h_desc_) (void)hipHostFree(h_desc_);
   if (d_y_) (void)hipFree(d_y_);
@@ -470,6 +505,7 @@ void Engine::remove(System* s, std::vector<void*>* owned) {
     for (auto& b : q) (void)finish_block(b);
     q.clear();
   }
+  if (inflight_[0].empty() && inflight_[1].empty()) end_turn();
   if (s->slot >= 0 && slots_[s->slot] == s) slots_[s->slot] = nullptr;
   if (owned)
     owned->insert(owned->end(), s->owned.begin(), s->owned.end());
@@ -1006,10 +1042,41 @@ hipError_t Engine::launch_gangs(const std::vector<System*>& v, bool single, Bloc
   return hipSuccess;
 }
 
+void Engine::end_turn() {
+  if (turn_ > 0) turns_.give(turn_);
+  turn_ = 0;
+}
+
+// Before gangs are launched in the given precision: the turn for them.  One that is held goes
+// on, unless it is too small now or another engine waits; then what is in flight is read back
+// first.
+hipError_t Engine::begin_turn(bool single) {
+  auto need = [&] {
+    int wgs = 0;
+    for (System* s : slots_)
+      if (s && !s->done && s->gang && s->gang_steps == 0 && s->phase == (single ? (int)PH_F_INNER : (int)PH_CG_ITER))
+        wgs += s->desc.gang.g > 1 ? s->desc.gang.g : 0;
+    return std::min(wgs, kGangMaxWgs);
+  };
+  int wgs = need();
+  if (wgs == 0) return hipSuccess;
+  if (turn_ > 0 && (turn_ < wgs || turns_.wanted())) {
+    for (auto& q : inflight_) {
+      for (auto& b : q) HUB_TRY(finish_block(b));
+      q.clear();
+    }
+    end_turn();
+    wgs = need();
+  }
+  if (turn_ == 0 && wgs > 0 && turns_.take(wgs)) turn_ = wgs;
+  return hipSuccess;
+}
+
 // Enqueue one block of CG iterations over every system that is iterating in the
 // given precision, followed by an asynchronous read-back of their flags.
 hipError_t Engine::launch_block(bool single, bool& launched) {
   launched = false;
+  HUB_TRY(begin_turn(single));
   std::vector<System*> v, gangs;
   int k = 1 << 30;
   for (System* s : slots_) {
@@ -1208,7 +1275,7 @@ hipError_t Engine::finish_block(Block& b) {
   return hipSuccess;
 }
 
-hipError_t Engine::step() {
+hipError_t Engine::advance() {
   // 0. descriptors of systems added since the last step
   HUB_TRY(flush_desc());
   // 1. keep the GPU busy: enqueue the next block for every system still iterating

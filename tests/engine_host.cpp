@@ -24,6 +24,7 @@ struct Device {
   double resid2 = 9e-20;   // |b - A x|^2 that the next true residuals show (|b| = 1)
   int cgs = 0;             // second halves of Arnoldi steps so far
   int steps = 0;           // blocks of a system in steps
+  bool fail = false;       // launches of gangs fail
   size_t freed = 0;        // hipFree calls
   std::function<void(const SysDesc*, const GangList&, int, bool)> gang;
   std::function<void(const SysDesc&, Scal&)> tiled;  // a block of one system
@@ -132,6 +133,7 @@ hipError_t launch_cgs(const SysDesc*, const LaunchList& L, int j, const Publish&
   return publish(pub, dev.lose_flag), hipSuccess;
 }
 hipError_t launch_gang(const SysDesc* sys, const GangList& L, int K, bool single, hipStream_t, hipEvent_t, hipEvent_t) {
+  if (dev.fail) return hipErrorLaunchFailure;
   if (dev.gang) return dev.gang(sys, L, K, single), hipSuccess;
   for (int k = 0; k < L.nsys; ++k) stop(L.scal[L.sys[k]]);
   return hipSuccess;
@@ -414,7 +416,81 @@ void kernels_by_request() {
   }
 }
 
+// Turns are taken in the order of asking, as many at once as fit; an engine at work gives its
+// own up when another one waits, after a block or two, and when a step fails.
+void turns() {
+  GangTurns& t = GangTurns::of(7);
+  CHECK(t.take(100) && t.take(100) && !t.wanted());
+  std::mutex mu;
+  std::string order;
+  std::vector<std::thread> ts;
+  auto ask = [&](char name, int wgs) {
+    const bool before = t.wanted();
+    ts.emplace_back([&, name, wgs] {
+      CHECK(t.take(wgs));
+      std::lock_guard<std::mutex> lk(mu);
+      order += name;
+    });
+    while (!before && !t.wanted()) std::this_thread::yield();
+    std::this_thread::sleep_for(std::chrono::milliseconds(20));
+  };
+  ask('a', 256);
+  ask('b', 10);  // would fit, but came later
+  CHECK(order.empty());
+  t.give(100);
+  t.give(100);
+  while (order.size() < 1) std::this_thread::yield();
+  CHECK(order == "a");
+  t.give(256);
+  for (std::thread& x : ts) x.join();
+  CHECK(order == "ab" && !t.wanted());
+  CHECK(!t.take(250));  // a second later: without
+  CHECK(t.take(246) && !t.wanted());
+  t.give(246);
+  t.give(10);
+
+  Pool pool(0, kPlenty);
+  for (bool fails : {false, true}) {
+    dev = Device{};
+    dev.resid2 = 0.0;
+    std::atomic<int> launches{0};
+    dev.gang = [&](const SysDesc*, const GangList&, int, bool) { ++launches; };  // never stops
+    Engine eng(&pool, nullptr);
+    System s = system_of(48, 48, 64, HUB_CG_FP64);
+    std::vector<void*> owned;
+    bool room = false;
+    CHECK(eng.add(&s) == Engine::ADD_OK);
+    CHECK(eng.join_gangs({&s}, owned, room) == hipSuccess && room && s.desc.gang.g == kGangMaxWgs);
+    for (int k = 0; k < 10; ++k) CHECK(eng.step() == hipSuccess);
+    GangTurns& u = GangTurns::of(0);
+    CHECK(!u.wanted());
+    std::atomic<bool> got{false};
+    std::thread other([&] {
+      CHECK(u.take(1));
+      got = true;
+      u.give(1);
+    });
+    while (!u.wanted() && !got) std::this_thread::yield();
+    const int before = launches;
+    if (fails) {
+      dev.fail = true;
+      CHECK(eng.step() != hipSuccess);
+    } else {
+      CHECK(eng.step() == hipSuccess);
+      CHECK(eng.step() == hipSuccess);
+    }
+    other.join();
+    CHECK(got && launches <= before + 2);
+    dev.fail = false;
+    eng.remove(&s, &owned);
+    pool.release_all(owned, nullptr);
+    CHECK(u.take(kGangMaxWgs));  // nothing is left behind
+    u.give(kGangMaxWgs);
+  }
+}
+
 const std::map<std::string, void (*)()> scenarios = {
+    {"turns", turns},
     {"kernels_by_request", kernels_by_request},
     {"gangs_that_never_meet", gangs_that_never_meet},
     {"gang_without_an_answer", gang_without_an_answer},
