@@ -84,6 +84,8 @@ class GangTurns {
   // False after a second: whoever holds the others has other troubles, the device decides.
   bool take(int wgs);
   void give(int wgs);
+  // So many beside those held, if nobody waits and they are free.
+  bool add(int wgs);
   bool wanted() const { return asked_.load() != served_.load(); }
 
  private:

@@ -257,6 +257,13 @@ bool GangTurns::take(int wgs) {
   return got;
 }
 
+bool GangTurns::add(int wgs) {
+  std::lock_guard<std::mutex> lk(mu_);
+  if (wanted() || held_ + wgs > kGangMaxWgs) return false;
+  held_ += wgs;
+  return true;
+}
+
 void GangTurns::give(int wgs) {
   std::lock_guard<std::mutex> lk(mu_);
   held_ -= wgs;
@@ -1060,6 +1067,7 @@ hipError_t Engine::begin_turn(bool single) {
   };
   int wgs = need();
   if (wgs == 0) return hipSuccess;
+  if (turn_ > 0 && turn_ < wgs && turns_.add(wgs - turn_)) turn_ = wgs;
   if (turn_ > 0 && (turn_ < wgs || turns_.wanted())) {
     for (auto& q : inflight_) {
       for (auto& b : q) HUB_TRY(finish_block(b));
