@@ -234,6 +234,7 @@ class Engine {
   void end_turn();
   hipError_t take_event(std::vector<hipEvent_t>& dst);
   GangCut cut_of(const Geom& g, bool single);
+  void look_at_device();
   hipError_t read_scal(const std::vector<System*>& v);
   // The publication of the Scal records of v at the end of a following launch, and the wait
   // for it (h_scal_ holds the records then).
@@ -274,6 +275,7 @@ class Engine {
   unsigned blk_seq_ = 0;
   GangCut cut_[2] = {};                 // the last cut computed per precision, of extents cut_ext_
   int cut_ext_[2][3] = {};
+  bool all_cus_ = true;  // the stream has the CUs that gangs of several workgroups count on
   // The smallest gang that went on in steps lately, and for how many blocks: where the CUs are
   // taken for long, the systems of the next solve begin with that.
   int tight_g_ = kGangMaxWgs + 1, tight_backoff_ = 0;

@@ -430,6 +430,22 @@ Engine::AddResult Engine::add(System* s) {
   return ADD_OK;
 }
 
+// A stream with fewer CUs than a gang launch may have workgroups (a mask, a partition of the
+// device) would miss its meetings: there, only systems of one workgroup have a gang.
+void Engine::look_at_device() {
+  constexpr int kWords = 32;
+  uint32_t mask[kWords] = {0};
+  int cus = 0, masked = 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, pool_->device()) != hipSuccess) cus = 0;
+  if (hipExtStreamGetCUMask(st_, kWords, mask) == hipSuccess) {
+    for (uint32_t m : mask) masked += __builtin_popcount(m);
+    cus = std::min(cus, masked);
+  } else {
+    (void)hipGetLastError();
+  }
+  all_cus_ = cus >= kGangMaxWgs;
+}
+
 GangCut Engine::cut_of(const Geom& g, bool single) {
   const int k = single ? 1 : 0;
   int* e = cut_ext_[k];
@@ -437,7 +453,7 @@ GangCut Engine::cut_of(const Geom& g, bool single) {
     cut_[k] = single ? gang_cut<float>(g.L1, g.L2, g.Nt) : gang_cut<double>(g.L1, g.L2, g.Nt);
     e[0] = g.L1, e[1] = g.L2, e[2] = g.Nt;
   }
-  return cut_[k];
+  return all_cus_ || cut_[k].g == 1 ? cut_[k] : GangCut{};
 }
 
 // 8-byte words of a gang's exchange memory and of its state.
@@ -449,6 +465,7 @@ static size_t state(const GangCut& c, bool single) {
 }
 
 size_t Engine::gang_bytes(const System& s) {
+  look_at_device();
   const bool single = is_fgmres(s.opts);
   const GangCut c = cut_of(s.g, single);
   return c.g > 0 ? Pool::rounded((state(c, single) + (c.g > 1 ? exch(c, single) : 0)) * 8) : 0;
@@ -456,6 +473,7 @@ size_t Engine::gang_bytes(const System& s) {
 
 hipError_t Engine::join_gangs(const std::vector<System*>& v, std::vector<void*>& owned, bool& room) {
   room = true;
+  look_at_device();
   size_t words = 0, clear = 0;
   for (System* s : v) {
     const bool single = is_fgmres(s->opts);

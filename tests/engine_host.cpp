@@ -25,6 +25,7 @@ struct Device {
   int cgs = 0;             // second halves of Arnoldi steps so far
   int steps = 0;           // blocks of a system in steps
   bool fail = false;       // launches of gangs fail
+  int cus = 256, masked = 256;  // of the device, of the stream
   size_t freed = 0;        // hipFree calls
   std::function<void(const SysDesc*, const GangList&, int, bool)> gang;
   std::function<void(const SysDesc&, Scal&)> tiled;  // a block of one system
@@ -59,6 +60,12 @@ hipError_t hipGetSymbolAddress(void** p, const void* s) { return *p = (void*)s, 
 const char* hipGetErrorString(hipError_t) { return "an error"; }
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { return *s = (hipStream_t)std::malloc(1), hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t s) { return std::free((void*)s), hipSuccess; }
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { return *v = dev.cus, hipSuccess; }
+hipError_t hipExtStreamGetCUMask(hipStream_t, uint32_t n, uint32_t* mask) {
+  for (uint32_t k = 0; k < n; ++k) mask[k] = 0;
+  for (int k = 0; k < dev.masked; ++k) mask[k / 32] |= 1u << k % 32;
+  return hipSuccess;
+}
 hipError_t hipStreamQuery(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipSetDevice(int) { return hipSuccess; }
@@ -489,7 +496,31 @@ void turns() {
   }
 }
 
+// Without the CUs for a full launch a system of several workgroups has no gang; one engine
+// sees its stream change (the handle may be another stream's by the next call).
+void cus_of_the_stream() {
+  Pool pool(0, kPlenty);
+  dev = Device{};
+  Engine eng(&pool, nullptr);
+  for (auto c : {std::pair<int, int>{256, 256}, {256, 255}, {32, 32}, {256, 256}, {304, 304}}) {
+    dev.cus = c.first, dev.masked = c.second;
+    for (int L : {6, 12}) {
+      System s = system_of(L, L, L == 6 ? 16 : 32, HUB_FGMRES_MIXED);
+      std::vector<void*> owned;
+      bool room = false;
+      const bool want = L == 6 || c.second >= 256;
+      CHECK((eng.gang_bytes(s) > 0) == want);
+      CHECK(eng.add(&s) == Engine::ADD_OK);
+      CHECK(eng.join_gangs({&s}, owned, room) == hipSuccess && room);
+      CHECK(s.gang == want && (s.desc.gang.g == 1) == (L == 6));
+      eng.remove(&s, &owned);
+      pool.release_all(owned, nullptr);
+    }
+  }
+}
+
 const std::map<std::string, void (*)()> scenarios = {
+    {"cus_of_the_stream", cus_of_the_stream},
     {"turns", turns},
     {"kernels_by_request", kernels_by_request},
     {"gangs_that_never_meet", gangs_that_never_meet},
