@@ -98,9 +98,14 @@ class GangTurns {
 
 // Block length (CG iterations between flag reads) near a system's expected end.
 constexpr int kTailBlock = 4;
-// Iterations of a gang launch (a gang leaves its launch at convergence): a system that has
-// stopped waits for the others of its launch, and only with others; a launch costs 12 us
-// (6x6x16) to 32 us (102x102x64) before its first iteration.
+// Iterations of a gang launch (a gang leaves its launch at convergence), and of one that holds
+// a single system.  The launches of a stream follow one another, so a system that has stopped
+// waits for the rest of its launch and for the other launches of the engine, two blocks of
+// them where one is ahead; a launch costs 12 us (6x6x16) to 32 us (102x102x64) before its
+// first iteration.  With 128 for every launch of the server, a request of 6x6x16 that comes
+// while another one runs took 3.54 ms instead of 3.77 beside 24x24x64 (mixed; FP64 3.32 and
+// 4.01), 12.6 instead of 12.3 beside three of 48x48x64 and 9.5 in both beside 102x102x64,
+// and the requests together 2 to 3% longer.
 constexpr int kGangIters = 128, kGangItersAlone = 512;
 // Meetings in a row that a gang may miss (or be refused) before it goes on in steps; and how:
 // blocks of so many iterations, one of them before the next attempt to meet, twice as many
