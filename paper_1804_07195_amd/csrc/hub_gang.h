@@ -299,10 +299,12 @@ inline double gang_cost(const GangBlock& B, int cls, int g) {
 // The cut of a lattice; g = 0: none fits.  It depends on the lattice alone, so that a
 // system's results do not depend on what it shares a launch with: the shortest iteration
 // among the cuts whose workgroups times their time, per site, stay below what a launch full
-// of such systems may take.  The bounds are the device time per site and iteration of the
-// kernels that a batch would otherwise run on: the tiled iteration at a full device (88 and
-// 184 bytes per site at 5 TB/s over 256 CUs, less a fifth), and for complex64 systems of
-// up to 10,200 sites one workgroup per system (7.1 us at 9,216 sites) with 64 systems.
+// of such systems may take: the tiled iteration at a full device (88 and 184 bytes per site
+// at 5 TB/s over 256 CUs), less a fifth.  Up to 10,200 complex64 sites a smaller bound keeps
+// gangs of four, of which 64, the largest batch, are one launch: 9x6x58 takes 3.68 us an
+// iteration alone, 0.245 per system for 16 and 0.065 for 64 with it, and 2.50, 0.172 and 0.088
+// with eight workgroups, as the larger bound has it (9x9x40: 3.47, 0.232, 0.062; 2.62, 0.180,
+// 0.092).
 template <typename R>
 inline GangCut gang_cut(int L1, int L2, int Nt) {
   const double n = 2.0 * L1 * L2 * Nt;
@@ -318,8 +320,9 @@ inline GangCut gang_cut(int L1, int L2, int Nt) {
         const int cls = gang_class<R>(B);
         if (cls < 0) continue;
         // a fifth more where the gangs of a full launch leave CUs over (sixteen systems of
-        // 18 workgroups take two launches, of 16 workgroups one); a cut beyond its room
-        // counts by how far it is beyond
+        // 18 workgroups take two launches, of 16 workgroups one: FP64 12x23x15 alone 3.70 us
+        // with it and 3.20 without, sixteen 0.303 and 0.469 each); a cut beyond its room counts
+        // by how far it is beyond
         const double t = gang_cost<R>(B, cls, g) * (kGangMaxWgs % g == 0 ? 1.0 : 1.2);
         const double c = g == 1 || t * g <= room ? t : 1000.0 * t * g;
         if (best.g == 0 || c < cost) {
