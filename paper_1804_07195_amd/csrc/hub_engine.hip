@@ -1028,10 +1028,14 @@ bool Engine::gang_entry(GangList& G, int (&taken)[kNumXcd], System* s, bool sing
 
 // Gang launches over the systems of v, as many systems to a launch as the device has CUs
 // for: every workgroup of a launch has to be on the device for its gang to meet.  Systems
-// whose gang keeps missing its meetings come first, in steps, which need no meeting.
+// whose gang keeps missing its meetings come first, in steps, which need no meeting.  The
+// others go by their shift, so that those of a launch stop at about the same time: its CUs
+// are taken until the last one does.  (64 systems of 11x88x22 with four shifts in any order,
+// FP64: 28.8 ms as they come, 20.2 ms by shift, 24.7 ms with the tiled kernels.)
 hipError_t Engine::launch_gangs(const std::vector<System*>& v, bool single, Block& b) {
   std::vector<System*> meet, step;
   for (System* s : v) (s->gang_steps > 0 ? step : meet).push_back(s);
+  std::stable_sort(meet.begin(), meet.end(), [](const System* a, const System* b) { return a->mu2 < b->mu2; });
   for (int steps = 1; steps >= 0; --steps) {
     const std::vector<System*>& w = steps ? step : meet;
     for (size_t q = 0; q < w.size();) {

@@ -519,7 +519,49 @@ void cus_of_the_stream() {
   }
 }
 
+// Systems that stop at about the same time share a launch, in whatever order they are given:
+// a launch holds its CUs until its last system is through.
+void like_with_like() {
+  dev = Device{};
+  dev.resid2 = 0.0;
+  int launches = 0, mixed = 0;
+  std::map<double, int> seen;
+  dev.gang = [&](const SysDesc* sys, const GangList& L, int, bool) {
+    ++launches;
+    bool same = true;
+    for (int k = 0; k < L.nsys; ++k) {
+      const SysDesc& d = sys[L.sys[k]];
+      same = same && d.mu2 == sys[L.sys[0]].mu2;
+      CHECK(L.pi[k] == S_X && L.tag[k] == 0 && L.seq[k] == 1);
+      ++seen[d.mu2];
+      stop(L.scal[L.sys[k]]);
+    }
+    mixed += same ? 0 : 1;
+  };
+  Pool pool(0, (size_t)64 << 30);
+  Engine eng(&pool, nullptr);
+  std::vector<System> s;
+  const double shifts[4] = {0.1, 0.0, 1.0, 0.01};
+  for (int k = 0; k < 40; ++k) {
+    s.push_back(system_of(12, 12, 32, HUB_CG_FP64));
+    s.back().mu2 = shifts[(k * k + k / 3) % 4];
+  }
+  std::vector<System*> all;
+  std::vector<void*> owned;
+  bool room = false;
+  for (System& q : s) {
+    CHECK(eng.add(&q) == Engine::ADD_OK);
+    all.push_back(&q);
+  }
+  CHECK(eng.join_gangs(all, owned, room) == hipSuccess && room);
+  for (int k = 0; k < 3 && launches == 0; ++k) CHECK(eng.step() == hipSuccess);
+  CHECK(launches == (40 * s[0].desc.gang.g + 255) / 256 && mixed < (int)seen.size());
+  for (System& q : s) eng.remove(&q, &owned);
+  pool.release_all(owned, nullptr);
+}
+
 const std::map<std::string, void (*)()> scenarios = {
+    {"like_with_like", like_with_like},
     {"cus_of_the_stream", cus_of_the_stream},
     {"turns", turns},
     {"kernels_by_request", kernels_by_request},

@@ -29,7 +29,7 @@ def exe(tmp_path_factory):
 
 @pytest.mark.parametrize("scenario", ["lost_publication", "refusal_keeps_cache", "tables_of_fields",
                                       "gang_without_an_answer", "gangs_that_never_meet", "kernels_by_request",
-                                      "turns", "cus_of_the_stream"])
+                                      "turns", "cus_of_the_stream", "like_with_like"])
 def test_engine(exe, scenario):
     r = subprocess.run([exe, scenario], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout
