@@ -456,9 +456,15 @@ hub_status hub_apply_normal(hub_ctx* ctx, const hub_lattice* lat, const double* 
   }
   HUB_HIP(hipSetDevice(ctx->device), "hipSetDevice");
   const Geom g = make_geom(*lat);
-  double2* ws = (double2*)ctx->pool->alloc(normal_scratch(g, batch), stream);
+  size_t bytes = normal_scratch(g, batch);
+  double2* ws = (double2*)ctx->pool->alloc(bytes, stream);
+  if (!ws) {
+    bytes = normal_scratch(g, batch, true);
+    ws = (double2*)ctx->pool->alloc(bytes, stream);
+    if (ws) set_error("");
+  }
   if (!ws) return fail(HUB_ERR_OOM, "workspace for the normal operator");
-  const hipError_t e = launch_normal(g, phi, ws, m2, (const double2*)x, (double2*)y, batch, stream);
+  const hipError_t e = launch_normal(g, phi, ws, bytes, m2, (const double2*)x, (double2*)y, batch, stream);
   ctx->pool->release(ws, stream);
   if (e != hipSuccess) return hip_fail(e, "normal operator launch");
   return HUB_OK;
@@ -486,7 +492,8 @@ hub_status hub_apply_normal_noalloc(hub_ctx* ctx, const hub_lattice* lat, const 
   if (!ctx->scratch) return fail(HUB_ERR_HIP, "no scratch address for this device");
   HUB_HIP(hipSetDevice(ctx->device), "hipSetDevice");
   // the kernels of hub_apply_normal on the scratch (every entry written before it is read)
-  const hipError_t e = launch_normal(g, phi, (double2*)ctx->scratch, m2, (const double2*)x, (double2*)y, batch, stream);
+  const hipError_t e = launch_normal(g, phi, (double2*)ctx->scratch, HUB_NOALLOC_SCRATCH_BYTES, m2, (const double2*)x,
+                                     (double2*)y, batch, stream);
   if (e != hipSuccess) return hip_fail(e, "normal operator launch");
   return HUB_OK;
 }

@@ -317,9 +317,10 @@ hipError_t launch_phase_jobs(const PhaseJobs& J, int njob, int n, hipStream_t st
 // p64 = (cos phi, sin phi) in FP64 and, if p32 is not NULL, phi reduced to [-pi, pi]
 // and rounded to float (the complex64 kernels evaluate the phase from it).
 hipError_t launch_phase(const double* phi, double2* p64, float* p32, int n, hipStream_t st);
-// y_b = (M M^dagger + mu2_b) x_b; ws: normal_scratch(g, batch) bytes (the phases, or M^dagger x).
-size_t normal_scratch(const Geom& g, int batch);
-hipError_t launch_normal(const Geom& g, const double* phi, double2* ws, const double mu2_host[kMaxSys],
+// y_b = (M M^dagger + mu2_b) x_b; ws: normal_scratch(g, batch) bytes (the phases, or M^dagger x),
+// or the least that does (the phases).
+size_t normal_scratch(const Geom& g, int batch, bool least = false);
+hipError_t launch_normal(const Geom& g, const double* phi, double2* ws, size_t ws_bytes, const double mu2_host[kMaxSys],
                          const double2* x, double2* y, int batch, hipStream_t st);
 // phi += eps pi;  pi -= G + cg phi (G may be NULL).
 hipError_t launch_md_drift(double* phi, const double* pi, double eps, int n, hipStream_t st);

@@ -2106,21 +2106,31 @@ hipError_t launch_ms_iter(const MsDesc* d, int ntiles, int it, hipStream_t st) {
   return hipGetLastError();
 }
 
-// One pass pays for the phases' kernel where a workgroup takes two vectors or more; with one
-// (a batch of one, or lattices that need a workgroup per vector to fill the device) two passes
-// are faster: 102x102x64, one vector 25.6 us against 31.2; 48x48x64 11.7 against 13.4;
-// 24x24x64, four vectors 12.0 against 13.4.  Both give the same bits.
-static int normal_group(int n, int batch) { return pub_group((n + kBlock - 1) / kBlock, batch); }
+// One pass pays for the phases' kernel where the batch is large: from a million sites of all
+// vectors on, from half as many with six vectors or more (microseconds of the kernels in two
+// passes and in one, buffers resident; rotated: one pass gains more).  Below: 30x30x128, three
+// vectors 13.8, 16.9; 90x60x40, two 16.1, 18.0; 24x24x64, five 9.9, 10.2; 102x102x64, one 25.6,
+// 31.2.  Above: 30x30x128, five 21.7, 19.3, eight 28.5, 23.4; 64x64x64, two 19.8, 18.8;
+// 24x24x64, eight 12.7, 11.9; 102x102x64, two 38.6, 35.8.  Both give the same bits.
+static bool normal_one_pass(int n, int batch) {
+  return batch > 1 && (long)n * batch >= (batch < 6 ? 1L << 20 : 1L << 19);
+}
 
-size_t normal_scratch(const Geom& g, int batch) { return (size_t)g.n * 16 * (normal_group(g.n, batch) > 1 ? 1 : batch); }
+size_t normal_scratch(const Geom& g, int batch, bool least) {
+  return (size_t)g.n * 16 * (least || normal_one_pass(g.n, batch) ? 1 : batch);
+}
 
-hipError_t launch_normal(const Geom& g, const double* phi, double2* ws, const double mu2_host[kMaxSys],
+hipError_t launch_normal(const Geom& g, const double* phi, double2* ws, size_t ws_bytes, const double mu2_host[kMaxSys],
                          const double2* x, double2* y, int batch, hipStream_t st) {
   Mu2Arr m;
   for (int b = 0; b < kMaxSys; ++b) m.v[b] = b < batch ? mu2_host[b] : 0.0;
-  const int per = normal_group(g.n, batch);
-  if (per > 1) {
+  if (normal_one_pass(g.n, batch) || ws_bytes < (size_t)g.n * 16 * batch) {
     const int nt = (g.n + kBlock - 1) / kBlock;
+    // groups of even size: seven vectors and one in two groups took as long as two of seven
+    // (30x30x128, eight vectors 34.7 us, 23.4 with four and four)
+    int per = pub_group(nt, batch);
+    const int groups = (batch + per - 1) / per;
+    per = (batch + groups - 1) / groups;
     hipLaunchKernelGGL(k_phase_pub, dim3(nt), dim3(kBlock), 0, st, phi, ws, g.n);
     hipLaunchKernelGGL(k_normal_pub, dim3(nt * ((batch + per - 1) / per)), dim3(kBlock), 0, st, g, ws, m, x, y, nt, per,
                        batch);

@@ -88,10 +88,11 @@ hipError_t launch_force(const Geom&, const double*, const double2*, const double
 hipError_t launch_dot_re(const Geom&, const double2*, const double2*, int, double*, double*, hipStream_t) { return hipSuccess; }
 hipError_t launch_phase(const double*, double2*, float*, int, hipStream_t) { return hipSuccess; }
 hipError_t launch_phase_jobs(const PhaseJobs&, int, int, hipStream_t) { return hipSuccess; }
-hipError_t launch_normal(const Geom&, const double*, double2*, const double*, const double2*, double2*, int, hipStream_t) {
+hipError_t launch_normal(const Geom&, const double*, double2*, size_t, const double*, const double2*, double2*, int,
+                         hipStream_t) {
   return hipSuccess;
 }
-size_t normal_scratch(const Geom& g, int batch) { return (size_t)g.n * 16 * batch; }
+size_t normal_scratch(const Geom& g, int batch, bool least) { return (size_t)g.n * 16 * (least ? 1 : batch); }
 hipError_t launch_force_sum(const Geom&, const double*, const double2*, const double2*, const double*, int, double*, int,
                             hipStream_t) {
   return hipSuccess;
