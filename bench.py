@@ -253,30 +253,26 @@ def main():
 
     # dominant kernel of the step (largest summed time among the timed CG kernels)
     dom_name, dom = max(prof.items(), key=lambda kv: kv[1]["total_ms"])
-    # The gang CG keeps its vectors in registers and LDS, so it has no algorithmic HBM bytes per
-    # iteration.  What is reported for it is the rate at which the two tiled kernels of an
-    # iteration would have to stream their vectors to finish in the same time (84 and 184
-    # bytes per site, odd and even iterations averaged); its own bound is the exchange between
-    # workgroups, once per iteration.
+    # The gang CG keeps its vectors in registers and LDS: no algorithmic HBM bytes, no rate.  What
+    # is reported for it is the time of an iteration.
     gang = dom_name.startswith("cgwg_")
-    if gang:
-        per_site = 84.0 if dom_name.endswith("c64") else 184.0
-        dom = dict(dom, bytes=per_site * w.nsites * prof_steps * sum(i["inner_iters"] for i in last_info))
-        dom["GBps"] = dom["bytes"] / (dom["total_ms"] * 1e6)
-    achieved = dom["GBps"]
+    achieved = None if gang else dom["GBps"]
     traffic = measured_traffic(dom_name)
-    roofline = {"bound": "exchange latency (HBM rate of the tiled iteration that takes as long)" if gang else "hbm", "kernel": dom_name, "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS,
+    roofline = {"bound": "waits between workgroups and vector ALU" if gang else "hbm", "kernel": dom_name,
+                "achieved": None if gang else round(achieved, 1), "peak": HBM_PEAK_GBPS,
                 "unit": "GB/s", "frac": None if gang else round(achieved / HBM_PEAK_GBPS, 4),
                 "traffic": None if traffic is None else round(traffic),
                 "avg_launch_us": round(dom["avg_us"], 3), "launches": dom["launches"],
+                "us_per_iteration": round(1e3 * dom["total_ms"] / (prof_steps * sum(i["inner_iters"] for i in last_info)),
+                                          3) if gang else None,
                 "timed_over": f"{prof_steps} steps after the timed region, HIP events bound to every launch",
-                "alg_bytes_per_launch": round(dom["bytes"] / max(dom["launches"], 1)),
+                "alg_bytes_per_launch": None if gang else round(dom["bytes"] / max(dom["launches"], 1)),
                 # what the complex64 CG of the step keeps live per iteration (r, the p pair, u,
                 # the solution z_j, the float angle: 44 bytes per site and system) against the
                 # infinity cache: the bytes above are algorithmic, and while the working set fits
                 # in the cache much of that traffic is served from it rather than from DRAM
                 "working_set_bytes": int(44 * w.nsites * w.batch), "infinity_cache_bytes": MALL_BYTES}
-    if traffic is not None:
+    if traffic is not None and not gang:
         roofline["traffic_over_alg"] = round(traffic / max(roofline["alg_bytes_per_launch"], 1), 4)
 
     m_apply = apply_measure(ctx, hb, torch, w, hl, pd, ed)
