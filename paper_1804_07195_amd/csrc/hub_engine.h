@@ -155,8 +155,9 @@ struct System {
 };
 
 // Drives any number (<= kMaxSys) of systems of any lattice sizes to convergence on
-// one stream.  Systems iterate together: every CG iteration is one pair of launches
-// over all systems currently iterating, whatever their phase or shape.
+// one stream.  Systems iterate together, whatever their phase or shape: by gangs, as many of
+// them to a launch as the device has CUs for, or by the tiled kernels, one pair of launches
+// per iteration over all systems that use them.
 class Engine {
  public:
   Engine(Pool* pool, hipStream_t st);

@@ -1499,17 +1499,12 @@ __global__ __launch_bounds__(kBlock) void k_ms2(const MsDesc* __restrict__ d, in
   if (threadIdx.x == 0) Real<double>(d->part2).set(tile, tot);
 }
 
-template <typename Tin> __device__ __forceinline__ double2 to_c128(Tin v);
-template <> __device__ __forceinline__ double2 to_c128<double2>(double2 v) { return v; }
-template <> __device__ __forceinline__ double2 to_c128<float2>(float2 v) {
+__device__ __forceinline__ double2 to_c128(float2 v) {
   double2 o;
   o.x = v.x;
   o.y = v.y;
   return o;
 }
-
-
-
 
 // Scal records to host-coherent memory in 8-byte words, every store arrived there before the
 // flag is written.
@@ -1802,7 +1797,7 @@ __global__ __launch_bounds__(kBlock) void k_arnoldi_dots(const SysDesc* __restri
     f.y = (float)a.y;
     return f;
   };
-  auto ld = [=](int k) { return to_c128<float2>(FROM_W ? single(scaled(k)) : z[k]); };
+  auto ld = [=](int k) { return to_c128(FROM_W ? single(scaled(k)) : z[k]); };
 #pragma unroll 2
   for (int m = 0; m < SPT; ++m) {
     const int n = base + m * kBlock;
