@@ -983,11 +983,12 @@ hipError_t Engine::take_event(std::vector<hipEvent_t>& dst) {
   return hipSuccess;
 }
 
-// System s joins the launch G, of whose blocks `taken` are given away per XCD; false: no room.  Blocks go to the XCDs in turn (block b to
-// XCD b mod 8), so a gang takes its blocks with a stride, consecutive workgroups on one XCD:
-// a reduction among 16 workgroups takes 2.0 us on one XCD and 2.45 us over all.  More than
-// about a dozen of one gang on an XCD get into each other's way (the FP64 iteration of a
-// 48x48x64 system 8.1 us with 28 on each of five XCDs, 7.0 us with 18 on each of eight).
+// System s joins the launch G, of whose blocks `taken` are given away per XCD; false: no room.
+// Blocks go to the XCDs in turn (block b to XCD b mod 8), so a gang takes its blocks with a
+// stride, consecutive workgroups on one XCD: a reduction among 16 workgroups by itself takes
+// 2.0 us on one XCD and 2.45 us over all.  More than about a dozen of one gang on an XCD get
+// into each other's way (the FP64 iteration of a 48x48x64 system cut in some 140 blocks 8.1 us
+// with 28 on each of five XCDs, 7.0 us with 18 on each of eight).
 bool Engine::gang_entry(GangList& G, int (&taken)[kNumXcd], System* s, bool single) const {
   constexpr int kPer = kGangMaxWgs / kNumXcd;  // blocks per XCD
   constexpr int kSpread = 12;                  // workgroups of a gang per XCD, while others are free

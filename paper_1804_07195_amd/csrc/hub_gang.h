@@ -281,9 +281,9 @@ __host__ __device__ inline size_t gang_state_words(int g, int cls) {
 // Time of one CG iteration of a cut in microseconds, fitted to measurements (complex64 /
 // complex128; one workgroup 0.95 to 1.3 with one site per thread, 1.5 / 2.2 at 6x6x16;
 // 12x12x32 3.25 / 4.7 with 8 workgroups and 2.95 / 3.6 with 16; 24x24x64 3.5 / 5.0 with 64;
-// 48x48x64 4.8 with 128, 4.2 / 6.2 with 256; 102x102x64 8.9 with 256; several workgroups
-// have become 0.1 to 0.3 faster since): the arithmetic of the largest block, and with more
-// than one workgroup a reduction and an exchange of faces.
+// 48x48x64 4.8 with 128, 4.2 / 6.2 with 256; 102x102x64 8.9 with 256, when it was fitted): the
+// arithmetic of the largest block, and with more than one workgroup a reduction and an
+// exchange of faces.
 template <typename R>
 inline double gang_cost(const GangBlock& B, int cls, int g) {
   constexpr bool single = sizeof(R) == 4;

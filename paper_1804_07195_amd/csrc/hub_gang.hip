@@ -21,10 +21,11 @@
 // their halo, so what they wait for is the faces of w, which travel with the reduction.
 //
 // Microseconds per iteration, before (tiled, or one workgroup per small complex64 system) and
-// here: 12x12x32 7.1 complex64, 13.6 FP64 (16 systems) -> 2.85 and 3.64 for one, 3.1 and 4.9
-// for the sixteen; 24x24x64 complex64 11 -> 3.35; 48x48x64 13 and 15 -> 4.0 and 6.4; 102x102x64
-// complex64 26 -> 8.8.  A round of records and faces without the arithmetic takes 2.1 with
-// 16 workgroups, 2.3 with 64, 4.1 with 256 (800 faces each) and 7.4 with 256 and 2,600.
+// here: 12x12x32 7.1 complex64, 13.6 FP64 (16 systems) -> 2.95 and 3.6 for one, 3.1 and 4.75
+// for the sixteen; 24x24x64 complex64 11 -> 3.4; 48x48x64 13 and 15 -> 4.0 and 6.4; 102x102x64
+// complex64 26 -> 8.5.  By its counters the waves wait for 45% (102x102x64) to 66% (sixteen
+// systems in FP64) of the time, for the words of other workgroups and at four barriers, and
+// the vector ALU issues in 50% to 23% of its cycles.
 //
 // A gang needs all its workgroups on the device at once.  They meet at the start of a
 // launch before they change anything; a gang that does not fit beside others is refused
@@ -268,8 +269,8 @@ __device__ __forceinline__ void gang_run(const SysDesc* __restrict__ d, Scal* sc
   constexpr bool ZMEM = CLS == GangTab<R>::n - 1;
   // Two bonds of a site share a register where a register per bond would not fit.
   constexpr bool PACK = single ? M > 8 : M > 3;
-  // The small bodies have registers for every address (12x12x32: 3.1 us an iteration when they
-  // work them out anew, 2.9 us when not); the others do not (FP64 at 48x48x64: 6.6, 8.6).
+  // The small bodies have registers for every address (12x12x32: an iteration takes 7% longer
+  // when they work them out anew); the others do not (FP64 at 48x48x64: 30% longer with them).
   constexpr bool KEEP = M <= (single ? 3 : 2);
   constexpr int sR = single ? (int)S_R32 : (int)S_R;
   double2* const red = reinterpret_cast<double2*>(lds);        // (gamma, |u|^2) of each wave
@@ -833,14 +834,21 @@ __device__ __forceinline__ void gang_run(const SysDesc* __restrict__ d, Scal* sc
       }
       return;
     }
-    double uu, beta, alpha;
-    totals(gamma, uu);
+    // totals and step_of, written out: called here, they make the bodies of three sites 1%
+    // slower (24x24x64 complex64 3.34 and 3.38 us)
+    gamma = red2[0].x;
+    double uu = red2[0].y;
+    for (int k = 1; k < nw; ++k) {
+      gamma += red2[k].x;
+      uu += red2[k].y;
+    }
     // the stopping test of iteration it (at it = 0 the CG setup decided)
     if (it > 0 && (!(gamma > stop2) || it >= maxit)) {
       stopped = true;
       break;
     }
-    step_of(it, gamma, uu, beta, alpha);
+    const double beta = it == 0 ? 0.0 : gamma / gamma_prev;
+    const double alpha = gamma / (fma(mu2, gamma, uu) - (it == 0 ? 0.0 : beta * gamma / alpha_prev));
     const R rb = (R)beta, ra = (R)alpha;
     o = advance(v, rb, ra);
     put_own(r, o);
