@@ -275,7 +275,7 @@ class Server {
     s.on_done = [this, t](System* sp) { complete(t, sp); };
     s.ph64 = nullptr;
     s.ph32 = nullptr;
-    const size_t ws = Engine::workspace_bytes(s.g, s.opts), gang = engine_->gang_bytes(s);
+    const size_t ws = Engine::workspace_bytes(s.g, s.opts), gang = engine_->gang_bytes({&s});
     const bool by_gang = gang > 0 && ws + gang <= pool.budget();
     ++pool.requests;
     if (pool.waiting > 0 || pool.in_use() + ws + (by_gang ? gang : 0) > pool.budget()) {
@@ -567,11 +567,14 @@ hub_status run_solves(hub_ctx* ctx, std::vector<System>& sys, const hub_solve_op
   if (result == HUB_OK) {
     std::vector<System*> all;
     for (System& sy : sys) all.push_back(&sy);
-    // room that served requests hold is waited for: they end without anything of this call
+    // room that served requests hold is waited for (they end without anything of this call),
+    // unless the call would not fit without them either
     Pool& pool = *ctx->pool;
+    size_t need = eng->gang_bytes(all);
+    for (const System& sy : sys) need += sy.bytes;
     ++pool.waiting;
     for (bool room = false, others = true; !room && others && result == HUB_OK;) {
-      others = pool.requests > 0;
+      others = need <= pool.budget() && pool.requests > 0;
       const hipError_t e = eng->join_gangs(all, owned, room);
       if (e != hipSuccess) result = hip_fail(e, "solve");
       if (!room && others) std::this_thread::sleep_for(std::chrono::microseconds(50));

@@ -149,6 +149,7 @@ struct System {
   double bnorm = 0.0, err = 0.0, wnorm = 0.0, rnorm_cycle = 0.0, bb = -1.0;
   std::vector<std::complex<double>> H;  // (m+1) x m, column-major
   std::vector<void*> owned;             // workspace blocks of this system
+  size_t bytes = 0;                     // what they take of the budget
   SysDesc desc{};
   std::function<void(System*)> on_done; // serving: S, force and completion
   void* user = nullptr;
@@ -168,8 +169,9 @@ class Engine {
   // the workspace is over budget; ADD_HIP: a HIP call failed while joining.
   enum AddResult { ADD_OK = 0, ADD_NO_ROOM = 1, ADD_HIP = 2 };
   AddResult add(System* s);
-  // Bytes of the budget that a system like s takes for its gang (0: its lattice has no cut).
-  size_t gang_bytes(const System& s);
+  // Bytes of the budget that systems like these take for their gangs, in one block (0: no
+  // lattice of theirs has a cut).
+  size_t gang_bytes(const std::vector<System*>& v);
   // Let the systems of v that have just been added iterate by gangs, where their lattice has a
   // cut; their memory is one block, appended to `owned`.  room = false: the budget has none
   // just now, nothing was done and the systems keep the tiled kernels.  They also do should

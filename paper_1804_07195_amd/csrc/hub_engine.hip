@@ -361,9 +361,11 @@ Engine::AddResult Engine::add(System* s) {
   d.tseg = tg.seg;
   d.ntiles = tg.ntiles;
   d.sc = d_scal_ + slot;
+  s->bytes = 0;
   auto get = [&](size_t bytes) -> void* {
     void* p = pool_->alloc(bytes, st_);
     if (p) s->owned.push_back(p);
+    if (p) s->bytes += Pool::rounded(bytes);
     return p;
   };
   bool ok = true, hip_ok = true;
@@ -464,11 +466,15 @@ static size_t state(const GangCut& c, bool single) {
   return single ? gang_state_words<float>(c.g, c.cls) : gang_state_words<double>(c.g, c.cls);
 }
 
-size_t Engine::gang_bytes(const System& s) {
+size_t Engine::gang_bytes(const std::vector<System*>& v) {
   look_at_device();
-  const bool single = is_fgmres(s.opts);
-  const GangCut c = cut_of(s.g, single);
-  return c.g > 0 ? Pool::rounded((state(c, single) + (c.g > 1 ? exch(c, single) : 0)) * 8) : 0;
+  size_t words = 0;
+  for (System* s : v) {
+    const bool single = is_fgmres(s->opts);
+    const GangCut c = cut_of(s->g, single);
+    if (c.g > 0) words += state(c, single) + (c.g > 1 ? exch(c, single) : 0);
+  }
+  return words > 0 ? Pool::rounded(words * 8) : 0;
 }
 
 hipError_t Engine::join_gangs(const std::vector<System*>& v, std::vector<void*>& owned, bool& room) {

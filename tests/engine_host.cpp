@@ -364,7 +364,8 @@ void kernels_by_request() {
     const System s = system_of(12, 12, 32, solver);
     const size_t ws = Engine::workspace_bytes(s.g, s.opts);
     Pool pool(0, kPlenty);
-    const size_t gang = Engine(&pool, nullptr).gang_bytes(s);
+    System like = s;
+    const size_t gang = Engine(&pool, nullptr).gang_bytes({&like});
     bool seen[2] = {false, false};
     for (double part : {1.0, 1.2, 1.5, 2.0, 2.5, 3.0, 3.7, 4.0, 5.0, 100.0}) {
       dev = Device{};
@@ -421,6 +422,32 @@ void kernels_by_request() {
     CHECK(hub_solve(ctx, &c.r.lat, c.r.phi, &c.r.mu2, 1, c.r.chi, c.r.x_out, &c.r.opts, &info, nullptr) == HUB_OK);
     CHECK(path[0.7] == "gang ");
     CHECK(r.wait(ctx) == HUB_OK);
+    CHECK(hub_destroy(ctx) == HUB_OK);
+    // one that would not fit without it either does not wait: the request ends after the call
+    path.clear();
+    served = 0;
+    std::atomic<bool> returned{false};
+    dev.gang = [&](const SysDesc* sys, const GangList& L, int, bool) {
+      for (int k = 0; k < L.nsys; ++k) {
+        ++served;
+        note(sys[L.sys[k]].mu2, "gang ");
+        if (returned) stop(L.scal[L.sys[k]]);
+      }
+    };
+    const int many = 8;
+    System small = system_of(6, 6, 64, solver);
+    const size_t others = Engine::workspace_bytes(small.g, small.opts) + Engine(&pool, nullptr).gang_bytes({&small});
+    CHECK(hub_create(&ctx, 0, many * ws + others) == HUB_OK);
+    Request r2(6, 6, 64, 0.1, solver);
+    r2.submit(ctx);
+    while (served == 0) std::this_thread::yield();
+    std::vector<hub_c128> b(many * c.x.size()), x(many * c.x.size());
+    std::vector<hub_solve_info> infos(many);
+    const std::vector<double> mu2(many, 0.7);
+    CHECK(hub_solve(ctx, &c.r.lat, c.r.phi, mu2.data(), many, b.data(), x.data(), &c.r.opts, infos.data(), nullptr) == HUB_OK);
+    CHECK(path[0.7] == "tiled ");
+    returned = true;
+    CHECK(r2.wait(ctx) == HUB_OK && path[0.1] == "gang ");
     CHECK(hub_destroy(ctx) == HUB_OK);
   }
 }
@@ -511,7 +538,7 @@ void cus_of_the_stream() {
       std::vector<void*> owned;
       bool room = false;
       const bool want = L == 6 || c.second >= 256;
-      CHECK((eng.gang_bytes(s) > 0) == want);
+      CHECK((eng.gang_bytes({&s}) > 0) == want);
       CHECK(eng.add(&s) == Engine::ADD_OK);
       CHECK(eng.join_gangs({&s}, owned, room) == hipSuccess && room);
       CHECK(s.gang == want && (s.desc.gang.g == 1) == (L == 6));
