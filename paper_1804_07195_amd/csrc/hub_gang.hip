@@ -21,8 +21,8 @@
 // their halo, so what they wait for is the faces of w, which travel with the reduction.
 //
 // Microseconds per iteration, before (tiled, or one workgroup per small complex64 system) and
-// here: 12x12x32 7.1 complex64, 13.6 FP64 (16 systems) -> 2.95 and 3.6 for one, 3.1 and 4.75
-// for the sixteen; 24x24x64 complex64 11 -> 3.4; 48x48x64 13 and 15 -> 4.0 and 6.4; 102x102x64
+// here: 12x12x32 7.1 complex64, 13.6 FP64 (16 systems) -> 2.9 and 3.6 for one, 3.1 and 4.75
+// for the sixteen; 24x24x64 complex64 11 -> 3.35; 48x48x64 13 and 15 -> 4.0 and 6.4; 102x102x64
 // complex64 26 -> 8.5.  By its counters the waves wait for 45% (102x102x64) to 66% (sixteen
 // systems in FP64) of the time, for the words of other workgroups and at four barriers, and
 // the vector ALU issues in 50% to 23% of its cycles.
