@@ -155,7 +155,8 @@ typedef struct {
  * filled on return.  opts may be NULL (defaults).  Synchronises `stream`.
  * Returns HUB_ERR_NOCONV if any system missed tol (x holds its last iterate).
  * The same call on a context of the same budget gives the same bits, whatever else runs
- * on the device (a call that finds the budget held by served requests waits for these). */
+ * on the device (a call that finds the budget held by served requests waits for these),
+ * unless the device itself has less memory left than the budget promises. */
 hub_status hub_solve(hub_ctx *ctx, const hub_lattice *lat, const double *phi, const double *mu2,
                      int32_t batch, const hub_c128 *b, hub_c128 *x, const hub_solve_opts *opts,
                      hub_solve_info *info, hipStream_t stream);
