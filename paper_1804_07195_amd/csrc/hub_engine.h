@@ -108,8 +108,9 @@ constexpr int kTailBlock = 4;
 // and the requests together 2 to 3% longer.
 constexpr int kGangIters = 128, kGangItersAlone = 512;
 // Meetings in a row that a gang may miss (or be refused) before it goes on in steps; and how:
-// blocks of so many iterations, one of them before the next attempt to meet, twice as many
-// after each attempt that fails, up to kGangStepBlocks.
+// blocks of so many iterations (half a millisecond; an attempt takes 2 ms to fail), one of
+// them before the next attempt to meet, twice as many after each attempt that fails, up to
+// kGangStepBlocks.
 constexpr int kGangMisses = 3, kGangSteps = 16, kGangStepBlocks = 64;
 
 // Host-side state of one linear system (M M^dagger + mu2) x = b.
